@@ -137,13 +137,17 @@ uint32_t magic_for(uint32_t g)
 }
 
 // Fills a BoxSide (everything but the LDS layout).
-void fill_side(BoxSide& b, const Side& s, const std::vector<uint64_t>& ptr, const uint64_t* off, const SidePlan& sp,
-               const Record& r)
+void fill_side(BoxSide& b, const Side& s, const std::vector<uint64_t>& ptr, const uint64_t* off, const uint32_t* shift,
+               const SidePlan& sp, const Record& r)
 {
     std::memset(&b, 0, sizeof(b));
+    uint64_t st = 1;
     for (uint32_t k = 0; k < s.rank; k++) {
-        b.offset[k] = off[k];
-        b.extent[k] = s.extents[k];
+        const uint32_t d = s.lin == LLAMA_COL_MAJOR ? k : s.rank - 1 - k; // fastest first
+        b.offset[d] = off[d];
+        b.stride[d] = st;
+        b.base += (off[d] - shift[d]) * st; // modulo 2^64: a frame may begin before the view
+        st *= s.extents[d];
     }
     b.blob = ptr.empty() ? 0 : ptr[0];
     b.npad = s.npad;
@@ -161,6 +165,51 @@ void fill_side(BoxSide& b, const Side& s, const std::vector<uint64_t>& ptr, cons
         b.block = s.block;
         b.log2_lanes = log2u(s.lanes);
     }
+}
+
+// How a leaf's values go to a field-major or AoSoA destination
+// (BoxEntry::dst): in 16-byte granules where they fill them on the
+// destination's grid and a run has at least one, else value by value.
+uint32_t granule_bits(const BoxSide& d, const Side& D, uint64_t addr, uint32_t size)
+{
+    if (size > 8 || (size & (size - 1)) != 0 || addr % size != 0)
+        return 0;
+    const uint32_t lgper = 4 - log2u(size);
+    if (lgper > d.run_log2)
+        return 0;
+    if (d.mode != kFieldMajor) // lane runs of whole granules, at 4-byte aligned addresses
+        return addr % 4 == 0 && d.block % 4 == 0 && (D.lanes * size) % 16 == 0 ? lgper << 4 : 0u;
+    return (lgper << 4) | (uint32_t(addr % 16 / size) << 8);
+}
+
+// log2 of the alignment of x, at most 4 (16 bytes).
+uint32_t align_bits(uint64_t x)
+{
+    return uint32_t(__builtin_ctzll(x | 16));
+}
+
+// Bit b of a record's place in the tile's destination order (run index above
+// the element) to its bit in the source order: both orders number the tile's
+// coordinates by their bits, so one is a permutation of the other's.
+void order_bits(const BoxHeader& h, uint32_t order, std::vector<uint32_t>& out)
+{
+    // out[b] = coordinate bit (dimension * 32 + bit) that is bit b of the place
+    const int r = int(h.rank);
+    const int fast = order == kOrderRow ? r - 1 : order == kOrderCol ? 0 : -1;
+    out.clear();
+    if (order == kOrderMorton) {
+        for (uint32_t j = 0; j < h.qlog[0]; j++)
+            for (int d = r - 1; d >= 0; d--)
+                out.push_back(uint32_t(d) * 32 + j);
+        return;
+    }
+    if (fast >= 0)
+        for (uint32_t j = 0; j < h.qlog[fast]; j++)
+            out.push_back(uint32_t(fast) * 32 + j);
+    for (int d = r - 1; d >= 0; d--)
+        if (d != fast)
+            for (uint32_t j = 0; j < h.qlog[d]; j++)
+                out.push_back(uint32_t(d) * 32 + j);
 }
 
 // Builds the box plan for 2^qsum records per tile; false when its LDS does
@@ -194,8 +243,12 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
     for (uint32_t k = 0; k < rank; k++) {
         h.box[k] = box[k];
         const uint64_t q = uint64_t(1) << h.qlog[k];
-        h.shift[k] = anchor ? aoff[k] & (q - 1) : 0;
-        h.grid[k] = (box[k] + h.shift[k] + q - 1) >> h.qlog[k];
+        h.shift[k] = anchor ? uint32_t(aoff[k] & (q - 1)) : 0;
+        const uint64_t g = (box[k] + h.shift[k] + q - 1) >> h.qlog[k];
+        if (g >= (uint64_t(1) << 32))
+            fail(LLAMA_E_UNSUPPORTED, "a box copy of more than 2^32 tiles");
+        h.grid[k] = uint32_t(g);
+        h.gmagic[k] = g < 2 ? ~0u : uint32_t((uint64_t(1) << 32) / g);
     }
     auto aligned = [&](const uint64_t* off) {
         for (uint32_t k = 0; k < rank; k++)
@@ -207,8 +260,8 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
         ss.order = kOrderPoint;
     if (ds.order == kOrderMorton && !aligned(dof))
         ds.order = kOrderPoint;
-    fill_side(a.src, S, rq.src_ptr, so, ss, r);
-    fill_side(a.dst, D, rq.dst_ptr, dof, ds, r);
+    fill_side(a.src, S, rq.src_ptr, so, h.shift, ss, r);
+    fill_side(a.dst, D, rq.dst_ptr, dof, h.shift, ds, r);
     a.src.run_log2 = run_log2(ss.order, rank, h.qlog, h.qlog_sum);
     a.dst.run_log2 = run_log2(ds.order, rank, h.qlog, h.qlog_sum);
 
@@ -243,19 +296,51 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
     const uint64_t Q = uint64_t(1) << h.qlog_sum;
     const uint64_t Rs = Q / Ws, Rd = Q / Wd;
     uint64_t lds = 0; // source runs first
+    if (ss.field_major) {
+        // A run's slot begins at its start index rounded down to A records,
+        // whole granules of every leaf; it holds a run that starts up to A - 1
+        // records later, and A more where a leaf begins off the 16-byte grid
+        uint64_t A = 1;
+        bool off = false;
+        for (size_t f = 0; f < F; f++) {
+            while (A * r.leaves[f].size % 16 != 0)
+                A *= 2;
+            off = off || (rq.src_ptr[S.blob[f]] + S.base[f]) % 16 != 0;
+        }
+        a.src.amask = uint32_t(A - 1);
+        a.src.gran = uint32_t((Ws + A - 1 + A - 1) / A * A + (off ? A : 0));
+        if (budget != ~0u && Rs * a.src.gran > 16384) // a map entry's value number
+            return false;
+    }
     for (size_t f = 0; f < F; f++) {
         BoxEntry& e = a.e[f];
         const uint32_t sz = r.leaves[f].size;
         e.size = sz;
         e.dst_addr = rq.dst_ptr[D.blob[f]] + D.base[f];
         e.dst_off = uint32_t(D.base[f]);
+        if (!aos_dst)
+            e.dst = granule_bits(a.dst, D, e.dst_addr, sz);
+        // LDS positions keep their addresses' alignment: record-major values
+        // at the block, its stride and the leaf's offset, field-major ones at
+        // the leaf's address and the value size
+        const uint64_t sat = ss.field_major ? (rq.src_ptr[S.blob[f]] + S.base[f]) | sz
+                                            : rq.src_ptr[S.blob[f]] | S.base[f] | (ss.one ? 0 : S.block) |
+                                                  (S.lanes > 1 ? sz : 0);
+        const uint64_t dat = aos_dst ? rq.dst_ptr[0] | D.block | D.base[f] : 0;
+        e.dst |= align_bits(sat) << 12 | ((1u << align_bits(sat)) < sz ? 1u << 15 : 0u) | align_bits(dat) << 16;
         if (ss.field_major) {
             // leaf f's runs, one slot of `gran` granules each
             e.src_addr = rq.src_ptr[S.blob[f]] + S.base[f];
-            e.src_off = uint32_t(std::min<uint64_t>(lds, ~0u));
-            e.gran = round16(Ws * sz + 16) / 16;
-            e.magic = magic_for(e.gran);
-            lds += Rs * e.gran * 16;
+            e.src_off = uint32_t(std::min<uint64_t>(lds, 1u << 30)) + uint32_t(e.src_addr & 15);
+            e.gran = a.src.gran * sz / 16;
+            e.magic = e.gran > 1 ? magic_for(e.gran) : 0;
+            // a single run of a few granules more than whole chunks loads them
+            // with its last chunk (128 values of 8 bytes off the granule grid)
+            const uint32_t more = Rs == 1 && e.gran > 64 ? 8 : 0;
+            h.load_chunks = std::max(h.load_chunks, uint32_t((Rs * e.gran - more + 63) / 64));
+            // an odd number of granules from leaf to leaf, so that the words of
+            // a record in neighbouring leaves lie in different banks
+            lds += (Rs * e.gran | 1) * 16;
         } else {
             e.src_off = uint32_t(S.base[f]);
         }
@@ -263,7 +348,7 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
     if (aos_dst)
         for (size_t g = 0; g < D.gaps.size(); g++) {
             BoxEntry& e = a.e[F + g];
-            e.gap = 1;
+            e.dst = 1;
             e.dst_off = uint32_t(D.gaps[g].first);
             e.size = uint32_t(D.gaps[g].second);
         }
@@ -310,23 +395,55 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
             uint32_t e = kBoxWordZero;
             for (size_t f = 0; f < F; f++)
                 if (D.base[f] <= 4 * w && 4 * w < D.base[f] + r.leaves[f].size)
-                    e = uint32_t(f) | (uint32_t(4 * w - D.base[f]) << 8);
-            a.words[w] = e;
+                    e = uint32_t(f) | (uint32_t(4 * w - D.base[f]) / 4 << 8);
+            a.words[w] = uint16_t(e);
         }
         h.wtab = uint32_t(std::min<uint64_t>(lds, ~0u));
-        lds += ((h.words * 4 + 15) & ~15u) + F * 16;
+        lds += (h.words * 8 + 15) & ~15u;
     }
     h.map = uint32_t(std::min<uint64_t>(lds, ~0u));
-    lds += Q * 16;
+    lds += (Q * 4 + 15) & ~uint64_t(15);
     a.src.table = uint32_t(std::min<uint64_t>(lds, ~0u));
     lds += Rs * 8;
     a.dst.table = uint32_t(std::min<uint64_t>(lds, ~0u));
     lds += Rd * 8;
-    if (lds > budget)
+    // (a map entry holds lanes below 2^14 and, of a record-major source, LDS bytes below 2^16)
+    if (lds > budget || (budget != ~0u && (h.qlog_sum > 13 || (!ss.field_major && S.lanes > 16384))))
         return false;
+    std::vector<uint32_t> bs, bd;
+    order_bits(h, ss.order, bs);
+    order_bits(h, ds.order, bd);
+    for (size_t b = 0; ss.order != kOrderOne && b < bd.size(); b++)
+        h.perm |= uint64_t(std::find(bs.begin(), bs.end(), bd[b]) - bs.begin()) << (4 * b);
+    if (bs == bd)
+        h.flags |= kBoxSameOrder;
+    for (size_t k = 0; k < ne; k++) {
+        const uint32_t lgper = staged ? 0 : (a.e[k].dst >> 4) & 15;
+        h.store_chunks = std::max(h.store_chunks, uint32_t(((Q >> lgper) + 63) / 64));
+    }
+    h.load_magic = magic_for(std::max(h.load_chunks, 1u));
+    h.store_magic = magic_for(h.store_chunks);
     h.lds_bytes = uint32_t(lds);
     p.lds_bytes = h.lds_bytes;
     return true;
+}
+
+// Whether the smallest tile's values, runs and records fit `budget` bytes of
+// LDS when every run's slot begins at its own 16-byte granule of each leaf.
+bool bytes_fit(const Request& rq, const uint64_t* so, const uint64_t* dof, const uint64_t* box, bool full, bool preserve,
+               uint32_t budget, Plan& p)
+{
+    if (!try_plan(rq, so, dof, box, full, preserve, 1, ~0u, p))
+        return false;
+    const BoxArgs& a = p.box;
+    const uint64_t Q = uint64_t(1) << a.h.qlog_sum, Ws = uint64_t(1) << a.src.run_log2;
+    const uint64_t Rs = Q / Ws, Rd = Q >> a.dst.run_log2;
+    uint64_t lds = Q * 16 + (Rs + Rd) * 8;
+    for (const Leaf& l : rq.record.leaves)
+        lds += Rs * round16(Ws * l.size + 16);
+    if ((a.h.flags & (kBoxStaged | kBoxGather)) == kBoxStaged)
+        lds += Rd * a.dst.gran * 16;
+    return lds <= budget;
 }
 
 } // namespace
@@ -369,7 +486,7 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
             t += b;
         return t;
     }() : nbox * dst_rec;
-    if (want == LLAMA_PATH_NAIVE) {
+    auto naive = [&] {
         // the element-wise baseline: the same descriptors, one thread per
         // record (of the box, or of the destination's indices)
         if (!try_plan(rq, so, dof, box, full, preserve, 4, ~0u, p))
@@ -379,14 +496,40 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
         const uint64_t items = full ? D.npad : nbox;
         p.workgroups = (items + threads - 1) / threads;
         plans.push_back(p);
+    };
+    if (want == LLAMA_PATH_NAIVE) {
+        naive();
         return plans;
     }
-    // records per tile: about 16 KiB of source values, at least 64
-    uint32_t qsum = T ? log2u(T) : std::min<uint32_t>(12, std::max<uint32_t>(6, log2u(24576 / std::max<uint64_t>(r.packed_size, 1))));
+    // Records per tile, without a given size: about 24 KiB of source values
+    // (rounded up where the two sides' orders differ: a tile's runs are then
+    // its square root, and 1,024 particles in place of 512 took 252 to 199 us
+    // for 2^24 of them from row-major AoSoA8 into column-major AoSoA64), at
+    // most 40 KiB of LDS, so that four workgroups share a compute unit (listing
+    // 1's record into aligned AoS, 1,024 records in 60 KiB: 603 us, 512 in 30
+    // KiB: 336 us), and at least 64 records where 64 KiB hold them.
+    uint32_t qsum;
     const uint32_t budget = 64 * 1024;
+    if (T) {
+        qsum = log2u(T);
+    } else {
+        const uint64_t q = 24576 / std::max<uint64_t>(r.packed_size, 1);
+        const bool across = S.kind != LLAMA_ONE && S.lin != D.lin;
+        qsum = std::min<uint32_t>(12, std::max<uint32_t>(6, across ? log2_ceil(q) : log2u(q)));
+        while (qsum > 6 && !try_plan(rq, so, dof, box, full, preserve, qsum, 40 * 1024, p))
+            qsum--;
+    }
     while (!try_plan(rq, so, dof, box, full, preserve, qsum, budget, p)) {
-        if (qsum <= 1)
-            fail(LLAMA_E_UNSUPPORTED, "the record does not fit a box tile's LDS");
+        if (qsum <= 1) {
+            // a record too wide for a tile of two: element-wise while its
+            // bytes alone fit, which a field-major source's slots of whole
+            // granules of every leaf exceed sooner (leaves of 1 byte next to
+            // leaves of kilobytes)
+            if (S.lanes != 0 || S.kind == LLAMA_ONE || !bytes_fit(rq, so, dof, box, full, preserve, budget, p))
+                fail(LLAMA_E_UNSUPPORTED, "the record does not fit a box tile's LDS");
+            naive();
+            return plans;
+        }
         qsum--;
     }
     p.workgroups = p.box.h.num_units;

@@ -337,9 +337,10 @@ constexpr uint32_t kBatchLoadsOnce = 1;
 //   kOrderOne     a One source: a single run of its single record.
 // The source runs are loaded into LDS (a record-major side as the 16-byte
 // granules of the blocks a run touches, a field-major side per leaf); the
-// destination is written value by value from there (field-major and AoSoA
-// destinations), or through a destination region of whole records stored as
-// exact byte spans (AoS destinations).
+// destination is written from there in 16-byte granules of one leaf's values
+// (field-major and AoSoA destinations; value by value where a leaf's values
+// do not fill granules), or through a destination region of whole records
+// stored as exact byte spans (AoS destinations).
 // ---------------------------------------------------------------------------
 
 enum : uint32_t { kOrderRow = 0, kOrderCol = 1, kOrderMorton = 2, kOrderPoint = 3, kOrderOne = 4 };
@@ -349,7 +350,8 @@ constexpr int kBoxMaxEntries = 80;
 
 struct BoxSide {
     uint64_t offset[LLAMA_MAX_RANK]; // the box's origin in this view's coordinates
-    uint64_t extent[LLAMA_MAX_RANK]; // this view's extents
+    uint64_t stride[LLAMA_MAX_RANK]; // row- and column-major views: the linear index is sum of coordinate * stride
+    uint64_t base;     // linear index of the first tile's frame origin (row- and column-major views)
     uint64_t blob;     // record-major: device address of the blob
     uint64_t npad;     // linear indices the blob spans (loads and stores stay below)
     uint64_t block;    // K (record-major)
@@ -359,10 +361,14 @@ struct BoxSide {
     uint32_t order;    // kOrder*: how a tile's records form runs
     uint32_t morton_bits; // bits per dimension of the Morton index
     uint32_t run_log2; // log2 of a run's records (unclipped)
-    uint32_t gran;     // record-major source, staged destination: 16-byte granules of a run's LDS slot
+    uint32_t gran;     // record-major source, staged destination: 16-byte granules of a run's LDS slot;
+                       // field-major source: records of a run's slot (of every leaf)
     uint32_t magic;    // ceil(2^32 / gran): g / gran == mulhi(g, magic) for the granule counts of a tile
     uint32_t lds_base; // LDS byte of run 0
     uint32_t table;    // LDS byte of the run table (one 64-bit start index per run)
+    uint32_t amask;    // field-major source: a run's slot starts at its start index with these bits
+                       // cleared, a whole number of 16-byte granules into every leaf
+    uint32_t pad;
 };
 
 struct BoxEntry {
@@ -372,27 +378,39 @@ struct BoxEntry {
     uint32_t src_off;  // record-major source: the leaf's byte in a block; field-major: the LDS byte of its
                        // runs' slots (leaf by leaf)
     uint32_t dst_off;  // AoS destination: the leaf's (or gap's) byte in a record
-    uint32_t gap;      // 1: a destination gap (zeros)
+    uint32_t dst;      // bit 0: a destination gap (zeros); bits 4-7: log2 of the values of a 16-byte
+                       // destination granule (0: stored value by value); bits 8-11: values by which
+                       // the destination's 16-byte grid lies before the leaf's first value; bits
+                       // 12-14: log2 of the alignment of the values in the source region (at most
+                       // 4), bit 15: it is below their size; bits 16-18: log2 of the alignment in
+                       // the destination region
     uint32_t gran;     // field-major source: 16-byte granules of one run's slot of this leaf
-    uint32_t magic;    // ceil(2^32 / gran)
+    uint32_t magic;    // ceil(2^32 / gran), 0 where gran is 1
 };
 
 struct BoxHeader {
     uint32_t rank;
     uint32_t num_leaves;
     uint32_t num_entries; // leaves, then the gaps of an AoS destination
-    uint32_t flags;       // kBoxFull, kBoxPreserve, kBoxStaged, kBoxUnitMorton
+    uint32_t flags;       // kBoxFull, kBoxPreserve, kBoxStaged, kBoxUnitMorton, kBoxGather, kBoxSameOrder
     uint32_t qlog[LLAMA_MAX_RANK]; // tile extents, log2
     uint32_t qlog_sum;             // log2 of the records of a tile
     uint32_t lds_bytes;
-    uint32_t map;                  // LDS byte of the record map (16 bytes per record of a tile)
+    uint32_t map;                  // LDS byte of the record map (4 bytes per record of a tile)
     uint32_t words;                // kBoxGather: 4-byte words of a destination record
-    uint32_t wtab;                 // kBoxGather: LDS byte of the word table, then the leaves' source fields
+    uint32_t wtab;                 // kBoxGather: LDS byte of the word table (8 bytes per word)
     uint32_t kmagic;               // kBoxGather: ceil(2^32 / K) for the destination record stride K
-    uint32_t pad;
+    uint32_t load_chunks;          // field-major source: 64-granule chunks per leaf (the most of any leaf; a
+                                   // single run's last chunk takes up to 64 granules more)
+    uint32_t load_magic;           // ceil(2^32 / load_chunks)
+    uint32_t store_chunks;         // 64-item chunks per entry (the most of any entry)
+    uint32_t store_magic;          // ceil(2^32 / store_chunks)
+    uint64_t perm;                 // bit b of a record's place in the tile's destination order is bit
+                                   // (perm >> 4 b) & 15 of its place in the source order
+    uint32_t grid[LLAMA_MAX_RANK];  // tiles per dimension
+    uint32_t gmagic[LLAMA_MAX_RANK]; // floor(2^32 / grid), at most 2^32 - 1
+    uint32_t shift[LLAMA_MAX_RANK]; // tile t covers box coordinates [t q - shift, (t + 1) q - shift)
     uint64_t box[LLAMA_MAX_RANK];   // the copy's box (full copies: the extents)
-    uint64_t grid[LLAMA_MAX_RANK];  // tiles per dimension
-    uint64_t shift[LLAMA_MAX_RANK]; // tile t covers box coordinates [t q - shift, (t + 1) q - shift)
     uint64_t num_units;
 };
 
@@ -412,15 +430,17 @@ constexpr uint32_t kBoxUnitMorton = 8;
 // destination region in LDS
 constexpr uint32_t kBoxGather = 16;
 constexpr int kBoxMaxWords = 52;
-// a word-table entry: the leaf (bits 0-7; kBoxWordZero: a gap) and the byte
-// of the leaf's value (bits 8-19)
+// a word-table entry: the leaf (bits 0-7; kBoxWordZero: a gap) and the word
+// of the leaf's value (bits 8-15)
 constexpr uint32_t kBoxWordZero = 0xFFu;
+// both orders number a tile's records alike (perm is the identity)
+constexpr uint32_t kBoxSameOrder = 32;
 
 struct BoxArgs {
     BoxHeader h;
     BoxSide src, dst;
     BoxEntry e[kBoxMaxEntries];
-    uint32_t words[kBoxMaxWords]; // kBoxGather: the destination record's words
+    uint16_t words[kBoxMaxWords]; // kBoxGather: the destination record's words
 };
 static_assert(sizeof(BoxArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 

@@ -1306,16 +1306,11 @@ __device__ __forceinline__ uint64_t box_linear(const BoxSide& s, uint32_t r, con
             for (uint32_t d = 0; d < R; d++)
                 if (d < r)
                     i |= ((c[d] >> j) & 1ull) << (j * r + r - 1 - d);
-    } else if (s.lin == kLinCol) {
-#pragma unroll
-        for (int d = R - 1; d >= 0; d--)
-            if (d < int(r))
-                i = i * s.extent[d] + c[d];
     } else {
 #pragma unroll
         for (int d = 0; d < R; d++)
             if (d < int(r))
-                i = i * s.extent[d] + c[d];
+                i += c[d] * s.stride[d];
     }
     return i;
 }
@@ -1413,18 +1408,112 @@ __device__ __forceinline__ void box_load_group(uint32_t base, uint32_t nspans, u
     }
 }
 
-// Record map entries (16 bytes per record of a tile, in the destination's
-// order): a = kMapSkip (no record), kMapHole (a hole of a full copy: zeros),
-// or the source position: record-major source: a = LDS byte of the record's
-// block plus its phase, b = its lane; field-major: a = run, b = element, c =
-// the run's start index (low bits).  d: staged destination: LDS byte of the
-// destination record.
-constexpr uint32_t kMapSkip = 0xFFFFFFFFu, kMapHole = 0xFFFFFFFEu;
+// Record map entries (4 bytes per record of a tile, in the destination's
+// order).  Without a value (bit 31): kMapSkip (no record) or kMapHole (a hole
+// of a full copy: zeros).  Else where the record lies in the source region,
+// as value number l (bits 16-29) after byte p (bits 0-15):
+//   record-major source: the LDS byte of the record's block (its phase
+//                        included), and the record's lane;
+//   field-major source:  p = 0, l the record's place in every leaf's slots.
+// The same for every leaf, and four bytes: a granule of four consecutive
+// records reads its entries with two LDS instructions.
+constexpr uint32_t kMapSkip = 0xFFFFFFFFu, kMapHole = 0xFFFFFFFEu, kMapNoValue = 0x80000000u;
+
+// LDS byte of an entry's value for the record map entry m; off: the leaf's
+// byte in a block (record-major), or of its first slot (field-major).
+template <bool kSrcField>
+__device__ __forceinline__ uint32_t box_pos(uint32_t m, uint32_t off, uint32_t size)
+{
+    return off + (kSrcField ? 0u : m & 0xFFFFu) + (m >> 16) * size;
+}
+
+// One leaf's values of a tile to a field-major or AoSoA destination, 16-byte
+// granule by granule on the destination's own grid (16-byte addresses in a
+// field-major leaf, 16 / sizeof(T) lanes in an AoSoA block): every lane builds
+// a granule of 16 / sizeof(T) consecutive records of one destination run from
+// the source region; item `idx` of a leaf is one granule.  A run that starts
+// off the grid touches one granule more than it has items: its first lane
+// takes the values of the last granule with those of the first, the two
+// holding as many as one whole granule.  Granules that the run does not fill
+// store their values one by one.  inner: every record of the tile has a value.
+// kSplit: source values aligned to 2^rd bytes only, read from the aligned
+// words that hold them (a misaligned LDS access takes 65 cycles per wave
+// against 4: the lanes one after another).
+template <typename T, bool kSrcField, bool kSplit, bool kCount>
+__device__ __forceinline__ void box_granules(const BoxArgs& a, const BoxEntry& en, uint32_t idx, uint32_t Q, bool inner,
+                                             uint32_t len_d, const uint32_t* map, const uint64_t* tab_d,
+                                             const uint8_t* lds)
+{
+    constexpr uint32_t per = 16 / sizeof(T), lgper = per == 16 ? 4 : per == 8 ? 3 : per == 4 ? 2 : per == 2 ? 1 : 0;
+    const BoxSide& D = a.dst;
+    const uint32_t wlog = D.run_log2, reg = wlog - lgper, W = 1u << wlog;
+    const uint32_t k = idx >> reg, gi = idx & ((1u << reg) - 1u);
+    if (idx >= Q >> lgper)
+        return;
+    const uint64_t st = tab_d[k];
+    const uint32_t w = inner ? W : box_run_len(D, Q, st, len_d);
+    const uint32_t ph = (en.dst >> 8) & 15u, rd = (en.dst >> 12) & 7u;
+    const int32_t e0 = int32_t(gi * per) - int32_t((uint32_t(st) + ph) & (per - 1u));
+    if (w == 0 || e0 >= int32_t(w))
+        return;
+    const uint32_t* mp = map + (k << wlog);
+    auto value = [&](uint32_t m) -> T {
+        const uint32_t p = box_pos<kSrcField>(m, en.src_off, sizeof(T));
+        if constexpr (kSplit && sizeof(T) > 1)
+            return read_split<T>(lds, p, rd);
+        else
+            return *(const T*)(lds + p);
+    };
+    auto address = [&](uint32_t e) -> uint64_t {
+        const uint64_t i = st + e;
+        if (D.mode == kFieldMajor)
+            return en.dst_addr + i * sizeof(T);
+        return en.dst_addr + (i >> D.log2_lanes) * D.block + (i & ((uint64_t(1) << D.log2_lanes) - 1u)) * sizeof(T);
+    };
+    if (inner && e0 >= 0 && e0 + int32_t(per) <= int32_t(w)) {
+        union {
+            u32x4 v;
+            T t[per];
+        } u;
+#pragma unroll
+        for (uint32_t j = 0; j < per; j++)
+            u.t[j] = value(mp[e0 + int32_t(j)]);
+        // an AoSoA block need not lie on the 16-byte grid, only its values on theirs
+        const uint64_t g = address(uint32_t(e0));
+        note_write<kCount>(g, 16);
+        *(GLOBAL u32x4_a4*)g = u.v;
+        return;
+    }
+#pragma clang loop unroll(disable)
+    for (uint32_t j = 0; j < per; j++) {
+        const int32_t e1 = e0 + int32_t(j);
+        const uint32_t e = e1 < 0 ? uint32_t(e1) + W : uint32_t(e1);
+        if (e >= w)
+            continue;
+        const uint32_t m = mp[e];
+        if (m != kMapSkip)
+            gput<kCount>(address(e), (m & kMapNoValue) ? T{} : value(m));
+    }
+}
 
 // R: the largest rank this instantiation handles (loops over dimensions are
-// unrolled to R, which keeps the per-dimension values in registers)
-template <int R, bool kStaged, bool kCount>
-__device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* lds)
+// unrolled to R, which keeps the per-dimension values in registers).
+// kMorton: a side may be in Morton order; else both are row- or column-major
+// (or One), and every index is a base plus coordinates times strides.
+//
+// What a tile costs beside its memory accesses decides this kernel: with
+// 64-bit origin arithmetic, run walks and value stores it spent about 1,000
+// scalar and 900 vector instructions per wave on ten 1 KiB accesses, which
+// kept the compute units' scalar and vector issue busy for most of the copy.
+// So the host provides strides and reciprocals, the waves take chunks of all
+// leaves in turn (a leaf is a division away), and a record's source is one
+// 4-byte entry for all leaves; it takes 670 and 680 now.  128^3 lattice-
+// Boltzmann cells out of a grid with a halo: SoA into aligned AoS 237 -> 149
+// us (4.4 TB/s), aligned AoS into SoA 161 -> 129 us (5.1 TB/s); 2^24
+// particles: row-major AoS into column-major SoA 353 -> 195 us (4.8 TB/s),
+// column-major SoA into Morton AoSoA32 628 -> 250 us (3.8 TB/s).
+template <int R, bool kMorton, bool kStaged, bool kSrcField, bool kCount>
+__device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* lds)
 {
     const BoxHeader& h = a.h;
     const BoxSide &S = a.src, &D = a.dst;
@@ -1434,48 +1523,60 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* 
     const uint32_t Q = 1u << h.qlog_sum;
     const bool full = (h.flags & kBoxFull) != 0, preserve = (h.flags & kBoxPreserve) != 0;
 
-    // ---- the tile's frame origin in box coordinates
-    int64_t o[R];
-    if (h.flags & kBoxUnitMorton) {
+    // ---- the tile's place in the grid, and the linear index of its frame
+    //      origin on each row- or column-major side
+    uint32_t tc[R];
+    uint64_t ls = S.base, ld = D.base;
+    if (kMorton && (h.flags & kBoxUnitMorton)) {
         // cube u of the destination's Morton order: deinterleave u
-        uint64_t c[R] = {};
-        for (uint32_t j = 0; j * r < 64; j++)
-#pragma unroll
-            for (uint32_t d = 0; d < R; d++)
-                if (d < r && j * r + r - 1 - d < 64)
-                    c[d] |= ((u >> (j * r + r - 1 - d)) & 1ull) << j;
 #pragma unroll
         for (uint32_t d = 0; d < R; d++)
-            o[d] = d < r ? int64_t(c[d] << h.qlog[d]) : 0;
+            tc[d] = 0;
+        for (uint32_t j = 0; j * r < 32; j++)
+#pragma unroll
+            for (uint32_t d = 0; d < R; d++)
+                if (d < r && j * r + r - 1 - d < 32)
+                    tc[d] |= ((u >> (j * r + r - 1 - d)) & 1u) << j;
     } else {
-        // the unit count and every grid extent fit 32 bits (checked by the planner)
-        uint32_t rem = uint32_t(u);
+        uint32_t rem = u;
 #pragma unroll
         for (int d = R - 1; d >= 0; d--) {
-            o[d] = 0;
+            tc[d] = 0;
             if (d < int(r)) {
-                const uint32_t g = uint32_t(h.grid[d]), q = rem / g, t = rem - q * g;
+                uint32_t q = __umulhi(rem, h.gmagic[d]), t = rem - q * h.grid[d];
+                if (t >= h.grid[d]) { // the reciprocal is rounded down: at most one short
+                    q++;
+                    t -= h.grid[d];
+                }
+                tc[d] = t;
                 rem = q;
-                o[d] = int64_t(uint64_t(t) << h.qlog[d]) - int64_t(h.shift[d]);
             }
         }
     }
-    // the clipped fast range of each side: [lo, lo + len)
+    // the clipped range [lo, lo + n) of the tile in each dimension; inner: no
+    // coordinate of the tile lies outside the box
     const int fs = box_fast(S.order, r), fd = box_fast(D.order, r);
-    uint32_t lo_s = 0, len_s = 0, lo_d = 0, len_d = 0;
+    uint32_t lo[R], n[R], lo_s = 0, len_s = 0, lo_d = 0, len_d = 0;
+    bool inner = true;
 #pragma unroll
     for (int d = 0; d < R; d++) {
+        lo[d] = n[d] = 0;
         if (d >= int(r))
             continue;
-        const int64_t lo = max<int64_t>(0, -o[d]), hi = min<int64_t>(1ll << h.qlog[d], int64_t(h.box[d]) - o[d]);
-        const uint32_t l = uint32_t(lo), n = hi > lo ? uint32_t(hi - lo) : 0u;
+        ls += tc[d] * (S.stride[d] << h.qlog[d]);
+        ld += tc[d] * (D.stride[d] << h.qlog[d]);
+        const int64_t o = int64_t(uint64_t(tc[d]) << h.qlog[d]) - int64_t(h.shift[d]);
+        const int64_t hi = min<int64_t>(1ll << h.qlog[d], int64_t(h.box[d]) - o);
+        lo[d] = o < 0 ? uint32_t(-o) : 0u;
+        n[d] = hi > int64_t(lo[d]) ? uint32_t(hi) - lo[d] : 0u;
+        inner = inner && (n[d] >> h.qlog[d]) != 0;
         if (d == fs) {
-            lo_s = l;
-            len_s = n;
+            lo_s = lo[d];
+            len_s = n[d];
         }
         if (d == fd) {
-            lo_d = l;
-            len_d = n;
+            lo_d = lo[d];
+            len_d = n[d];
         }
     }
 
@@ -1484,51 +1585,80 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* 
     const uint32_t Rs = Q >> S.run_log2, Rd = Q >> D.run_log2;
     uint64_t* tab_s = (uint64_t*)(lds + S.table);
     uint64_t* tab_d = (uint64_t*)(lds + D.table);
-    auto run_start = [&](const BoxSide& X, int fx, uint32_t lo, uint32_t len, uint32_t k) -> uint64_t {
+    auto run_start = [&](const BoxSide& X, int fx, uint64_t lx, uint32_t lo_x, uint32_t len, uint32_t k) -> uint64_t {
         if (X.order == kOrderOne)
             return 0;
         uint32_t x[R];
-        box_coord<R>(h, X.order, k, fx >= 0 ? lo : 0u, x);
+        box_coord<R>(h, X.order, k, fx >= 0 ? lo_x : 0u, x);
         bool in = fx < 0 || len > 0;
-        uint64_t c[R];
+        if (kMorton && fx < 0) {
+            uint64_t c[R];
 #pragma unroll
-        for (uint32_t d = 0; d < R; d++) {
-            c[d] = 0;
-            if (d < r) {
-                const int64_t b = o[d] + int64_t(x[d]);
-                // a Morton run's cube may reach past the box: its records are
-                // checked one by one
-                if (X.order != kOrderMorton && (b < 0 || b >= int64_t(h.box[d])))
-                    in = false;
-                c[d] = uint64_t(int64_t(X.offset[d]) + b);
+            for (uint32_t d = 0; d < R; d++) {
+                c[d] = 0;
+                if (d < r) {
+                    // a Morton run's cube may reach past the box: its records are
+                    // checked one by one
+                    if (X.order != kOrderMorton && x[d] - lo[d] >= n[d])
+                        in = false;
+                    c[d] = X.offset[d] + (uint64_t(tc[d]) << h.qlog[d]) - h.shift[d] + x[d];
+                }
             }
+            return in ? box_linear<R>(X, r, c) : ~0ull;
         }
-        return in ? box_linear<R>(X, r, c) : ~0ull;
+        uint64_t i = lx;
+#pragma unroll
+        for (uint32_t d = 0; d < R; d++)
+            if (d < r) {
+                if (!inner && x[d] - lo[d] >= n[d])
+                    in = false;
+                i += x[d] * X.stride[d];
+            }
+        return in ? i : ~0ull;
     };
     for (uint32_t k = tid; k < Rs; k += nthr)
-        tab_s[k] = run_start(S, fs, lo_s, len_s, k);
+        tab_s[k] = run_start(S, fs, ls, lo_s, len_s, k);
     for (uint32_t k = tid; k < Rd; k += nthr)
-        tab_d[k] = (h.flags & kBoxUnitMorton) ? (u << h.qlog_sum) // the cube's first Morton index
-                                              : run_start(D, fd, lo_d, len_d, k);
+        tab_d[k] = (kMorton && (h.flags & kBoxUnitMorton)) ? uint64_t(u) << h.qlog_sum // the cube's first Morton index
+                                                           : run_start(D, fd, ld, lo_d, len_d, k);
     __syncthreads();
+    auto run_len = [&](const BoxSide& X, uint64_t st, uint32_t fast_len) -> uint32_t {
+        if constexpr (kMorton)
+            return box_run_len(X, Q, st, fast_len);
+        return inner ? (X.order == kOrderOne ? 1u : 1u << X.run_log2) : st == ~0ull ? 0u : X.order == kOrderOne ? 1u : fast_len;
+    };
 
     // ---- source runs -> LDS, granule by granule over all waves
-    if (S.mode == kFieldMajor) {
-        for (uint32_t f = 0; f < h.num_leaves; f++) {
+    if constexpr (kSrcField) {
+        const uint32_t nch = h.num_leaves * h.load_chunks;
+        for (uint32_t c = wave; c < nch; c += nwaves) {
+            const uint32_t f = h.load_chunks == 1u ? c : __umulhi(c, h.load_magic), sub = c - f * h.load_chunks;
             const BoxEntry& en = a.e[f];
-            box_load_group<kCount>(S.lds_base + en.src_off, Rs, en.gran, en.magic, wave, nwaves, lane, lds_base,
-                                   [&](uint32_t k, uint64_t& g0, uint32_t& len) {
-                                       const uint64_t st = tab_s[k];
-                                       const uint32_t w = box_run_len(S, Q, st, len_s);
-                                       g0 = en.src_addr + st * en.size;
-                                       len = w * en.size;
-                                   });
+            const uint32_t g = sub * 64u + lane;
+            uint32_t k = 0, gi = g;
+            if (Rs > 1u) {
+                k = en.magic ? __umulhi(g, en.magic) : g;
+                gi = g - k * en.gran;
+            }
+            if (k < Rs) {
+                const uint64_t st = tab_s[k];
+                const uint32_t w = run_len(S, st, len_s);
+                const uint32_t rel = (uint32_t(st) & S.amask) * en.size + (uint32_t(en.src_addr) & 15u);
+                const uint32_t g0 = rel >> 4, g1 = w ? (rel + w * en.size + 15u) >> 4 : 0u;
+                const uint64_t ga = (en.src_addr & ~uint64_t(15)) + (st & ~uint64_t(S.amask)) * en.size + uint64_t(gi) * 16u;
+                const uint32_t la = uniform(lds_base + (en.src_off & ~15u) + sub * 1024u);
+                if (gi >= g0 && gi < g1)
+                    lds_dma16<false, kCount>(ga, la);
+                // a single run's last few granules go with its last chunk
+                if (Rs == 1u && sub + 1u == h.load_chunks && gi + 64u >= g0 && gi + 64u < g1)
+                    lds_dma16<false, kCount>(ga + 1024u, la + 1024u);
+            }
         }
     } else {
         box_load_group<kCount>(S.lds_base, Rs, S.gran, S.magic, wave, nwaves, lane, lds_base,
                                [&](uint32_t k, uint64_t& g0, uint32_t& len) {
                                    const uint64_t st = tab_s[k];
-                                   const uint32_t w = box_run_len(S, Q, st, len_s);
+                                   const uint32_t w = run_len(S, st, len_s);
                                    len = 0;
                                    if (w > 0)
                                        box_span(S, st, w, g0, len);
@@ -1538,132 +1668,104 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* 
         box_load_group<kCount>(D.lds_base, Rd, D.gran, D.magic, wave, nwaves, lane, lds_base,
                                [&](uint32_t k, uint64_t& g0, uint32_t& len) {
                                    const uint64_t st = tab_d[k];
-                                   const uint32_t w = box_run_len(D, Q, st, len_d);
+                                   const uint32_t w = run_len(D, st, len_d);
                                    g0 = D.blob + st * D.block;
                                    len = w * uint32_t(D.block);
                                });
 
     // ---- the record map, in the destination's order (overlaps the loads)
     const uint32_t wlog = D.run_log2, wmask = (1u << wlog) - 1u;
-    uint4* map = (uint4*)(lds + h.map);
-    for (uint32_t j = tid; j < Q; j += nthr) {
-        const uint32_t kd = j >> wlog, ed = j & wmask;
-        const uint64_t sd = tab_d[kd];
-        uint4 m{kMapSkip, 0u, 0u, 0u};
-        if (ed < box_run_len(D, Q, sd, len_d)) {
-            if (kStaged)
-                m.w = D.lds_base + kd * (D.gran << 4) + ((uint32_t(D.blob) + uint32_t(sd) * uint32_t(D.block)) & 15u) +
-                      ed * uint32_t(D.block);
-            uint32_t x[R];
-            box_coord<R>(h, D.order, kd, fd >= 0 ? lo_d + ed : ed, x);
-            bool in = true;
+    uint32_t* map = (uint32_t*)(lds + h.map);
+    // the map entry of the record that is element es of source run ks
+    auto source_of = [&](uint32_t ks, uint32_t es) -> uint32_t {
+        if (!kSrcField && S.order == kOrderOne)
+            return S.lds_base + (uint32_t(S.blob) & 15u);
+        const uint64_t ss = tab_s[ks];
+        if constexpr (kSrcField)
+            return (ks * S.gran + (uint32_t(ss) & S.amask) + es) << 16;
+        const uint32_t l0 = uint32_t(ss) & ((1u << S.log2_lanes) - 1u), i = l0 + es; // records from the first block on
+        return (S.lds_base + ks * (S.gran << 4) +
+                ((uint32_t(S.blob) + uint32_t(ss >> S.log2_lanes) * uint32_t(S.block)) & 15u) +
+                (i >> S.log2_lanes) * uint32_t(S.block)) |
+               ((i & ((1u << S.log2_lanes) - 1u)) << 16);
+    };
+    if (inner && S.order != kOrderOne) {
+        // every record of the tile is in the box: its place in the source's
+        // order is a permutation of the bits of its place in the destination's
+        for (uint32_t j = tid; j < Q; j += nthr) {
+            uint32_t js = j;
+            if (!(h.flags & kBoxSameOrder)) {
+                js = 0;
+                uint64_t perm = h.perm;
+                for (uint32_t b = 0; b < h.qlog_sum; b++, perm >>= 4)
+                    js |= ((j >> b) & 1u) << (uint32_t(perm) & 15u);
+            }
+            map[j] = source_of(js >> S.run_log2, js & ((1u << S.run_log2) - 1u));
+        }
+    } else {
+        for (uint32_t j = tid; j < Q; j += nthr) {
+            const uint32_t kd = j >> wlog, ed = j & wmask;
+            uint32_t m = kMapSkip;
+            if (ed < run_len(D, tab_d[kd], len_d)) {
+                uint32_t x[R];
+                box_coord<R>(h, D.order, kd, fd >= 0 ? lo_d + ed : ed, x);
+                bool in = true;
 #pragma unroll
-            for (uint32_t d = 0; d < R; d++)
-                if (d < r) {
-                    const int64_t b = o[d] + int64_t(x[d]);
-                    in = in && b >= 0 && b < int64_t(h.box[d]);
-                }
-            if (!in) {
-                // a hole or tail lane of a full copy into a Morton destination
-                m.x = full && !preserve ? kMapHole : kMapSkip;
-            } else {
-                uint32_t ks, es;
-                box_run<R>(h, S.order, x, ks, es);
-                if (fs >= 0)
-                    es -= lo_s;
-                const uint64_t ss = tab_s[ks];
-                if (S.mode == kFieldMajor) {
-                    m.x = ks;
-                    m.y = es;
-                    m.z = uint32_t(ss);
-                } else if (S.order == kOrderOne) {
-                    m.x = S.lds_base + (uint32_t(S.blob) & 15u);
-                    m.y = 0;
+                for (uint32_t d = 0; d < R; d++)
+                    if (d < r)
+                        in = in && x[d] - lo[d] < n[d];
+                if (!in) {
+                    // a hole or tail lane of a full copy into a Morton destination
+                    m = full && !preserve ? kMapHole : kMapSkip;
                 } else {
-                    const uint64_t i = ss + es, b0 = ss >> S.log2_lanes;
-                    m.x = S.lds_base + ks * (S.gran << 4) +
-                          ((uint32_t(S.blob) + uint32_t(b0) * uint32_t(S.block)) & 15u) +
-                          uint32_t((i >> S.log2_lanes) - b0) * uint32_t(S.block);
-                    m.y = uint32_t(i & ((uint64_t(1) << S.log2_lanes) - 1u));
+                    uint32_t ks, es;
+                    box_run<R>(h, S.order, x, ks, es);
+                    m = source_of(ks, fs >= 0 ? es - lo_s : es);
                 }
             }
+            map[j] = m;
         }
-        map[j] = m;
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    // ---- every (entry, record) pair; the lanes of a wave hold consecutive
-    //      records of one entry, whose fields then load as scalars
-    const uint32_t E = h.num_entries;
     const uint64_t lmask = (uint64_t(1) << D.log2_lanes) - 1u;
-    auto move = [&](const BoxEntry& en, uint32_t rec) {
-        const uint4 m = map[rec];
-        if (m.x == kMapSkip)
-            return;
-        const bool zero = en.gap || m.x == kMapHole;
-        if (zero && preserve)
-            return;
-        uint32_t sp = 0;
-        if (!zero)
-            sp = S.mode == kFieldMajor
-                     ? S.lds_base + en.src_off + m.x * (en.gran << 4) +
-                           ((uint32_t(en.src_addr) + m.z * en.size) & 15u) + m.y * en.size
-                     : m.x + en.src_off + m.y * en.size;
-        if constexpr (kStaged) {
-            if (zero) {
-                for (uint32_t b = 0; b < en.size; b++)
-                    lds[m.w + en.dst_off + b] = 0;
-            } else {
-                box_move_lds(lds, sp, m.w + en.dst_off, en.size);
-            }
-        } else {
-            const uint64_t i = tab_d[rec >> wlog] + (rec & wmask);
-            uint64_t g;
-            if (en.gap)
-                g = D.blob + i * D.block + en.dst_off; // an AoS destination (lanes 1)
-            else if (D.mode == kFieldMajor)
-                g = en.dst_addr + i * en.size;
-            else
-                g = en.dst_addr + (i >> D.log2_lanes) * D.block + (i & lmask) * en.size;
-            box_store_value<kCount>(lds, sp, g, en.size, zero);
-        }
-    };
     if (kStaged && (h.flags & kBoxGather)) {
         // ---- AoS destination of whole words: every granule of every
         //      destination run assembled word by word, stored at once
-        const uint32_t* wt = (const uint32_t*)(lds + h.wtab);
-        const uint4* lf = (const uint4*)(lds + h.wtab + ((h.words * 4u + 15u) & ~15u));
+        const uint2* wt = (const uint2*)(lds + h.wtab); // per word: its value's LDS offset, size
         const uint32_t K = uint32_t(D.block);
         const uint32_t total = Rd * D.gran;
         for (uint32_t g = tid; g < total; g += nthr) {
-            const uint32_t k = __umulhi(g, D.magic), gi = g - k * D.gran;
+            const uint32_t k = Rd == 1u ? 0u : __umulhi(g, D.magic), gi = g - k * D.gran;
             const uint64_t st = tab_d[k];
-            const uint32_t w = box_run_len(D, Q, st, len_d);
+            const uint32_t w = run_len(D, st, len_d);
             if (w == 0)
                 continue;
             const uint64_t g0 = D.blob + st * D.block;
             const uint32_t shift = uint32_t(g0) & 15u, end = shift + w * K;
             if (gi * 16u >= end)
                 continue;
+            // the granule's first byte in the run's span, its record and word
+            // (a granule that begins before the span starts at record 0 with
+            // words that are not stored)
+            const int32_t b0 = int32_t(gi * 16u) - int32_t(shift);
+            uint32_t rr = b0 < 0 ? 0u : __umulhi(uint32_t(b0), h.kmagic);
+            int32_t wi = (b0 - int32_t(rr * K)) >> 2;
             uint32_t v[4];
 #pragma unroll
             for (uint32_t c = 0; c < 4; c++) {
                 v[c] = 0;
-                const int32_t b = int32_t(gi * 16u + 4u * c) - int32_t(shift); // byte of the run's span
-                if (b < 0 || uint32_t(b) >= w * K)
-                    continue;
-                const uint32_t rr = __umulhi(uint32_t(b), h.kmagic); // record of the run
-                const uint32_t wi = (uint32_t(b) - rr * K) >> 2;
-                const uint4 m = map[(k << wlog) + rr];
-                const uint32_t e = wt[wi];
-                if (m.x >= kMapHole || (e & 0xFFu) == kBoxWordZero)
-                    continue; // a hole of a full copy, or a gap: zero
-                const uint4 L = lf[e & 0xFFu]; // src_off, size, slot bytes, address low bits
-                const uint32_t sp = S.mode == kFieldMajor
-                                        ? S.lds_base + L.x + m.x * L.z + ((L.w + m.z * L.y) & 15u) + m.y * L.y
-                                        : m.x + L.x + m.y * L.y;
-                v[c] = *(const uint32_t*)(lds + sp + (e >> 8));
+                if (wi >= 0 && rr < w) {
+                    const uint32_t m = map[(k << wlog) + rr];
+                    const uint2 L = wt[wi];
+                    if (!((m | L.x) & kMapNoValue)) // a hole of a full copy, or a gap: zero
+                        v[c] = *(const uint32_t*)(lds + box_pos<kSrcField>(m, L.x, L.y));
+                }
+                if (++wi == int32_t(h.words)) {
+                    wi = 0;
+                    rr++;
+                }
             }
             const uint64_t ga = (g0 & ~uint64_t(15)) + uint64_t(gi) * 16u;
             const uint32_t lo = gi == 0 ? shift : 0u, hi = min(16u, end - gi * 16u);
@@ -1678,14 +1780,66 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* 
         }
         return;
     }
-    if (h.qlog_sum >= 6) {
-        // a wave's 64 consecutive pairs lie in one entry: all threads busy
-        for (uint32_t j = tid; j < (E << h.qlog_sum); j += nthr)
-            move(a.e[uniform(j >> h.qlog_sum)], j & (Q - 1u));
-    } else {
-        for (uint32_t f = 0; f < E; f++)
-            for (uint32_t rec = tid; rec < Q; rec += nthr)
-                move(a.e[f], rec);
+
+    // ---- values: chunks of 64 granules (or of 64 records of one entry), the
+    //      entry uniform, its fields scalars
+    const uint32_t nch = h.num_entries * h.store_chunks;
+    for (uint32_t c = wave; c < nch; c += nwaves) {
+        const uint32_t f = h.store_chunks == 1u ? c : __umulhi(c, h.store_magic), sub = c - f * h.store_chunks;
+        const BoxEntry& en = a.e[f];
+        const uint32_t lgper = kStaged ? 0u : (en.dst >> 4) & 15u;
+        const uint32_t rec = sub * 64u + lane;
+        const uint32_t rd = (en.dst >> 12) & 7u, wr = (en.dst >> 16) & 7u; // log2 of the values' alignment in LDS
+        if (lgper) {
+            const bool all = inner && S.order != kOrderOne;
+            if ((en.dst >> 15) & 1u) {
+                switch (lgper) {
+                case 3: box_granules<uint16_t, kSrcField, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 2: box_granules<uint32_t, kSrcField, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                default: box_granules<uint64_t, kSrcField, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                }
+            } else {
+                switch (lgper) {
+                case 4: box_granules<uint8_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 3: box_granules<uint16_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 2: box_granules<uint32_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                default: box_granules<uint64_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                }
+            }
+            continue;
+        }
+        const uint32_t m = rec < Q ? map[rec] : kMapSkip;
+        const bool zero = (en.dst & 1u) || m == kMapHole;
+        if (m == kMapSkip || (zero && preserve))
+            continue;
+        const uint32_t sp = zero ? 0u : box_pos<kSrcField>(m, en.src_off, en.size);
+        const uint64_t i = tab_d[rec >> wlog] + (rec & wmask);
+        if constexpr (kStaged) {
+            const uint32_t kd = rec >> wlog, ed = rec & wmask;
+            const uint32_t dp = D.lds_base + kd * (D.gran << 4) +
+                                ((uint32_t(D.blob) + (uint32_t(i) - ed) * uint32_t(D.block)) & 15u) +
+                                ed * uint32_t(D.block) + en.dst_off;
+            if (zero) {
+                for (uint32_t b = 0; b < en.size; b++)
+                    lds[dp + b] = 0;
+            } else {
+                switch (en.size) {
+                case 2: write_split<uint16_t>(lds, dp, read_split<uint16_t>(lds, sp, rd), wr); break;
+                case 4: write_split<uint32_t>(lds, dp, read_split<uint32_t>(lds, sp, rd), wr); break;
+                case 8: write_split<uint64_t>(lds, dp, read_split<uint64_t>(lds, sp, rd), wr); break;
+                default: box_move_lds(lds, sp, dp, en.size); break;
+                }
+            }
+        } else {
+            uint64_t g;
+            if (en.dst & 1u)
+                g = D.blob + i * D.block + en.dst_off; // a gap of an AoS destination (lanes 1)
+            else if (D.mode == kFieldMajor)
+                g = en.dst_addr + i * en.size;
+            else
+                g = en.dst_addr + (i >> D.log2_lanes) * D.block + (i & lmask) * en.size;
+            box_store_value<kCount>(lds, sp, g, en.size, zero);
+        }
     }
 
     if constexpr (kStaged) {
@@ -1693,9 +1847,9 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* 
         __syncthreads();
         const uint32_t total = Rd * D.gran;
         for (uint32_t g = tid; g < total; g += nthr) {
-            const uint32_t k = __umulhi(g, D.magic), gi = g - k * D.gran;
+            const uint32_t k = Rd == 1u ? 0u : __umulhi(g, D.magic), gi = g - k * D.gran;
             const uint64_t st = tab_d[k];
-            const uint32_t w = box_run_len(D, Q, st, len_d);
+            const uint32_t w = run_len(D, st, len_d);
             if (w == 0)
                 continue;
             const uint64_t g0 = D.blob + st * D.block;
@@ -1715,38 +1869,37 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint64_t u, uint8_t* 
     }
 }
 
-template <int R, bool kStaged, bool kCount>
+template <int R, bool kMorton, bool kStaged, bool kSrcField, bool kCount>
 __global__ void __launch_bounds__(1024) box_kernel(const BoxArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     if (kStaged && (a.h.flags & kBoxGather)) {
-        // the word table, then per leaf its source fields (src_off, size,
-        // slot bytes, address low bits), read by lanes of different leaves;
-        // the first tile's barriers publish them
-        uint32_t* t = (uint32_t*)(lds + a.h.wtab);
-        for (uint32_t k = threadIdx.x; k < a.h.words; k += blockDim.x)
-            t[k] = a.words[k];
-        uint4* l = (uint4*)(lds + a.h.wtab + ((a.h.words * 4u + 15u) & ~15u));
-        for (uint32_t f = threadIdx.x; f < a.h.num_leaves; f += blockDim.x)
-            l[f] = uint4{a.e[f].src_off, a.e[f].size, a.e[f].gran << 4, uint32_t(a.e[f].src_addr)};
+        // per word of the destination record its source: the arguments of
+        // box_pos (bit 31 of the first: a gap); the first tile's barriers
+        // publish them
+        uint2* wt = (uint2*)(lds + a.h.wtab);
+        for (uint32_t k = threadIdx.x; k < a.h.words; k += blockDim.x) {
+            const uint32_t e = a.words[k], f = e & 0xFFu;
+            wt[k] = f == kBoxWordZero ? uint2{kMapNoValue, 0u} : uint2{a.e[f].src_off + ((e >> 8) << 2), a.e[f].size};
+        }
     }
-    const uint64_t nt = a.h.num_units;
-    uint64_t t = blockIdx.x, stride = gridDim.x;
+    const uint32_t nt = uint32_t(a.h.num_units); // below 2^32 (checked by the planner)
+    uint32_t t = blockIdx.x, stride = gridDim.x;
     if (!kCount && gridDim.x == nt) { // each XCD one contiguous eighth of the tiles
-        const uint64_t b = blockIdx.x, x = b & 7u, k = b >> 3, q = nt >> 3, rem = nt & 7u;
+        const uint32_t b = blockIdx.x, x = b & 7u, k = b >> 3, q = nt >> 3, rem = nt & 7u;
         t = x * q + min(x, rem) + k;
         stride = nt;
     }
-    for (; t < nt; t += stride) {
-        box_body<R, kStaged, kCount>(a, t, lds);
-        if (t + stride < nt)
+    for (uint64_t v = t; v < nt; v += stride) {
+        box_body<R, kMorton, kStaged, kSrcField, kCount>(a, uint32_t(v), lds);
+        if (v + stride < nt)
             __syncthreads();
     }
 }
 
 // The coordinate of linear index i on side s; false when no coordinate inside
 // the view's extents has that index (a Morton hole, an AoSoA tail lane).
-__device__ __forceinline__ bool box_delinear(const BoxSide& s, uint32_t r, uint64_t i, uint64_t* c)
+__device__ __forceinline__ bool box_delinear(const BoxSide& s, const uint64_t* extent, uint32_t r, uint64_t i, uint64_t* c)
 {
     bool in = true;
     if (s.lin == kLinMorton) {
@@ -1762,7 +1915,7 @@ __device__ __forceinline__ bool box_delinear(const BoxSide& s, uint32_t r, uint6
             in = false;
 #pragma unroll
         for (uint32_t d = 0; d < LLAMA_MAX_RANK; d++)
-            if (d < r && c[d] >= s.extent[d])
+            if (d < r && c[d] >= extent[d])
                 in = false;
         return in;
     }
@@ -1772,8 +1925,8 @@ __device__ __forceinline__ bool box_delinear(const BoxSide& s, uint32_t r, uint6
         for (int d = 0; d < LLAMA_MAX_RANK; d++) {
             c[d] = 0;
             if (d < int(r)) {
-                c[d] = rem % s.extent[d];
-                rem /= s.extent[d];
+                c[d] = rem % extent[d];
+                rem /= extent[d];
             }
         }
     } else {
@@ -1781,8 +1934,8 @@ __device__ __forceinline__ bool box_delinear(const BoxSide& s, uint32_t r, uint6
         for (int d = LLAMA_MAX_RANK - 1; d >= 0; d--) {
             c[d] = 0;
             if (d < int(r)) {
-                c[d] = rem % s.extent[d];
-                rem /= s.extent[d];
+                c[d] = rem % extent[d];
+                rem /= extent[d];
             }
         }
     }
@@ -1813,7 +1966,7 @@ __global__ void __launch_bounds__(1024) box_naive_kernel(const BoxArgs a)
         uint64_t id = 0;
         if (full) {
             id = i;
-            in = box_delinear(a.dst, r, i, cd);
+            in = box_delinear(a.dst, h.box, r, i, cd); // a full copy: the box is the extents
 #pragma unroll
             for (uint32_t d = 0; d < LLAMA_MAX_RANK; d++)
                 cs[d] = cd[d];
@@ -1836,12 +1989,12 @@ __global__ void __launch_bounds__(1024) box_naive_kernel(const BoxArgs a)
             uint64_t gd;
             if (a.dst.mode == kFieldMajor)
                 gd = en.dst_addr + id * en.size;
-            else if (en.gap)
+            else if (en.dst & 1u)
                 gd = a.dst.blob + id * a.dst.block + en.dst_off;
             else
                 gd = en.dst_addr + (id >> a.dst.log2_lanes) * a.dst.block +
                      (id & ((uint64_t(1) << a.dst.log2_lanes) - 1u)) * en.size;
-            if (en.gap || !in) {
+            if ((en.dst & 1u) || !in) {
                 if (!preserve)
                     for (uint32_t b = 0; b < en.size; b++)
                         gput<kCount>(gd + b, uint8_t(0));
@@ -2059,16 +2212,22 @@ const void* const kTileVirtualCountKernels[kTileModes] = {
     (const void*)tile_count_kernel<kModeStaged | kV>, (const void*)tile_count_kernel<kModeDirectStore | kV>, nullptr,
     (const void*)tile_count_kernel<kModeGatherStore | kV>, (const void*)tile_count_kernel<kModeGatherOdd | kV>};
 
-// box_kernel<R, staged, counted>: index (R == 8) * 4 + staged * 2 + counted
-const void* const kBoxKernels[8] = {
-    (const void*)box_kernel<4, false, false>, (const void*)box_kernel<4, false, true>,
-    (const void*)box_kernel<4, true, false>,  (const void*)box_kernel<4, true, true>,
-    (const void*)box_kernel<8, false, false>, (const void*)box_kernel<8, false, true>,
-    (const void*)box_kernel<8, true, false>,  (const void*)box_kernel<8, true, true>};
+// box_kernel<R, Morton, staged, field-major source, counted>: index
+// (0: rank <= 4, row and column orders; 1: rank <= 4; 2: any rank) * 8 +
+// staged * 4 + field-major * 2 + counted
+#define BOX_KERNELS(R, M)                                                                           \
+    (const void*)box_kernel<R, M, false, false, false>, (const void*)box_kernel<R, M, false, false, true>, \
+    (const void*)box_kernel<R, M, false, true, false>, (const void*)box_kernel<R, M, false, true, true>,   \
+    (const void*)box_kernel<R, M, true, false, false>, (const void*)box_kernel<R, M, true, false, true>,   \
+    (const void*)box_kernel<R, M, true, true, false>, (const void*)box_kernel<R, M, true, true, true>
+const void* const kBoxKernels[24] = {BOX_KERNELS(4, false), BOX_KERNELS(4, true), BOX_KERNELS(8, true)};
+#undef BOX_KERNELS
 
 const void* box_kernel_for(const BoxArgs& b, bool counted)
 {
-    return kBoxKernels[(b.h.rank > 4 ? 4 : 0) + ((b.h.flags & kBoxStaged) ? 2 : 0) + (counted ? 1 : 0)];
+    auto morton = [](const BoxSide& s) { return s.order == kOrderMorton || s.order == kOrderPoint; };
+    return kBoxKernels[(b.h.rank > 4 ? 16 : morton(b.src) || morton(b.dst) ? 8 : 0) + ((b.h.flags & kBoxStaged) ? 4 : 0) +
+                       (b.src.mode == kFieldMajor ? 2 : 0) + (counted ? 1 : 0)];
 }
 
 bool g_attr_set = false;

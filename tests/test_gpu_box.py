@@ -264,3 +264,57 @@ def test_box_errors(L):
     with pytest.raises(L.LlamaError) as e:
         L.Batch([(a, sa, d, d.alloc())])
     assert e.value.status == L.E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("name", ["bytes", "shorts", "words", "doubles", "mixed", "listing1"])
+@pytest.mark.parametrize("dst", [("soa_single", 0), ("soa_multi", 0), ("aosoa", 2), ("aosoa", 8), ("aosoa", 32)])
+def test_box_granules(L, orc, name, dst):
+    """Destination granules: runs that start at every place on the granule
+    grid and end inside, before and past a granule, runs shorter than one,
+    sources with values below their alignment, and blobs off the 16-byte grid
+    on both sides."""
+    rec = {"bytes": [("u8", 3)], "shorts": [("u16", 2), "u8"], "words": ["u32", "f32"], "doubles": ["f64", "u64"],
+           "mixed": W.MIXED, "listing1": W.LISTING1}[name]
+    ro, rg = orc.Record(rec), L.Record(rec)
+    g = random.Random(hash((name, dst)) & 0xFFFF)
+    for k, (width, off) in enumerate([(1, 0), (3, 1), (15, 5), (16, 7), (17, 15), (64, 3), (127, 0), (130, 9), (257, 2)]):
+        src = g.choice([("aos_packed", 0), ("aos_aligned", 0), ("soa_single", 0), ("soa_multi", 0), ("aosoa", 4)])
+        sext, dext, so, do, box = [3, width + 3], [4, width + off + 1], [1, k % 4], [1, off], [2, width]
+        ms_o, ms = orc.Mapping(ro, src[0], sext, src[1]), L.Mapping(rg, src[0], sext, src[1])
+        md_o, md = orc.Mapping(ro, dst[0], dext, dst[1]), L.Mapping(rg, dst[0], dext, dst[1])
+        s = [W.random_bytes(n, 3 * k + j) for j, n in enumerate(ms_o.blob_sizes())]
+        canary = [W.random_bytes(n, 70 + 3 * k + j) for j, n in enumerate(md_o.blob_sizes())]
+        want = orc.copy_box(ms_o, s, so, md_o, [c.copy() for c in canary], do, box)
+
+        def place(arrays, at):  # device blobs that start `at` bytes off the 16-byte grid
+            out = []
+            for x in arrays:
+                t = torch.empty(x.size + 32, dtype=torch.uint8, device="cuda")[at:at + x.size]
+                t.copy_(torch.from_numpy(x))
+                out.append(t)
+            return out
+        for at_s, at_d in [(0, 0), (g.choice([4, 8, 12]), g.choice([0, 4, 8])), (g.choice([1, 2, 7]), g.choice([1, 2, 3]))]:
+            sd, dd = place(s, at_s), place(canary, at_d)
+            L.copy_box(ms, sd, so, md, dd, do, box)
+            torch.cuda.synchronize()
+            _check(dd, want, f"{name} {src} -> {dst} width {width} at {off}, blobs {at_s} and {at_d} off the grid")
+
+
+def test_box_wide_record(L):
+    """A 1-byte leaf beside leaves of kilobytes: the tile's slots of whole
+    granules of every leaf do not fit, the copy still runs."""
+    import ctypes
+    rg = L.Record(["u8", "u8", "u8", "u8"])
+    for j, size in enumerate([1, 4096, 4096, 4096]):
+        rg.nodes[j] = L.Field(size, 1, 1, 0)
+    ext = [3, 5]
+    a, b = L.Mapping(rg, "soa_multi", ext, linearizer="col"), L.Mapping(rg, "aos_packed", ext)
+    assert ctypes.sizeof(L.Field) == 16 and a.blob_sizes() == [15, 61440, 61440, 61440]
+    src = [W.random_bytes(n, 5 + j) for j, n in enumerate(a.blob_sizes())]
+    sd = [torch.from_numpy(x).cuda() for x in src]
+    dd = b.alloc(fill=0xCD)
+    L.copy(a, sd, b, dd)
+    torch.cuda.synchronize()
+    got = dd[0].cpu().numpy().reshape(3, 5, -1)
+    leaves = [x.reshape(5, 3, -1).transpose(1, 0, 2) for x in src]  # column-major: the first index fastest
+    assert np.array_equal(got, np.concatenate(leaves, axis=2))
