@@ -516,6 +516,9 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
         const uint64_t q = 24576 / std::max<uint64_t>(r.packed_size, 1);
         const bool across = S.kind != LLAMA_ONE && S.lin != D.lin;
         qsum = std::min<uint32_t>(12, std::max<uint32_t>(6, across ? log2_ceil(q) : log2u(q)));
+        // (a small box in as many tiles as the chip has compute units)
+        while (qsum > 6 && (nbox >> qsum) < 256)
+            qsum--;
         while (qsum > 6 && !try_plan(rq, so, dof, box, full, preserve, qsum, 40 * 1024, p))
             qsum--;
     }

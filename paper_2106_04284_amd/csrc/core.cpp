@@ -1000,6 +1000,19 @@ uint32_t log2_move(uint64_t bits)
     return log2_exact(w);
 }
 
+// Field-major spans are short: rotates the first storing thread of p.threads
+// from leaf to leaf so that every wave takes a share.
+void rotate_stores(Plan& p, uint32_t T)
+{
+    uint32_t first = 0;
+    for (uint32_t f = 0; f < p.tile.h.num_leaves; f++) {
+        TileEntry& e = p.tile.e[f];
+        e.move = (e.move & ~(4095u << 8)) | (first << 8);
+        const uint32_t pad = (p.tile.h.flags & kTileDirectStore) ? 15 : 30;
+        first = uint32_t((first + (uint64_t(T) * e.size + pad) / 16) % p.threads);
+    }
+}
+
 bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
 {
     const Record& r = rq.record;
@@ -1118,8 +1131,9 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         return false; // a scattered destination is stored by the direct-store tile only
     if (direct) {
         a.flags |= kTileDirectStore;
-        a.dst.lds_bytes = 0;
-        a.lds_bytes = sb;
+        a.dst.lds_base = (sb + 15) & ~15u; // the leaf table
+        a.dst.lds_bytes = uint32_t(F) * 16;
+        a.lds_bytes = a.dst.lds_base + a.dst.lds_bytes;
         if (split_src)
             a.flags |= kTileSplitSrc;
         for (size_t f = 0; f < F; f++) { // the width is the leaf size; the phase replaces the split bits
@@ -1250,6 +1264,40 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         table.resize(quads_at, 0u);
         table.insert(table.end(), quads.begin(), quads.end());
         table.insert(table.end(), pairs.begin(), pairs.end());
+        // Words that are all one aligned word of the source, or padding, in
+        // super-blocks of whole granules (kTileGatherWhole): where one
+        // super-block is not, the table describes m = 2 or 4 of them (4 records
+        // of 28 bytes)
+        const uint32_t m = gwords % 4 == 0 ? 1 : gwords % 2 == 0 ? 2 : 4, lm = log2_exact(m);
+        bool whole = rq.dst.block % 4 == 0 && g.kq % 4 == 0 && quads.empty() && pairs.empty() &&
+                     recs * m <= kGatherMaxLanes && recs * m <= T &&
+                     (a.dst.tile_bytes / 4) * gwords * m < (uint64_t(1) << 32);
+        for (uint64_t w = 0; w < gwords && whole; w++)
+            whole = table[w] == 0 || ((table[w] >> 23) == 15u && (table[w] & 3u) == 0 &&
+                                      (g.q == 0 || ((table[w] >> 18) & 31u) >= 2));
+        if (whole && m > 1) {
+            std::vector<uint32_t> more(gwords * m, 0u);
+            for (uint32_t k = 0; k < m; k++)
+                for (uint64_t w = 0; w < gwords; w++) {
+                    if (table[w] == 0)
+                        continue;
+                    const uint32_t run = (table[w] >> 18) & 31u;
+                    const uint64_t p0 = (table[w] & 0x3FFFFu) + uint64_t(k >> g.q) * g.kq +
+                                        (uint64_t(k & ((1u << g.q) - 1u)) << run);
+                    whole = whole && p0 < (1u << 18);
+                    more[k * gwords + w] = uint32_t(p0 & 0x3FFFFu) | ((g.q == 0 ? 0u : run + lm) << 18) | (15u << 23);
+                }
+            if (whole) {
+                table = std::move(more);
+                g.words = uint32_t(gwords * m);
+                g.magic = uint32_t(((uint64_t(1) << 32) + g.words - 1) / g.words);
+                g.lg += lm;
+                if (g.q != 31) { // records past the source block's lanes
+                    g.kq *= g.q >= lm ? 1u : m >> g.q;
+                    g.q = g.q >= lm ? g.q - lm : 0u;
+                }
+            }
+        }
         g.table = uint32_t(table.size());
         // a word of two pieces costs about two reads of one, of four about
         // four; the gather store takes the tile while the table fits the
@@ -1265,6 +1313,8 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
             a.flags |= kTileGatherStore;
             if (rq.dst.block % 4 != 0)
                 a.flags |= kTileGatherOdd;
+            if (whole)
+                a.flags |= kTileGatherWhole;
             a.dst.lds_base = uint32_t(base);
             a.dst.lds_bytes = uint32_t(table_bytes);
             a.lds_bytes = uint32_t(base + table_bytes);
@@ -1274,10 +1324,10 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
                 ta.e[f].dst_pos = uint32_t(rq.dst.base[f]); // the value of lane 0 in a destination block
         }
     }
-    // direct load: source leaf values in 16-byte granules of one leaf,
-    // starting 16-byte aligned, leaf sizes 4, 8 or 16, destination positions
-    // aligned to the leaf size, and at most kDirectLoadSlots granule slots
-    // per thread
+    // direct load: source leaf values in 16-byte granules of one leaf at any
+    // address (loads off the 16-byte grid: 6.2-6.3 TB/s of a copy's 6.45), leaf
+    // sizes 4, 8 or 16, destination positions aligned to the leaf size, and at
+    // most kDirectLoadSlots granule slots per thread
     // (a kept destination padding needs the destination region loaded first)
     if (preserve)
         a.flags |= kTilePreserve;
@@ -1299,7 +1349,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         const bool runs = granule_runs(a.src, sz) ||
                           (sz <= 2 && a.src.mode == kRecordMajor && rq.src.block % 16 == 0 &&
                            rq.src.lanes * sz >= 32 && (rq.src.lanes * sz) % 16 == 0);
-        dload = (sz == 1 || sz == 2 || whole) && runs && (e.src_addr & 15) == 0 &&
+        dload = (sz == 1 || sz == 2 || whole) && runs &&
                 ((aligned && whole) || (!(p.flags_in & kPlanNoSplit) && (sz <= 8 || aligned)));
         split_dst = split_dst || !aligned || !whole;
         wr_of[f] = std::min<uint32_t>(log2_move(dst_bits | sz), 7u);
@@ -1323,18 +1373,30 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         a.dst.lds_base = 0;
         a.lds_bytes = db;
     }
-    // field-major spans are short: rotate the first loading wave and the
-    // first storing thread from leaf to leaf so that every wave takes a share
-    const uint32_t nwaves = p.threads / 64;
-    uint32_t first_wave = 0, first_thread = 0;
-    for (size_t f = 0; f < F; f++) {
-        TileEntry& e = ta.e[f];
-        e.move |= (first_wave << 4) | (first_thread << 8);
-        uint64_t granules = (uint64_t(T) * e.size + 30) / 16;
-        if (a.flags & kTileDirectStore)
-            granules = (uint64_t(T) * e.size + 15) / 16;
-        first_wave = uint32_t((first_wave + (granules + 63) / 64) % nwaves);
-        first_thread = uint32_t((first_thread + granules) % p.threads);
+    uint64_t widest = 1;
+    for (size_t f = 0; f < F; f++)
+        widest = std::max<uint64_t>(widest, ta.e[f].size);
+    rotate_stores(p, T);
+    // chunks of 64 granules: as many places per leaf as the widest one fills
+    uint32_t lgc = 0;
+    while ((uint64_t(1024) << lgc) < uint64_t(T) * widest)
+        lgc++;
+    if (a.src.mode == kFieldMajor)
+        a.src.pad = lgc;
+    if (a.flags & kTileDirectStore) {
+        std::stable_sort(ta.e, ta.e + F, [](const TileEntry& x, const TileEntry& y) { return x.size > y.size; });
+        uint32_t ends[4] = {}; // leaves of at least 16, 8, 4 and 2 bytes
+        bool granules = true;
+        for (size_t f = 0; f < F; f++) {
+            const TileEntry& e = ta.e[f];
+            for (uint32_t c = 0; c < 4; c++)
+                ends[c] += e.size >= (16u >> c);
+            granules = granules && e.src_pos % 16 == 0 &&
+                       (a.src.mode == kFieldMajor || (rq.src.lanes * e.size % 16 == 0 && rq.src.block % 16 == 0));
+        }
+        a.dst.pad = ends[0] | (ends[1] << 7) | (ends[2] << 14) | (ends[3] << 21);
+        if (granules)
+            a.flags |= kTileReadsGranules;
     }
     if (total_bytes(rq.dst.blob_size) >= kStreamStoreBytes)
         a.flags |= kTileStreamStores;
@@ -1352,6 +1414,25 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
 void tile_grid(Plan& p, uint32_t wg_per_cu)
 {
     p.wg_per_cu = wg_per_cu;
+    // A copy far larger than the caches (kTileStreamStores) runs best with
+    // about 64 KiB of tiles in flight per compute unit: more only queues in
+    // front of the memory, and the lines in flight crowd the 4 MiB of L2 that
+    // 32 units share.  LDS set aside beyond a tile's own keeps the other
+    // workgroups out.  2^26 particles: AoS into SoA (3.5 KiB tiles) 640 us
+    // with 32 resident, 609 with 16, 665 with 12; AoSoA32 into AoS (14 KiB
+    // tiles) 620 with 8, 595 with 5 or 4; SoA into AoSoA32 628 with 11, 609
+    // with 6.  Below 1 GiB of destination it changes nothing (88.6 us with
+    // every count from 16 up for 2^23 particles).
+    // Only the modes that wait for memory alone: a gather store of shifted
+    // pieces needs every wave (the 49-byte mixed record from SoA into aligned
+    // AoS, 1.3 GB: 428 us with 10 groups, 529 with 5).
+    const uint32_t f = p.tile.h.flags;
+    if ((f & kTileStreamStores) && wg_per_cu == 0 &&
+        ((f & kTileGatherWhole) || ((f & kTileDirectStore) && !(f & kTileSplitSrc)))) {
+        const uint64_t tile = p.read_bytes * (uint64_t(1) << p.tile.h.log2_tile) / std::max<uint64_t>(p.tile.h.n, 1);
+        const uint32_t groups = uint32_t(std::max<uint64_t>((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), 4));
+        p.lds_bytes = std::max(p.tile.h.lds_bytes, kHardLdsBytes / groups / 512 * 512);
+    }
     p.workgroups = wg_per_cu ? std::min<uint64_t>(p.tiles, uint64_t(device_cu_count()) * wg_per_cu) : p.tiles;
 }
 
@@ -1367,13 +1448,19 @@ uint32_t default_tile(const Request& rq)
     return uint32_t(T);
 }
 
-// Default threads of a tile: about 112 source bytes per thread (128 threads
-// for a 14 KiB particle tile), a multiple of 64 in 64 .. 256.
-uint32_t default_threads(const Request& rq, uint32_t T)
+// Default threads of a direct store or gather store: about 112 source bytes
+// per thread (128 threads for a 14 KiB particle tile), a multiple of 64 in
+// 64 .. 256.
+uint32_t wide_threads(const Request& rq, uint32_t T, uint32_t bytes_per_thread)
 {
     const uint64_t bytes = uint64_t(T) * std::max<uint64_t>(rq.record.packed_size, 1);
-    const uint64_t th = (bytes / 112 + 63) / 64 * 64;
+    const uint64_t th = (bytes / bytes_per_thread + 63) / 64 * 64;
     return uint32_t(std::min<uint64_t>(std::max<uint64_t>(th, 64), kDefaultThreads));
+}
+
+uint32_t default_threads(const Request& rq, uint32_t T)
+{
+    return wide_threads(rq, T, 112);
 }
 
 void fill_naive(const Request& rq, Plan& p)
@@ -1554,12 +1641,34 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
         // four records per thread in the LDS remap
         auto nthreads = [&](uint32_t t) { return default_threads(rq, t); };
         uint32_t t = T ? T : default_tile(rq);
-        p.threads = threads ? threads : nthreads(t);
-        bool ok = fill_tile(rq, t, T ? kHardLdsBytes : kMaxLdsBytes, p);
+        // direct store of a small record (at most 64 bytes) into less than 1
+        // GiB: 256 records, a granule or two per thread (2^23 particles from
+        // AoS into SoA 88.6 us with 128 records and one wave, 85.7 with 256 of
+        // each; 10^6 listing 1 records 20.5 us with 512 records and 128
+        // threads, 16.3 so).  Only a field-major destination or one of long
+        // lane runs can take it.
+        bool small_store = false;
+        if (!T && !threads && rq.record.packed_size <= 64 && total_bytes(rq.dst.blob_size) < kStreamStoreBytes &&
+            rq.dst_stride.empty() && (rq.dst.lanes == 0 || rq.dst.lanes >= 32) && rq.src.lanes <= 256) {
+            p.threads = wide_threads(rq, 256, 28);
+            small_store = fill_tile(rq, 256, kMaxLdsBytes, p) && (p.tile.h.flags & kTileDirectStore);
+        }
+        if (!small_store)
+            p.threads = threads ? threads : nthreads(t);
+        bool ok = small_store || fill_tile(rq, t, T ? kHardLdsBytes : kMaxLdsBytes, p);
         while (!ok && !T && t > 16) {
             t /= 2;
             p.threads = threads ? threads : nthreads(t);
             ok = fill_tile(rq, t, kMaxLdsBytes, p);
+        }
+        if (ok && !threads && !(p.tile.h.flags & (kTileDirectStore | kTileGatherStore))) {
+            // staging and direct load spend more instructions per byte: about
+            // 48 source bytes per thread (listing 1's record from AoSoA16 into
+            // aligned AoS with its padding kept, 10^6 records: 23.7 us with 128
+            // threads, 20.7 with 256; the 49-byte mixed record from AoSoA8 into
+            // packed AoS, 2^21 records: 67.2 and 62.1)
+            p.threads = std::max(p.threads, wide_threads(rq, t, 48));
+            rotate_stores(p, t);
         }
         if (ok && !threads && !(p.tile.h.flags & (kTileDirectLoad | kTileDirectStore))) {
             // a source in granules of one leaf loads directly when every
@@ -1601,12 +1710,11 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             // field-major source the default gives 192 keeps them (the
             // lattice-Boltzmann cell from SoA multi-blob: 7% faster than
             // 256; from AoSoA32, 4% slower)
-            Plan q = p;
-            q.threads = 256;
-            if (fill_tile(rq, t, T ? kHardLdsBytes : kMaxLdsBytes, q) && (q.tile.h.flags & kTileGatherStore))
-                p = q;
+            p.threads = 256;
+            rotate_stores(p, t);
         }
-        if (ok && !T && !threads && (p.tile.h.flags & kTileDirectStore) && p.tile.h.src.mode == kRecordMajor) {
+        if (ok && !small_store && !T && !threads && (p.tile.h.flags & kTileDirectStore) &&
+            p.tile.h.src.mode == kRecordMajor) {
             // direct store of a small record (at most 32 bytes) from a
             // record-major source runs fastest with tiles of about 4 KiB and
             // one wave per workgroup (+2-5% on the particle pairs; a
@@ -1625,7 +1733,8 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
                     p = q;
             }
         }
-        if (ok && !T && !threads && (p.tile.h.flags & kTileDirectStore) && p.tile.h.src.mode == kFieldMajor) {
+        if (ok && !small_store && !T && !threads && (p.tile.h.flags & kTileDirectStore) &&
+            p.tile.h.src.mode == kFieldMajor) {
             // direct store from a field-major source reads one span per leaf:
             // where the widest leaf's span is under 2 KiB (the 156-byte
             // lattice-Boltzmann cell at 128 records), twice the records
@@ -1674,7 +1783,9 @@ void trace_plan(const Plan& p)
         const uint32_t f = p.tile.h.flags;
         mode = (f & kTileDirectLoad)    ? " mode=direct_load"
                : (f & kTileDirectStore) ? " mode=direct_store"
-               : (f & kTileGatherStore) ? ((f & kTileGatherOdd) ? " mode=gather_odd" : " mode=gather_store")
+               : (f & kTileGatherStore) ? ((f & kTileGatherOdd)     ? " mode=gather_odd"
+                                              : (f & kTileGatherWhole) ? " mode=gather_whole"
+                                                                       : " mode=gather_store")
                                         : " mode=staged";
         mode += " tile=" + std::to_string(1u << p.tile.h.log2_tile) + " entries=" +
                 std::to_string(p.tile.h.num_entries) + " lds=" + std::to_string(p.tile.h.lds_bytes);

@@ -34,7 +34,11 @@ struct TileSide {
     uint32_t lds_base;   // byte offset of this side's LDS region
     uint32_t lds_bytes;  // bytes of this side's LDS region
     // LDS position of record r of an entry: pos + (r >> pos_lg) * pos_k + (r & pos_m) * size
-    uint32_t pos_lg, pos_k, pos_m, pad;
+    uint32_t pos_lg, pos_k, pos_m;
+    uint32_t pad; // field-major source: log2 of the 64-granule chunk places per leaf; a gathered source
+                  // (kTileVirtualSrc): its reciprocal; a direct store's destination: the number of
+                  // leaves (sorted by size, largest first) of 16, of 8 and more, of 4 and more and of
+                  // 2 bytes and more, 7 bits each
 };
 
 // One entry of the remap: a leaf, or a destination gap inside every record
@@ -47,8 +51,7 @@ struct TileEntry {
     uint32_t dst_pos;  // LDS byte of record 0 in the destination region
     uint32_t size;     // bytes per record
     uint32_t move;     // bits 0-2: log2 of the move width (1 .. 16 bytes); bit 3: split move
-                       // (kMoveSplit); bits 4-7: first loading wave of this leaf's source span;
-                       // bits 8-19: first storing thread of this leaf's destination span;
+                       // (kMoveSplit); bits 8-19: first storing thread of this leaf's destination span;
                        // bits 20-22: log2 of the read alignment; bits 24-26: log2 of the write
                        // alignment (split moves); with kTileDirectStore, bits 20-23: the
                        // destination span's phase in values, (dst_addr mod 16) / size;
@@ -109,7 +112,8 @@ struct TileHeader {
     uint32_t lds_bytes;
     uint32_t flags;       // kTileDirectStore, kTileDirectLoad, kTilePreserve, kTileGatherStore,
                           // kTileStreamStores, kTileStreamLoads, kTileGatherOdd, kTileVirtualSrc,
-                          // kTileVirtualDst, kTileSplitSrc, kTileSplitDst
+                          // kTileVirtualDst, kTileSplitSrc, kTileSplitDst, kTileGatherWhole,
+                          // kTileReadsGranules
     uint32_t slots;       // kTileDirectLoad: granule slots of a tile (a multiple of 64);
                           // kTileVirtualSrc: the chunks after the entries
     TileSide src, dst;
@@ -118,11 +122,12 @@ struct TileHeader {
 // Destination field-major with 16-byte aligned leaf spans and leaf sizes of 1,
 // 2, 4, 8 or 16 bytes: every 16-byte granule of a destination span holds whole
 // values of one leaf, gathered straight from the source region into registers
-// and stored; the tile needs no destination region in LDS.
+// and stored; the tile needs no destination region in LDS, only 16 bytes per
+// leaf (at dst.lds_base).
 constexpr uint32_t kTileDirectStore = 1;
 
-// Source field-major with 16-byte aligned leaf spans and leaf sizes of 4, 8
-// or 16 bytes: every thread loads its granules of the source spans into
+// Source field-major (leaf spans at any address) or in AoSoA lane runs, with
+// leaf sizes of 4, 8 or 16 bytes: every thread loads its granules of the source spans into
 // registers (all loads of the tile in flight at once) and writes the values to
 // their destination positions in LDS; the tile needs no source region.  Leaf f
 // owns slots [src_pos, src_pos + 64 * ceil(G_f / 64)) of the tile's granule
@@ -169,6 +174,17 @@ constexpr uint32_t kTileStreamLoads = 32;
 // one by one): the gather runs in its own kernel variant, so that the common
 // case keeps its registers.
 constexpr uint32_t kTileGatherOdd = 64;
+
+// A gathering tile whose super-block is whole 16-byte granules and whose
+// every word is one piece of four bytes at a 4-byte aligned place of the
+// source region in every super-block, or padding (records of 4- and 8-byte
+// leaves): it runs in its own kernel variant, without shifts and masks.
+constexpr uint32_t kTileGatherWhole = 2048;
+
+// Direct store from a source whose 16 / size consecutive values of a leaf
+// follow one another at 16-byte aligned places of the source region
+// (field-major, or AoSoA lane runs of whole granules): a granule is one read.
+constexpr uint32_t kTileReadsGranules = 4096;
 
 // A source gathered from several parts (a Split source, sec. 3.7): the tile's
 // source region is a run of virtual blocks of L records and K bytes (h.src

@@ -41,6 +41,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4))); // 16 bytes at a 4-byte-aligned address
+typedef u32x4 u32x4_a1 __attribute__((aligned(1))); // 16 bytes at any address
 
 // The Heatmap counters of a counted launch (sec. 3.7 Heatmap): set with
 // hipMemcpyAsync before the launch.  A counted kernel variant adds one to a
@@ -97,6 +98,11 @@ __device__ __forceinline__ uint32_t wave_id()
 
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 
+__device__ __forceinline__ uint64_t uniform64(uint64_t x)
+{
+    return uniform(uint32_t(x)) | (uint64_t(uniform(uint32_t(x >> 32))) << 32);
+}
+
 // Copies a read-only table record word by word (scalar loads for a uniform address).
 template <typename T>
 __device__ __forceinline__ T load_const(const CONSTANT T* p)
@@ -109,6 +115,20 @@ __device__ __forceinline__ T load_const(const CONSTANT T* p)
     for (uint32_t k = 0; k < sizeof(T) / 4; k++)
         dst[k] = src[k];
     return v;
+}
+
+// The kernel's argument block, read afresh where this is called.  A loop over
+// tiles whose body reads the arguments as usual has the compiler prepare
+// every value that any of the body's branches derives from them before the
+// loop, 200 scalar instructions and a dozen spills to VGPR lanes in kernels
+// whose workgroups run one tile of 300.
+template <typename Args>
+__device__ __forceinline__ const CONSTANT Args* kernel_arguments(const Args& a)
+{
+    (void)a; // the kernel's only parameter, at the start of the segment
+    const CONSTANT Args* p = (const CONSTANT Args*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
 }
 
 // 16-byte loads of source bytes.  A copy reads every source byte once;
@@ -135,6 +155,33 @@ __device__ __forceinline__ u32x4 load_src_a4(const GLOBAL u32x4_a4* p)
         return __builtin_nontemporal_load(p);
     else
         return *p;
+}
+
+// The same at any address.
+template <bool kOnce, bool kCount = false>
+__device__ __forceinline__ u32x4 load_src_a1(const GLOBAL u32x4_a1* p)
+{
+    note_read<kCount>(uint64_t(p), 16);
+    if constexpr (kOnce)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
+// The first n < 16 bytes at address a, then zeros.
+template <bool kCount>
+__device__ __forceinline__ u32x4 load_bytes(uint64_t a, uint32_t n)
+{
+    u32x4 v{0u, 0u, 0u, 0u};
+#pragma clang loop unroll(disable)
+    for (uint32_t b = 0; b < n; b++) {
+        const uint32_t x = uint32_t(gget<kCount, uint8_t>(a + b)) << (8u * (b & 3u));
+        v.x |= b < 4u ? x : 0u;
+        v.y |= (b >> 2) == 1u ? x : 0u;
+        v.z |= (b >> 2) == 2u ? x : 0u;
+        v.w |= (b >> 2) == 3u ? x : 0u;
+    }
+    return v;
 }
 
 // A 16-byte store of destination bytes; kStream marks it nontemporal, for
@@ -170,26 +217,75 @@ __device__ __forceinline__ void lds_dma16(uint64_t gaddr, uint32_t lds_addr)
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gaddr), "s"(lds_addr)
                      : "memory", "m0");
 }
+// The same from a uniform base plus 32 bits per lane: no vector instruction
+// computes an address.
+template <bool kOnce, bool kCount = false>
+__device__ __forceinline__ void lds_dma16_base(uint64_t base, uint32_t off, uint32_t lds_addr)
+{
+    note_read<kCount>(base + off, 16);
+    if constexpr (kOnce)
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(off), "s"(base), "s"(lds_addr)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds_addr)
+                     : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Loads bytes [gstart, gstart + len) into LDS at lds_region + (gstart & 15):
 // whole 16-byte granules from gstart rounded down, 64 granules (1 KiB) per
-// wave instruction; chunk c of the span goes to wave (c + first_wave) mod
-// nwaves.  A granule that holds a byte of the span lies in the same page as
+// wave instruction; chunk c of the span goes to wave c mod nwaves.  A granule that holds a byte of the span lies in the same page as
 // that byte, so the rounding never reaches an unmapped page; the extra bytes
 // are never used.
 template <bool kOnce, bool kCount = false>
 __device__ __forceinline__ void load_span(uint64_t gstart, uint32_t len, uint32_t lds_region, uint32_t wave,
-                                          uint32_t nwaves, uint32_t first_wave, uint32_t lane, uint32_t lds_base)
+                                          uint32_t nwaves, uint32_t lane, uint32_t lds_base)
 {
     const uint32_t shift = uint32_t(gstart) & 15u;
     const uint64_t g0 = gstart - shift;
     const uint32_t G = (shift + len + 15u) >> 4;
-    const uint32_t c0 = wave >= first_wave ? wave - first_wave : wave + nwaves - first_wave;
-    for (uint32_t c = c0; c * 64u < G; c += nwaves) {
-        const uint32_t gi = c * 64u + lane;
-        if (gi < G)
-            lds_dma16<kOnce, kCount>(g0 + uint64_t(gi) * 16u, uniform(lds_base + lds_region + c * 1024u));
+    for (uint32_t c = wave; c * 64u < G; c += nwaves)
+        if (lane < G - c * 64u)
+            lds_dma16_base<kOnce, kCount>(uniform64(g0 + uint64_t(c) * 1024u), lane * 16u,
+                                          uniform(lds_base + lds_region + c * 1024u));
+}
+
+// Global start of the field-major span of one leaf for the records of the
+// tile that starts at record i0.
+__device__ __forceinline__ uint64_t field_span_start(uint64_t addr, const TileSide& s, uint64_t i0, uint32_t size)
+{
+    if (s.lanes == 0)
+        return addr + i0 * size;
+    return addr + (i0 >> s.log2_lanes) * s.block + (i0 & (s.lanes - 1)) * size;
+}
+
+// Loads the leaf spans of a field-major source (records i0 .. i0 + nv - 1) in
+// chunks of 64 granules, 2^lgc chunk places per leaf (h.src.pad): the waves
+// take the places in turn, so that each wave runs only its own chunks.  A
+// span off the 16-byte grid has one granule more than its values fill, which
+// goes with its last chunk.  (Every wave walking every leaf took 60 scalar
+// instructions per leaf and wave; the scalar unit, one per compute unit, then
+// bound the copies of 2^26 particles.)
+template <bool kOnce, bool kCount, typename Entries>
+__device__ __forceinline__ void load_fields(const TileHeader& h, Entries ent, uint64_t i0, uint32_t nv, uint32_t wave,
+                                            uint32_t nwaves, uint32_t lane, uint32_t lds_base)
+{
+    const uint32_t lgc = h.src.pad, places = h.num_leaves << lgc;
+    for (uint32_t c = wave; c < places; c += nwaves) {
+        const uint32_t f = c >> lgc, sub = c & ((1u << lgc) - 1u);
+        const auto& e = ent(f);
+        const uint64_t start = field_span_start(e.src_addr, h.src, i0, e.size);
+        const uint32_t shift = uint32_t(start) & 15u, len = nv * e.size;
+        const uint32_t G = (shift + len + 15u) >> 4;          // granules the span touches
+        const uint32_t last = (max(len, 1u) - 1u) >> 10;      // its last chunk
+        if (sub > last)
+            continue;
+        const uint64_t base = uniform64(start - shift + uint64_t(sub) * 1024u);
+        const uint32_t at = uniform(lds_base + (e.src_pos & ~15u) + sub * 1024u);
+        if (lane < G - sub * 64u)
+            lds_dma16_base<kOnce, kCount>(base, lane * 16u, at);
+        if (sub == last && lane + 64u < G - sub * 64u)
+            lds_dma16_base<kOnce, kCount>(base, lane * 16u + 1024u, at + 1024u);
     }
 }
 
@@ -254,15 +350,6 @@ __device__ __forceinline__ void store_span(uint64_t gstart, uint32_t len, uint32
     }
 }
 
-// Global start of the field-major span of one leaf for the records of the
-// tile that starts at record i0.
-__device__ __forceinline__ uint64_t field_span_start(uint64_t addr, const TileSide& s, uint64_t i0, uint32_t size)
-{
-    if (s.lanes == 0)
-        return addr + i0 * size;
-    return addr + (i0 >> s.log2_lanes) * s.block + (i0 & (s.lanes - 1)) * size;
-}
-
 // Device address of 16-byte granule g of a leaf's values in a tile, from the
 // leaf's tile base; `lg` is log2 of the leaf size.  A field-major side holds
 // the values as one span; an AoSoA side as lane runs of 2^(log2 L + lg - 4)
@@ -312,6 +399,33 @@ __device__ __forceinline__ void move4(uint8_t* lds, uint32_t sp, uint32_t dp, co
             if (r < nd)
                 *(T*)(lds + dp + (r >> d.pos_lg) * d.pos_k + (r & d.pos_m) * size + k) = v[j];
         }
+    }
+}
+
+// move4 for one entry of a whole tile (2^lt records, all with values): the
+// general form tests every record twice.
+template <typename T>
+__device__ __forceinline__ void move_whole(uint8_t* lds, uint32_t sp, uint32_t dp, const TileSide& s, const TileSide& d,
+                                           uint32_t size, uint32_t n, uint32_t tid, uint32_t nthr)
+{
+    for (uint32_t k = 0; k < size; k += sizeof(T)) {
+        uint32_t r = tid;
+        for (; r + 3u * nthr < n; r += 4u * nthr) {
+            T v[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++) {
+                const uint32_t q = r + j * nthr;
+                v[j] = *(const T*)(lds + sp + (q >> s.pos_lg) * s.pos_k + (q & s.pos_m) * size + k);
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++) {
+                const uint32_t q = r + j * nthr;
+                *(T*)(lds + dp + (q >> d.pos_lg) * d.pos_k + (q & d.pos_m) * size + k) = v[j];
+            }
+        }
+        for (; r < n; r += nthr)
+            *(T*)(lds + dp + (r >> d.pos_lg) * d.pos_k + (r & d.pos_m) * size + k) =
+                *(const T*)(lds + sp + (r >> s.pos_lg) * s.pos_k + (r & s.pos_m) * size + k);
     }
 }
 
@@ -440,7 +554,103 @@ __device__ __forceinline__ void direct_store_leaf(const uint8_t* lds, uint32_t s
     }
 }
 
-// Direct store of a tile: every leaf in turn, at the width of its values.
+// Direct store of a whole tile (all records with values), the leaves of one
+// width: every thread takes granules of all these leaves in turn, each lane
+// its own leaf, whose tile address and source position come from a table in
+// LDS (direct_table).  No granule is partial and none needs a test, and no
+// instruction is spent on a leaf as a whole: walking the leaves with their
+// fields in scalar registers took 75 scalar instructions per leaf and wave,
+// and the scalar unit, one per compute unit, was busy for 500 of the 614 us
+// that 2^26 particles took from AoS into SoA.
+// A granule's records are r0 .. r0 + per - 1 with r0 a multiple of per, so
+// their source positions are that of r0 plus amounts that are the same for
+// every granule; where they follow one another at 16-byte aligned positions
+// (kTileReadsGranules) they are one read.  A field-major span that starts off
+// the 16-byte grid is stored with 16-byte stores at its own alignment (a copy
+// with such stores measured 6.0 TB/s, with aligned ones 6.45; partial granules
+// value by value were 11 of 17.5 store instructions per wave of a 49-byte
+// record's copy into single-blob SoA).
+template <typename T, bool kDstRecordMajor, bool kStream, bool kCount, bool kVirtualDst, bool kSplit>
+__device__ __forceinline__ void direct_store_width(const TileHeader& h, uint32_t first, uint32_t end, uint32_t tid,
+                                                   uint32_t nthr, const uint8_t* lds)
+{
+    if (first == end)
+        return;
+    constexpr uint32_t per = 16 / sizeof(T);
+    constexpr uint32_t lgper = per == 16 ? 4 : per == 8 ? 3 : per == 4 ? 2 : per == 2 ? 1 : 0, lg = 4 - lgper;
+    const u32x4* tab = (const u32x4*)(lds + h.dst.lds_base);
+    const uint32_t gl = h.log2_tile - lgper, n = (end - first) << gl;
+    const uint32_t slg = h.src.pos_lg, sk = h.src.pos_k, sm = h.src.pos_m;
+    const bool whole_reads = (h.flags & kTileReadsGranules) != 0;
+    for (uint32_t i = tid; i < n; i += nthr) {
+        const u32x4 e = tab[first + (i >> gl)];
+        const uint32_t g = i & ((1u << gl) - 1u), r0 = g << lgper;
+        const uint32_t p = e.z + (r0 >> slg) * sk + ((r0 & sm) << lg);
+        union {
+            u32x4 v;
+            T t[per];
+        } u;
+        if (!kSplit && whole_reads) {
+            u.v = *(const u32x4*)(lds + p);
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < per; j++) {
+                const uint32_t q = p + (j >> slg) * sk + ((j & sm) << lg);
+                if constexpr (kSplit && sizeof(T) >= 2 && sizeof(T) <= 8)
+                    u.t[j] = read_split<T>(lds, q, e.w);
+                else
+                    u.t[j] = *(const T*)(lds + q);
+            }
+        }
+        uint32_t off = g << 4;
+        if constexpr (kDstRecordMajor) {
+            const uint32_t run = h.dst.log2_lanes + lg - 4u;
+            off = (g >> run) * (kVirtualDst ? e.w : uint32_t(h.dst.block)) + ((g & ((1u << run) - 1u)) << 4);
+        }
+        const uint64_t at = (e.x | (uint64_t(e.y) << 32)) + off;
+        note_write<kCount>(at, 16);
+        if constexpr (kStream)
+            __builtin_nontemporal_store(u.v, (GLOBAL u32x4_a1*)at);
+        else
+            *(GLOBAL u32x4_a1*)at = u.v;
+    }
+}
+
+// The table of direct_store_width: per leaf its device address in tile t, its
+// source position, and the bytes between its runs (kVirtualDst) or log2 of its
+// source alignment (kSplit).  The barrier that publishes the source region
+// publishes it.
+template <bool kDstRecordMajor, bool kVirtualDst, typename Entries>
+__device__ __forceinline__ void direct_table(const TileHeader& h, Entries ent, uint64_t t, uint64_t i0, uint8_t* lds)
+{
+    u32x4* tab = (u32x4*)(lds + h.dst.lds_base);
+    for (uint32_t f = threadIdx.x; f < h.num_leaves; f += blockDim.x) {
+        const auto& e = ent(f);
+        uint64_t at;
+        if constexpr (kVirtualDst)
+            at = e.dst_addr + t * (uint64_t(e.dst_pos) << (h.log2_tile - h.dst.log2_lanes));
+        else
+            at = leaf_tile_base<kDstRecordMajor>(e.dst_addr, h.dst, t, i0, e.size);
+        tab[f] = u32x4{uint32_t(at), uint32_t(at >> 32), e.src_pos, kVirtualDst ? e.dst_pos : (e.move >> 24) & 7u};
+    }
+}
+
+// Direct store of a whole tile: the leaves are sorted by width, widest first
+// (the planner), and h.dst.pad holds where the widths end.
+template <bool kDstRecordMajor, bool kStream, bool kCount, bool kVirtualDst, bool kSplit>
+__device__ __forceinline__ void direct_store_whole(const TileHeader& h, uint32_t tid, uint32_t nthr, const uint8_t* lds)
+{
+    const uint32_t e16 = h.dst.pad & 127u, e8 = (h.dst.pad >> 7) & 127u, e4 = (h.dst.pad >> 14) & 127u,
+                   e2 = (h.dst.pad >> 21) & 127u;
+    direct_store_width<u32x4, kDstRecordMajor, kStream, kCount, kVirtualDst, false>(h, 0, e16, tid, nthr, lds);
+    direct_store_width<uint64_t, kDstRecordMajor, kStream, kCount, kVirtualDst, kSplit>(h, e16, e8, tid, nthr, lds);
+    direct_store_width<uint32_t, kDstRecordMajor, kStream, kCount, kVirtualDst, kSplit>(h, e8, e4, tid, nthr, lds);
+    direct_store_width<uint16_t, kDstRecordMajor, kStream, kCount, kVirtualDst, kSplit>(h, e4, e2, tid, nthr, lds);
+    direct_store_width<uint8_t, kDstRecordMajor, kStream, kCount, kVirtualDst, false>(h, e2, h.num_leaves, tid, nthr, lds);
+}
+
+// Direct store of a tile at the width of its values; the last, partial tile
+// goes leaf by leaf.
 // kVirtualDst: each leaf's runs of L values lie in its own part, e.dst_pos
 // bytes apart (kTileVirtualDst).
 // kSplit: leaves whose source positions are aligned below their size (bits
@@ -451,6 +661,10 @@ __device__ __forceinline__ void direct_store_tile(const TileHeader& h, Entries e
                                                   uint32_t nv, uint32_t nd, uint32_t tid, uint32_t nthr,
                                                   const uint8_t* lds)
 {
+    if (nv == 1u << h.log2_tile && nd == nv) {
+        direct_store_whole<kDstRecordMajor, kStream, kCount, kVirtualDst, kSplit>(h, tid, nthr, lds);
+        return;
+    }
     for (uint32_t f = 0; f < h.num_leaves; f++) {
         const auto& e = ent(f);
         TileSide d = h.dst;
@@ -467,23 +681,13 @@ __device__ __forceinline__ void direct_store_tile(const TileHeader& h, Entries e
         const uint32_t rot = (e.move >> 8) & 4095u;
         const uint32_t ph = (e.move >> 20) & 15u;
         const uint32_t sp = e.src_pos;
-        if constexpr (kSplit) {
-            const uint32_t rd = (e.move >> 24) & 7u;
-            switch (e.move & 7u) {
-            case 4: direct_store_leaf<u32x4, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
-            case 3: direct_store_leaf<uint64_t, kDstRecordMajor, kStream, kCount, true>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
-            case 2: direct_store_leaf<uint32_t, kDstRecordMajor, kStream, kCount, true>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
-            case 1: direct_store_leaf<uint16_t, kDstRecordMajor, kStream, kCount, true>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
-            default: direct_store_leaf<uint8_t, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
-            }
-            continue;
-        }
+        const uint32_t rd = kSplit ? (e.move >> 24) & 7u : 4u;
         switch (e.move & 7u) {
-        case 4: direct_store_leaf<u32x4, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
-        case 3: direct_store_leaf<uint64_t, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
-        case 2: direct_store_leaf<uint32_t, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
-        case 1: direct_store_leaf<uint16_t, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
-        default: direct_store_leaf<uint8_t, kDstRecordMajor, kStream, kCount>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph); break;
+        case 4: direct_store_leaf<u32x4, kDstRecordMajor, kStream, kCount, false>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
+        case 3: direct_store_leaf<uint64_t, kDstRecordMajor, kStream, kCount, kSplit>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
+        case 2: direct_store_leaf<uint32_t, kDstRecordMajor, kStream, kCount, kSplit>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
+        case 1: direct_store_leaf<uint16_t, kDstRecordMajor, kStream, kCount, kSplit>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
+        default: direct_store_leaf<uint8_t, kDstRecordMajor, kStream, kCount, false>(lds, sp, h.src, d, gdst, nv, ne, tid, nthr, rot, ph, rd); break;
         }
     }
 }
@@ -514,9 +718,15 @@ __device__ __forceinline__ void direct_load_tile(const TileHeader& h, Entries en
             f++;
         const auto& e = ent(f);
         const uint32_t g = q0 + lane - e.src_pos; // granule within the leaf's values of the tile
-        if (g * 16u < nv * e.size)
-            v[j] = load_src<kOnce, kCount>((const GLOBAL u32x4*)leaf_granule_addr<kSrcRecordMajor>(
-                leaf_tile_base<kSrcRecordMajor>(e.src_addr, h.src, t, i0, e.size), h.src, g, e.move & 7u));
+        const uint32_t left = nv * e.size; // bytes of the leaf's values in this tile
+        if (g * 16u < left) {
+            const uint64_t a = leaf_granule_addr<kSrcRecordMajor>(
+                leaf_tile_base<kSrcRecordMajor>(e.src_addr, h.src, t, i0, e.size), h.src, g, e.move & 7u);
+            if (kSrcRecordMajor || g * 16u + 16u <= left || (a & 15u) == 0)
+                v[j] = load_src_a1<kOnce, kCount>((const GLOBAL u32x4_a1*)a);
+            else // the span's last granule off the 16-byte grid could reach past the blob's page
+                v[j] = load_bytes<kCount>(a, left - g * 16u);
+        }
     }
     f = 0;
 #pragma unroll
@@ -596,8 +806,8 @@ __device__ __forceinline__ void direct_load_tile(const TileHeader& h, Entries en
 
 // Gather store (kTileGatherStore): copies the planner's word table into LDS
 // (at dst.lds_base) once per workgroup; the first tile's barrier publishes it.
-__device__ __forceinline__ void gather_table(const TileHeader& h, const TileGather& gg, const uint32_t* table,
-                                             uint8_t* lds)
+template <typename Table>
+__device__ __forceinline__ void gather_table(const TileHeader& h, const TileGather& gg, Table table, uint8_t* lds)
 {
     uint32_t* tab = (uint32_t*)(lds + h.dst.lds_base);
     for (uint32_t k = threadIdx.x; k < gg.table; k += blockDim.x)
@@ -718,6 +928,41 @@ __device__ __forceinline__ void gather_store_tile(const TileHeader& h, const Til
     }
 }
 
+// gather_store_tile where every word is one aligned word of the source (or
+// padding) and a super-block is whole granules (kTileGatherWhole): a granule's
+// four words lie in one super-block, their entries are one read, and each is
+// one LDS read at a position without shifts, masks or a second window.  The
+// general form takes 25 to 30 vector instructions per word, which bound the
+// particle's and the lattice-Boltzmann cell's gathers on VALU issue.
+template <bool kStream, bool kCount>
+__device__ __forceinline__ void gather_whole_tile(const TileHeader& h, const TileGather& gg, uint64_t t, uint32_t nd,
+                                                  uint32_t tid, uint32_t nthr, const uint8_t* lds)
+{
+    const u32x4* tab = (const u32x4*)(lds + h.dst.lds_base);
+    const uint32_t span = uint32_t(((uint64_t(nd) + h.dst.lanes - 1) >> h.dst.log2_lanes) * h.dst.block);
+    const uint64_t base = uniform64(h.dst.span_base + t * h.dst.tile_bytes);
+    const uint32_t qm = (1u << gg.q) - 1u;
+    for (uint32_t u = tid * 4u; u * 4u < span; u += nthr * 4u) {
+        const uint32_t blk = __umulhi(u, gg.magic);
+        const u32x4 e = tab[(u - blk * gg.words) >> 2];
+        const uint32_t bq = (blk >> gg.q) * gg.kq, bm = blk & qm;
+        u32x4 v;
+#pragma unroll
+        for (uint32_t c = 0; c < 4; c++) {
+            const uint32_t p = (e[c] & 0x3FFFFu) + bq + (bm << ((e[c] >> 18) & 31u));
+            v[c] = (e[c] >> 23) ? *(const uint32_t*)(lds + p) : 0u;
+        }
+        if (u * 4u + 16u <= span) {
+            store16<kStream, kCount>((GLOBAL u32x4*)((GLOBAL uint8_t*)base + u * 4u), v);
+        } else { // the span's last granule: blocks of whole words
+#pragma unroll
+            for (uint32_t c = 0; c < 4; c++)
+                if ((u + c) * 4u < span)
+                    gput<kCount>(base + (u + c) * 4u, v[c]);
+        }
+    }
+}
+
 // One tile: every wave issues its share of the source loads straight into
 // LDS, then all threads move the values to their destination positions
 // inside LDS, then all threads store the destination span(s).  `ent(k)`
@@ -732,7 +977,8 @@ enum : uint32_t {
     kModeDirectLoad = 3,
     kModeGatherStore = 4,
     kModeGatherOdd = 5, // gather store with kTileGatherOdd
-    kModeStreamUnits = 6 // the batch kernel over long-run items only
+    kModeStreamUnits = 6, // the batch kernel over long-run items only
+    kModeGatherWhole = 7  // gather store with kTileGatherWhole
 };
 // added to a mode: the tile's 16-byte destination stores are nontemporal
 constexpr uint32_t kModeStreamStores = 8;
@@ -770,7 +1016,7 @@ __device__ __forceinline__ void tile_body(const TileHeader& h, Entries ent, uint
     const bool split_dst = kSplitDst || (Mode == kModeAny && (h.flags & kTileSplitDst));
     const bool dload = Mode == kModeDirectLoad || (Mode == kModeAny && (h.flags & kTileDirectLoad));
     const bool dstore = Mode == kModeDirectStore || (Mode == kModeAny && (h.flags & kTileDirectStore));
-    const bool gstore = Mode == kModeGatherStore || Mode == kModeGatherOdd ||
+    const bool gstore = Mode == kModeGatherStore || Mode == kModeGatherOdd || Mode == kModeGatherWhole ||
                         (Mode == kModeAny && (h.flags & kTileGatherStore));
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
     const uint32_t lane = tid & 63u, wave = wave_id(), nwaves = nthr >> 6;
@@ -801,18 +1047,23 @@ __device__ __forceinline__ void tile_body(const TileHeader& h, Entries ent, uint
             load_virtual<kOnce, kCount>(h, ent, t, nv, wave, nwaves, lane, lds_base);
         } else if (h.src.mode == kRecordMajor) {
             const uint32_t len = uint32_t(((uint64_t(nv) + h.src.lanes - 1) >> h.src.log2_lanes) * h.src.block);
-            load_span<kOnce, kCount>(h.src.span_base + t * h.src.tile_bytes, len, h.src.lds_base, wave, nwaves, 0, lane, lds_base);
+            load_span<kOnce, kCount>(h.src.span_base + t * h.src.tile_bytes, len, h.src.lds_base, wave, nwaves, lane, lds_base);
         } else {
-            for (uint32_t f = 0; f < h.num_leaves; f++) {
-                const auto& e = ent(f);
-                load_span<kOnce, kCount>(field_span_start(e.src_addr, h.src, i0, e.size), nv * e.size, e.src_pos & ~15u, wave,
-                          nwaves, (e.move >> 4) & 15u, lane, lds_base);
-            }
+            load_fields<kOnce, kCount>(h, ent, i0, nv, wave, nwaves, lane, lds_base);
         }
     }
     if (preserve && !dstore && h.dst.mode == kRecordMajor) {
         const uint32_t len = uint32_t(((uint64_t(nd) + h.dst.lanes - 1) >> h.dst.log2_lanes) * h.dst.block);
-        load_span<false, kCount>(h.dst.span_base + t * h.dst.tile_bytes, len, h.dst.lds_base, wave, nwaves, 0, lane, lds_base);
+        load_span<false, kCount>(h.dst.span_base + t * h.dst.tile_bytes, len, h.dst.lds_base, wave, nwaves, lane, lds_base);
+    }
+    // (the table's entries load while the source does)
+    if (dstore && nv == T && ns == T) {
+        if (kVirtualDst)
+            direct_table<true, true>(h, ent, t, i0, lds);
+        else if (h.dst.mode == kRecordMajor)
+            direct_table<true, false>(h, ent, t, i0, lds);
+        else
+            direct_table<false, false>(h, ent, t, i0, lds);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -839,7 +1090,9 @@ __device__ __forceinline__ void tile_body(const TileHeader& h, Entries ent, uint
             zero_source_records(h, ent, nv, nd, tid, nthr, lds);
             __syncthreads();
         }
-        if (Mode == kModeGatherOdd || (Mode == kModeAny && (h.flags & kTileGatherOdd)))
+        if (Mode == kModeGatherWhole)
+            gather_whole_tile<kStream, kCount>(h, *gg, t, nd, tid, nthr, lds);
+        else if (Mode == kModeGatherOdd || (Mode == kModeAny && (h.flags & kTileGatherOdd)))
             gather_store_tile<kStream, true, kCount>(h, *gg, t, nd, tid, nthr, lds);
         else
             gather_store_tile<kStream, false, kCount>(h, *gg, t, nd, tid, nthr, lds);
@@ -880,6 +1133,16 @@ __device__ __forceinline__ void tile_body(const TileHeader& h, Entries ent, uint
             }
             continue;
         }
+        if (!gap && nv == T) {
+            switch (e.move & 7u) {
+            case 4: move_whole<u32x4>(lds, e.src_pos, e.dst_pos, h.src, h.dst, e.size, T, tid, nthr); break;
+            case 3: move_whole<uint64_t>(lds, e.src_pos, e.dst_pos, h.src, h.dst, e.size, T, tid, nthr); break;
+            case 2: move_whole<uint32_t>(lds, e.src_pos, e.dst_pos, h.src, h.dst, e.size, T, tid, nthr); break;
+            case 1: move_whole<uint16_t>(lds, e.src_pos, e.dst_pos, h.src, h.dst, e.size, T, tid, nthr); break;
+            default: move_whole<uint8_t>(lds, e.src_pos, e.dst_pos, h.src, h.dst, e.size, T, tid, nthr); break;
+            }
+            continue;
+        }
         for (uint32_t r0 = tid; r0 < ns; r0 += 4u * nthr) {
             switch (e.move & 7u) {
             case 4: move4<u32x4>(lds, e.src_pos, e.dst_pos, h.src, h.dst, e.size, r0, nthr, nv, ns, gap); break;
@@ -910,7 +1173,6 @@ __global__ void __launch_bounds__(1024) tile_kernel(const TileArgs a)
 {
     constexpr uint32_t Mode = ModeBits & 7u;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    auto ent = [&](uint32_t k) -> const TileEntry& { return a.e[k]; };
     const uint64_t nt = a.h.num_tiles;
     uint64_t t = blockIdx.x, stride = gridDim.x;
     if (Mode != kModeStaged && gridDim.x == nt) {
@@ -921,16 +1183,22 @@ __global__ void __launch_bounds__(1024) tile_kernel(const TileArgs a)
         // the plain order.  One call site of tile_body: a second inlined
         // copy changed how the compiler unrolled the direct-load registers
         // and moved them to scratch.
-        const uint64_t b = blockIdx.x, x = b & 7u, k = b >> 3, q = nt >> 3, rem = nt & 7u;
-        t = x * q + min(x, rem) + k;
+        const uint32_t b = blockIdx.x, n32 = uint32_t(nt), x = b & 7u;
+        t = x * (n32 >> 3) + min(x, n32 & 7u) + (b >> 3);
         stride = nt;
     }
-    if (Mode == kModeGatherStore || Mode == kModeGatherOdd) // the word table follows the entries (and chunks)
+    if (Mode == kModeGatherStore || Mode == kModeGatherOdd || Mode == kModeGatherWhole) { // the word table follows the entries (and chunks)
+        const CONSTANT TileArgs* p = kernel_arguments(a);
         gather_table(a.h, a.gather,
-                     reinterpret_cast<const uint32_t*>(a.e + a.h.num_entries + ((ModeBits & kModeVirtualSrc) ? a.h.slots : 0u)),
-                     lds);
+                     (const CONSTANT uint32_t*)(p->e + a.h.num_entries + ((ModeBits & kModeVirtualSrc) ? a.h.slots : 0u)), lds);
+    }
     for (; t < nt; t += stride) {
-        tile_body<ModeBits>(a.h, ent, t, lds, &a.gather);
+        const CONSTANT TileArgs* p = kernel_arguments(a);
+        const TileHeader h = load_const(&p->h);
+        TileGather gg{};
+        if (Mode == kModeGatherStore || Mode == kModeGatherOdd || Mode == kModeGatherWhole)
+            gg = load_const(&p->gather);
+        tile_body<ModeBits>(h, [&](uint32_t k) -> const CONSTANT TileEntry& { return p->e[k]; }, t, lds, &gg);
         if (t + stride < nt)
             __syncthreads();
     }
@@ -943,7 +1211,7 @@ __global__ void __launch_bounds__(1024) tile_count_kernel(const TileArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     auto ent = [&](uint32_t k) -> const TileEntry& { return a.e[k]; };
-    if ((Mode & 7u) == kModeGatherStore || (Mode & 7u) == kModeGatherOdd)
+    if ((Mode & 7u) == kModeGatherStore || (Mode & 7u) == kModeGatherOdd || (Mode & 7u) == kModeGatherWhole)
         gather_table(a.h, a.gather,
                      reinterpret_cast<const uint32_t*>(a.e + a.h.num_entries + ((Mode & kModeVirtualSrc) ? a.h.slots : 0u)),
                      lds);
@@ -1070,7 +1338,8 @@ __device__ __forceinline__ void batch_unit(const BatchArgs& a, const CONSTANT ui
     const uint64_t u = g - begin[j];
     // a launch for one tile mode holds tile items only, a launch for
     // kModeStreamUnits long-run items only (a table sorted by mode)
-    constexpr bool kGatherMode = (Mode & 7u) == kModeGatherStore || (Mode & 7u) == kModeGatherOdd;
+    constexpr bool kGatherMode = (Mode & 7u) == kModeGatherStore || (Mode & 7u) == kModeGatherOdd ||
+                                 (Mode & 7u) == kModeGatherWhole;
     if (Mode != kModeStreamUnits && (Mode != kModeAny || it->kind == kItemTile)) {
         const TileHeader h = load_const(&it->h);
         const CONSTANT TileEntry* entries = (const CONSTANT TileEntry*)a.entries + it->first;
@@ -1080,7 +1349,7 @@ __device__ __forceinline__ void batch_unit(const BatchArgs& a, const CONSTANT ui
             if (table_item != j) {
                 // the previous unit's barrier has ended every read of the
                 // region; this unit's first barrier publishes the table
-                gather_table(h, gg, (const uint32_t*)(entries + h.num_entries), lds);
+                gather_table(h, gg, (const CONSTANT uint32_t*)(entries + h.num_entries), lds);
                 table_item = j;
             }
         } else if (h.lds_bytes > 0) {
@@ -2160,36 +2429,28 @@ void check_hip(hipError_t e, const char* what)
         fail(LLAMA_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// tile_kernel variants by mode (kModeStaged .. kModeGatherOdd): plain loads
+// tile_kernel variants by mode (kModeStaged .. kModeGatherWhole): plain loads
 // and stores, then nontemporal loads, then nontemporal loads and stores
 constexpr uint32_t kLd = kModeStreamLoads, kLdSt = kModeStreamLoads | kModeStreamStores;
-constexpr uint32_t kTileModes = 5;
+constexpr uint32_t kTileModes = 7; // (kModeStreamUnits is the batch kernel's)
+#define TILE_KERNELS(K, M, DLOAD)                                                                                  \
+    (const void*)K<kModeStaged | (M)>, (const void*)K<kModeDirectStore | (M)>, DLOAD,                              \
+        (const void*)K<kModeGatherStore | (M)>, (const void*)K<kModeGatherOdd | (M)>, nullptr,                     \
+        (const void*)K<kModeGatherWhole | (M)>
 const void* const kTileKernels[3 * kTileModes] = {
-    (const void*)tile_kernel<kModeStaged>, (const void*)tile_kernel<kModeDirectStore>,
-    (const void*)tile_kernel<kModeDirectLoad>, (const void*)tile_kernel<kModeGatherStore>,
-    (const void*)tile_kernel<kModeGatherOdd>,
-    (const void*)tile_kernel<kModeStaged | kLd>, (const void*)tile_kernel<kModeDirectStore | kLd>,
-    (const void*)tile_kernel<kModeDirectLoad | kLd>, (const void*)tile_kernel<kModeGatherStore | kLd>,
-    (const void*)tile_kernel<kModeGatherOdd | kLd>,
-    (const void*)tile_kernel<kModeStaged | kLdSt>, (const void*)tile_kernel<kModeDirectStore | kLdSt>,
-    (const void*)tile_kernel<kModeDirectLoad | kLdSt>, (const void*)tile_kernel<kModeGatherStore | kLdSt>,
-    (const void*)tile_kernel<kModeGatherOdd | kLdSt>};
+    TILE_KERNELS(tile_kernel, 0u, (const void*)tile_kernel<kModeDirectLoad>),
+    TILE_KERNELS(tile_kernel, kLd, (const void*)tile_kernel<kModeDirectLoad | kLd>),
+    TILE_KERNELS(tile_kernel, kLdSt, (const void*)tile_kernel<kModeDirectLoad | kLdSt>)};
 
 const void* const kTileCountKernels[kTileModes] = {
-    (const void*)tile_count_kernel<kModeStaged>, (const void*)tile_count_kernel<kModeDirectStore>,
-    (const void*)tile_count_kernel<kModeDirectLoad>, (const void*)tile_count_kernel<kModeGatherStore>,
-    (const void*)tile_count_kernel<kModeGatherOdd>};
+    TILE_KERNELS(tile_count_kernel, 0u, (const void*)tile_count_kernel<kModeDirectLoad>)};
 
 // the same with the source gathered from several parts (kTileVirtualSrc);
 // never with direct load
 constexpr uint32_t kV = kModeVirtualSrc;
 const void* const kTileVirtualKernels[3 * kTileModes] = {
-    (const void*)tile_kernel<kModeStaged | kV>, (const void*)tile_kernel<kModeDirectStore | kV>, nullptr,
-    (const void*)tile_kernel<kModeGatherStore | kV>, (const void*)tile_kernel<kModeGatherOdd | kV>,
-    (const void*)tile_kernel<kModeStaged | kV | kLd>, (const void*)tile_kernel<kModeDirectStore | kV | kLd>, nullptr,
-    (const void*)tile_kernel<kModeGatherStore | kV | kLd>, (const void*)tile_kernel<kModeGatherOdd | kV | kLd>,
-    (const void*)tile_kernel<kModeStaged | kV | kLdSt>, (const void*)tile_kernel<kModeDirectStore | kV | kLdSt>, nullptr,
-    (const void*)tile_kernel<kModeGatherStore | kV | kLdSt>, (const void*)tile_kernel<kModeGatherOdd | kV | kLdSt>};
+    TILE_KERNELS(tile_kernel, kV, nullptr), TILE_KERNELS(tile_kernel, kV | kLd, nullptr),
+    TILE_KERNELS(tile_kernel, kV | kLdSt, nullptr)};
 
 // direct store into a destination scattered over several parts
 // (kTileVirtualDst): plain, nontemporal loads, nontemporal loads and stores;
@@ -2208,9 +2469,8 @@ const void* const kTileSplitSrcKernels[4] = {(const void*)tile_kernel<kSS>, (con
 const void* const kTileSplitDstKernels[4] = {(const void*)tile_kernel<kSD>, (const void*)tile_kernel<kSD | kLd>,
                                              (const void*)tile_kernel<kSD | kLdSt>, (const void*)tile_count_kernel<kSD>};
 
-const void* const kTileVirtualCountKernels[kTileModes] = {
-    (const void*)tile_count_kernel<kModeStaged | kV>, (const void*)tile_count_kernel<kModeDirectStore | kV>, nullptr,
-    (const void*)tile_count_kernel<kModeGatherStore | kV>, (const void*)tile_count_kernel<kModeGatherOdd | kV>};
+const void* const kTileVirtualCountKernels[kTileModes] = {TILE_KERNELS(tile_count_kernel, kV, nullptr)};
+#undef TILE_KERNELS
 
 // box_kernel<R, Morton, staged, field-major source, counted>: index
 // (0: rank <= 4, row and column orders; 1: rank <= 4; 2: any rank) * 8 +
@@ -2240,10 +2500,12 @@ void set_attributes()
     if (g_attr_set)
         return;
     for (const void* k : kTileKernels)
-        check_hip(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(kHardLdsBytes)),
+        if (k)
+            check_hip(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(kHardLdsBytes)),
                   "hipFuncSetAttribute(tile_kernel)");
     for (const void* k : kTileCountKernels)
-        check_hip(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(kHardLdsBytes)),
+        if (k)
+            check_hip(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(kHardLdsBytes)),
                   "hipFuncSetAttribute(tile_count_kernel)");
     for (const void* k : kBoxKernels)
         check_hip(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(kHardLdsBytes)),
@@ -2256,7 +2518,7 @@ void set_attributes()
                           "hipFuncSetAttribute(tile_kernel variant)");
     for (uint32_t key : {uint32_t(kModeAny), uint32_t(kModeStreamUnits), uint32_t(kModeStaged), uint32_t(kModeDirectStore),
                          kModeDirectStore | kModeSplitSrc, uint32_t(kModeDirectLoad), kModeDirectLoad | kModeSplitDst,
-                         uint32_t(kModeGatherStore), uint32_t(kModeGatherOdd)})
+                         uint32_t(kModeGatherStore), uint32_t(kModeGatherOdd), uint32_t(kModeGatherWhole)})
         for (const void* k : {batch_mode_kernel_for<false>(key), batch_mode_kernel_for<true>(key)})
             check_hip(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(kHardLdsBytes)),
                       "hipFuncSetAttribute(batch_mode_kernel)");
@@ -2311,7 +2573,13 @@ void set_counting(const CountTable* table, void* stream)
 
 namespace {
 void launch_one(const Plan& p, void* stream_ptr);
+
+// The kernel mode of a gathering tile with these flags.
+uint32_t gather_mode(uint32_t f)
+{
+    return (f & kTileGatherOdd) ? kModeGatherOdd : (f & kTileGatherWhole) ? kModeGatherWhole : kModeGatherStore;
 }
+} // namespace
 
 // A plan's launch, then the launches chained after it (the zero fill of an
 // aligned SoA destination's padding).
@@ -2341,7 +2609,7 @@ void launch_one(const Plan& p, void* stream_ptr)
             const uint32_t f = p.tile.h.flags;
             const uint32_t mode = (f & kTileDirectLoad)    ? kModeDirectLoad
                                   : (f & kTileDirectStore) ? kModeDirectStore
-                                  : (f & kTileGatherStore) ? ((f & kTileGatherOdd) ? kModeGatherOdd : kModeGatherStore)
+                                  : (f & kTileGatherStore) ? gather_mode(f)
                                                            : kModeStaged;
             k = (f & kTileVirtualSrc) ? kTileVirtualCountKernels[mode - 1] : kTileCountKernels[mode - 1];
             if (f & kTileVirtualDst)
@@ -2375,7 +2643,7 @@ void launch_one(const Plan& p, void* stream_ptr)
         const uint32_t f = p.tile.h.flags;
         const uint32_t mode = (f & kTileDirectLoad)    ? kModeDirectLoad
                               : (f & kTileDirectStore) ? kModeDirectStore
-                              : (f & kTileGatherStore) ? ((f & kTileGatherOdd) ? kModeGatherOdd : kModeGatherStore)
+                              : (f & kTileGatherStore) ? gather_mode(f)
                                                        : kModeStaged;
         // streaming stores come with streaming loads (a destination of 1 GiB
         // or more has a source of far more than 256 MB in every layout pair)
@@ -2391,8 +2659,7 @@ void launch_one(const Plan& p, void* stream_ptr)
         if (!k)
             fail(LLAMA_E_INVALID_ARG, "no kernel variant for this combination of gathered parts");
         void* args[] = {(void*)&p.tile};
-        check_hip(hipLaunchKernel(k, dim3(grid), dim3(p.threads), args, p.tile.h.lds_bytes, stream),
-                  "hipLaunchKernel(tile_kernel)");
+        check_hip(hipLaunchKernel(k, dim3(grid), dim3(p.threads), args, p.lds_bytes, stream), "hipLaunchKernel(tile_kernel)");
         break;
     }
     case LLAMA_PATH_STREAM:
@@ -2542,6 +2809,7 @@ const void* batch_mode_kernel_for(uint32_t key)
     case kModeDirectLoad | kModeSplitDst: return (const void*)batch_mode_kernel<kOnce, kModeDirectLoad | kModeSplitDst>;
     case kModeGatherStore: return (const void*)batch_mode_kernel<kOnce, kModeGatherStore>;
     case kModeGatherOdd: return (const void*)batch_mode_kernel<kOnce, kModeGatherOdd>;
+    case kModeGatherWhole: return (const void*)batch_mode_kernel<kOnce, kModeGatherWhole>;
     default: return nullptr;
     }
 }
@@ -2557,7 +2825,7 @@ uint32_t batch_mode_key(const BatchItem& it)
     if (f & kTileDirectStore)
         return kModeDirectStore | ((f & kTileSplitSrc) ? kModeSplitSrc : 0u);
     if (f & kTileGatherStore)
-        return (f & kTileGatherOdd) ? kModeGatherOdd : kModeGatherStore;
+        return gather_mode(f);
     return kModeStaged;
 }
 
