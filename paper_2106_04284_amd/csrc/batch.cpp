@@ -111,6 +111,15 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
             if (it != g_tile_memo.end())
                 start = it->second;
         }
+        // no more than 256 records (250 arrays of particle and mixed records,
+        // 7.9 GB: 1,560 us with up to 1,024, 1,543 with 512, 1,524 with 256;
+        // 200 arrays of up to 3 10^5 records 227.6 with 512, 224.0 with 256),
+        // and no more than
+        // the item has: a tile of 1,024 for the 256 records of a particle-in-
+        // cell frame kept four times the LDS it used and took the partial
+        // tile's path (4,096 frames, SoA into AoSoA32: 28.6 us, then 14.4)
+        while (start > 16 && (start > 256 || start / 2 >= rq.dst.npad))
+            start /= 2;
         bool found = false;
         uint32_t T = start;
         for (; T >= 16 && !found; T /= 2) {
@@ -341,6 +350,18 @@ BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama
         }
     }
     check_batch_overlap(rqs);
+
+    // Small items alone (tiles of up to 8 KiB, such as frames) run with half
+    // the threads: a workgroup's own cost, finding its item and reading its
+    // header, is per wave (4,096 frames of 256 particles: 14.4 us with 256
+    // threads, 12.8 with 128; arrays of 10^3 .. 3 10^6 records are 0.5% slower)
+    if (!(opt && opt->threads) && n > 0) {
+        uint64_t widest = 0;
+        for (const Request& rq : rqs)
+            widest = std::max<uint64_t>(widest, std::min<uint64_t>(rq.dst.npad, 512) * rq.record.packed_size);
+        if (widest <= 8192)
+            threads = 128;
+    }
 
     // An item with a Split side becomes its part copies, which write disjoint
     // bytes and so may run side by side; one that would write part of the

@@ -1244,7 +1244,14 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
                 table[w] = n ? piece[0] : 0u;
             } else if (n == 2) {
                 table[w] = (1u << 30) | uint32_t(pairs.size());
-                pairs.insert(pairs.end(), piece, piece + 2);
+                auto mask = [](uint32_t x) {
+                    uint32_t m = 0;
+                    for (uint32_t k = 0; k < 4; k++)
+                        m |= ((x >> (23 + k)) & 1u) ? 0xFFu << (8 * k) : 0u;
+                    return m;
+                };
+                const uint32_t group[4] = {piece[0], piece[1], mask(piece[0]), mask(piece[1])};
+                pairs.insert(pairs.end(), group, group + 4);
             } else { // byte by byte: the source byte of each (bit 31: a zero byte)
                 table[w] = (2u << 30) | uint32_t(quads.size());
                 for (uint32_t k = 0; k < 4; k++)
@@ -1252,8 +1259,8 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
                                                  : (x[k] & 0x3FFFFu) | ((g.q == 0 ? 0u : (x[k] >> 18) & 31u) << 18));
             }
         }
-        // groups of four at a 16-byte boundary, then the pairs; a group's
-        // entry holds its index in the table
+        // groups of four at a 16-byte boundary: the byte sources, then the
+        // pairs; a group's entry holds its index in the table
         const uint32_t quads_at = uint32_t((gwords + 3) & ~uint64_t(3));
         const uint32_t pairs_at = quads_at + uint32_t(quads.size());
         for (uint64_t w = 0; w < gwords; w++)
@@ -1303,7 +1310,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         // four; the gather store takes the tile while the table fits the
         // argument block and LDS and its words average at most
         // kGatherMaxReadsPct / 100 reads
-        const uint64_t cost = gwords + pairs.size() / 2 + 3 * (quads.size() / 4);
+        const uint64_t cost = gwords + pairs.size() / 4 + 3 * (quads.size() / 4);
         const uint64_t base = (uint64_t(sb) + 15) & ~uint64_t(15); // the table, 16-byte aligned
         const uint64_t table_bytes = (table.size() * 4 + 15) / 16 * 16;
         const uint64_t room = uint64_t(kTileMaxEntries - a.num_entries - C) * (sizeof(TileEntry) / 4);
@@ -1371,7 +1378,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         }
         a.src.lds_bytes = 0;
         a.dst.lds_base = 0;
-        a.lds_bytes = db;
+        a.lds_bytes = db + 16; // the last 16 take the values of records past the last one
     }
     uint64_t widest = 1;
     for (size_t f = 0; f < F; f++)
@@ -1649,7 +1656,7 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
         // lane runs can take it.
         bool small_store = false;
         if (!T && !threads && rq.record.packed_size <= 64 && total_bytes(rq.dst.blob_size) < kStreamStoreBytes &&
-            rq.dst_stride.empty() && (rq.dst.lanes == 0 || rq.dst.lanes >= 32) && rq.src.lanes <= 256) {
+            (rq.dst.lanes == 0 || rq.dst.lanes >= 32) && rq.src.lanes <= 256 && rq.dst.lanes <= 256) {
             p.threads = wide_threads(rq, 256, 28);
             small_store = fill_tile(rq, 256, kMaxLdsBytes, p) && (p.tile.h.flags & kTileDirectStore);
         }

@@ -76,13 +76,14 @@ constexpr uint32_t kMoveSplit = 1u << 3;
 // 18-22; 0 when q = 0) and the word bytes it gives (bits 23-26).  Entry w of
 // the table describes word w of super-block 0:
 //   bits 31-30 = 00:  the word is one piece, this entry (no byte: padding);
-//   bits 31-30 = 01:  two pieces, the entries at table index bits 0-15;
+//   bits 31-30 = 01:  two pieces: a group of four words at table index bits
+//                     0-15 (16-byte aligned), the two entries and the byte
+//                     masks of what they give;
 //   bits 31-30 = 10:  three or four pieces: four entries at index bits 0-15
 //                     (16-byte aligned) give its bytes one by one, entry k the
 //                     LDS byte p0 of byte k in super-block 0 and its run in
 //                     the same bits (bit 31: a zero byte).
-// The word entries are padded to a multiple of 4; the groups of four follow,
-// then the pairs.  Records without values (tail lanes of the last AoSoA
+// The word entries are padded to a multiple of 4; the groups of four follow.  Records without values (tail lanes of the last AoSoA
 // block) are cleared in the source region before the tile's words are read.
 // The table follows the entries: in the argument block at entry num_entries
 // (reinterpreted as 32-bit words), in a batch after the item's entries; in
@@ -99,7 +100,7 @@ struct TileGather {
     uint32_t magic; // ceil(2^32 / words): u / words == mulhi(u, magic) for u * words < 2^32
     uint32_t q, lg; // lg: log2 of the records of a super-block
     uint32_t kq;
-    uint32_t table; // 32-bit words of the table: word entries, groups of four, pairs
+    uint32_t table; // 32-bit words of the table: word entries, groups of four
 };
 
 struct TileHeader {

@@ -706,6 +706,7 @@ __device__ __forceinline__ void direct_load_tile(const TileHeader& h, Entries en
 {
     const uint32_t tid = threadIdx.x, nthr = blockDim.x, wave = wave_id(), lane = tid & 63u;
     u32x4 v[kDirectLoadSlots];
+    uint32_t leaf[kDirectLoadSlots];
     // slot of (wave, j): q = wave * 64 + j * nthr + lane; its leaf is uniform,
     // and the slots grow with j, so each leaf search resumes from the last
     uint32_t f = 0;
@@ -716,6 +717,7 @@ __device__ __forceinline__ void direct_load_tile(const TileHeader& h, Entries en
             break;
         while (f + 1 < h.num_leaves && ent(f + 1).src_pos <= q0)
             f++;
+        leaf[j] = f;
         const auto& e = ent(f);
         const uint32_t g = q0 + lane - e.src_pos; // granule within the leaf's values of the tile
         const uint32_t left = nv * e.size; // bytes of the leaf's values in this tile
@@ -728,67 +730,56 @@ __device__ __forceinline__ void direct_load_tile(const TileHeader& h, Entries en
                 v[j] = load_bytes<kCount>(a, left - g * 16u);
         }
     }
-    f = 0;
+    // the values of records past nv go to 16 bytes that nothing reads: a
+    // branch per value costs more scalar instructions than its write
+    const uint32_t spare = h.lds_bytes - 16u;
 #pragma unroll
     for (uint32_t j = 0; j < kDirectLoadSlots; j++) {
         const uint32_t q0 = uniform(wave * 64u + j * nthr);
         if (q0 >= h.slots)
             break;
-        while (f + 1 < h.num_leaves && ent(f + 1).src_pos <= q0)
-            f++;
-        const auto& e = ent(f);
+        const auto& e = ent(leaf[j]);
         const uint32_t g = q0 + lane - e.src_pos;
-        const uint32_t size = e.size; // 4, 8 or 16
-        const uint32_t r0 = g << (4u - (e.move & 7u)); // first record of the granule
-        if (g * 16u >= nv * size)
+        const uint32_t size = e.size, lg = e.move & 7u;
+        const uint32_t r0 = g << (4u - lg); // first record of the granule
+        if (r0 >= nv)
             continue;
-        const uint32_t d0 = e.dst_pos + (r0 >> h.dst.pos_lg) * h.dst.pos_k + (r0 & h.dst.pos_m) * size;
+        const uint32_t dp = e.dst_pos;
+        auto pos = [&](uint32_t r) {
+            const uint32_t p = dp + (r >> h.dst.pos_lg) * h.dst.pos_k + ((r & h.dst.pos_m) << lg);
+            return r < nv ? p : spare;
+        };
+        const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
         if constexpr (kSplit) {
             const uint32_t wr = (e.move >> 24) & 7u;
-            const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-            auto pos = [&](uint32_t r) { return e.dst_pos + (r >> h.dst.pos_lg) * h.dst.pos_k + (r & h.dst.pos_m) * size; };
             if (size == 16) {
-                *(u32x4*)(lds + d0) = v[j];
+                *(u32x4*)(lds + pos(r0)) = v[j];
             } else if (size == 8) {
 #pragma unroll
                 for (uint32_t k = 0; k < 2; k++)
-                    if (r0 + k < nv)
-                        write_split<uint64_t>(lds, pos(r0 + k), (uint64_t(w[2 * k + 1]) << 32) | w[2 * k], wr);
+                    write_split<uint64_t>(lds, pos(r0 + k), (uint64_t(w[2 * k + 1]) << 32) | w[2 * k], wr);
             } else if (size == 4) {
 #pragma unroll
                 for (uint32_t k = 0; k < 4; k++)
-                    if (r0 + k < nv)
-                        write_split<uint32_t>(lds, pos(r0 + k), w[k], wr);
+                    write_split<uint32_t>(lds, pos(r0 + k), w[k], wr);
             } else if (size == 2) {
 #pragma unroll
                 for (uint32_t k = 0; k < 8; k++)
-                    if (r0 + k < nv)
-                        write_split<uint16_t>(lds, pos(r0 + k), uint16_t(w[k >> 1] >> (16u * (k & 1u))), wr);
+                    write_split<uint16_t>(lds, pos(r0 + k), uint16_t(w[k >> 1] >> (16u * (k & 1u))), wr);
             } else {
 #pragma unroll
                 for (uint32_t k = 0; k < 16; k++)
-                    if (r0 + k < nv)
-                        lds[pos(r0 + k)] = uint8_t(w[k >> 2] >> (8u * (k & 3u)));
+                    lds[pos(r0 + k)] = uint8_t(w[k >> 2] >> (8u * (k & 3u)));
             }
-            continue;
-        }
-        if (size == 16) {
-            *(u32x4*)(lds + d0) = v[j];
+        } else if (size == 16) {
+            *(u32x4*)(lds + pos(r0)) = v[j];
         } else if (size == 8) {
-            *(uint2*)(lds + d0) = uint2{v[j].x, v[j].y};
-            if (r0 + 1 < nv) {
-                const uint32_t r = r0 + 1;
-                *(uint2*)(lds + e.dst_pos + (r >> h.dst.pos_lg) * h.dst.pos_k + (r & h.dst.pos_m) * 8u) =
-                    uint2{v[j].z, v[j].w};
-            }
+            *(uint2*)(lds + pos(r0)) = uint2{w[0], w[1]};
+            *(uint2*)(lds + pos(r0 + 1)) = uint2{w[2], w[3]};
         } else {
-            const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
 #pragma unroll
-            for (uint32_t k = 0; k < 4; k++) {
-                const uint32_t r = r0 + k;
-                if (r < nv)
-                    *(uint32_t*)(lds + e.dst_pos + (r >> h.dst.pos_lg) * h.dst.pos_k + (r & h.dst.pos_m) * 4u) = w[k];
-            }
+            for (uint32_t k = 0; k < 4; k++)
+                *(uint32_t*)(lds + pos(r0 + k)) = w[k];
         }
     }
     // zeros: every gap entry, and every leaf for records in [nv, nd)
@@ -814,20 +805,25 @@ __device__ __forceinline__ void gather_table(const TileHeader& h, const TileGath
         tab[k] = table[k];
 }
 
-// One piece of a destination word (a word-table entry, or an entry of a group
-// of pieces): the 4 source bytes at LDS byte p = p0 + (blk >> q) * kq +
-// ((blk & (2^q - 1)) << run) in destination super-block blk, read from the two
-// aligned words that hold them, with the bytes the piece does not give
-// cleared.  Bits 0-17: p0 (the source byte that the word's byte 0 lines up
-// with), 18-22: run, 23-26: the word bytes the piece gives.
-__device__ __forceinline__ uint32_t gather_piece(uint32_t x, uint32_t bq, uint32_t bm, const uint8_t* lds)
+// The 4 source bytes of one piece of a destination word (a word-table entry,
+// or an entry of a group of pieces): those at LDS byte p = p0 + (blk >> q) * kq
+// + ((blk & (2^q - 1)) << run) in destination super-block blk, read from the
+// two aligned words that hold them.  Bits 0-17: p0 (the source byte that the
+// word's byte 0 lines up with), 18-22: run.  kShift: q != 0.
+template <bool kShift>
+__device__ __forceinline__ uint32_t gather_window(uint32_t x, uint32_t bq, uint32_t bm, const uint8_t* lds)
 {
-    const uint32_t p = (x & 0x3FFFFu) + bq + (bm << ((x >> 18) & 31u));
+    const uint32_t p = (x & 0x3FFFFu) + bq + (kShift ? bm << ((x >> 18) & 31u) : 0u);
     const uint32_t* wp = (const uint32_t*)(lds + (p & ~3u));
-    const uint32_t v = __builtin_amdgcn_alignbyte(wp[1], wp[0], p & 3u);
-    // bit k of the 4-bit byte mask to all of byte k
-    const uint32_t m = ((((x >> 23) & 15u) * 0x204081u) & 0x01010101u) * 0xFFu;
-    return v & m;
+    return __builtin_amdgcn_alignbyte(wp[1], wp[0], p & 3u);
+}
+
+// Bit k of the 4 bits 23-26 to all of byte k (a 24-bit multiply, which runs at
+// the full rate, a 32-bit one at a quarter of it).
+__device__ __forceinline__ uint32_t byte_mask(uint32_t x)
+{
+    const uint32_t t = __umul24((x >> 23) & 15u, 0x204081u) & 0x01010101u;
+    return (t << 8) - t;
 }
 
 // One byte of a word of three or four pieces: the LDS byte p0 + (blk >> q) *
@@ -861,9 +857,9 @@ __device__ __forceinline__ void zero_source_records(const TileHeader& h, Entries
 // word is one piece (its entry in the table), two or four pieces (a group of
 // entries the table points to); padding bytes belong to no piece and stay
 // zero, and so do records without values (cleared in the source region).
-template <bool kStream, bool kOdd, bool kCount>
-__device__ __forceinline__ void gather_store_tile(const TileHeader& h, const TileGather& gg, uint64_t t, uint32_t nd,
-                                                  uint32_t tid, uint32_t nthr, const uint8_t* lds)
+template <bool kStream, bool kOdd, bool kShift, bool kCount>
+__device__ __forceinline__ void gather_store_words(const TileHeader& h, const TileGather& gg, uint64_t t, uint32_t nd,
+                                                   uint32_t tid, uint32_t nthr, const uint8_t* lds)
 {
     const uint32_t* tab = (const uint32_t*)(lds + h.dst.lds_base);
     const uint32_t qm = (1u << gg.q) - 1u;
@@ -877,23 +873,21 @@ __device__ __forceinline__ void gather_store_tile(const TileHeader& h, const Til
         uint32_t v[4];
 #pragma unroll
         for (uint32_t c = 0; c < 4; c++) {
-            const uint32_t e = tab[w];
-            const uint32_t bq = (blk >> gg.q) * gg.kq, bm = blk & qm;
+            const uint32_t e = tab[w], e0 = (e >> 31) ? 0u : e; // (byte sources: read below)
+            const uint32_t bq = kShift ? (blk >> gg.q) * gg.kq : blk * gg.kq, bm = kShift ? blk & qm : 0u;
             const uint32_t kind = e >> 30;
-            uint32_t x, e1 = kind == 0u ? e : 0u;
+            const uint32_t m = byte_mask(e);
+            uint32_t x;
             if (__any(kind == 1u)) {
                 // a wave with words of two pieces reads two for every word
                 // (a second piece of a one-piece word gives no byte), in one
                 // path instead of two divergent ones
-                const uint2 g = *(const uint2*)(tab + (kind == 1u ? (e & 0xFFFFu) : 0u));
-                uint32_t e2 = 0u;
-                if (kind == 1u) {
-                    e1 = g.x;
-                    e2 = g.y;
-                }
-                x = gather_piece(e1, bq, bm, lds) | gather_piece(e2, bq, bm, lds);
+                const u32x4 g = *(const u32x4*)(tab + (kind == 1u ? (e & 0xFFFFu) : 0u));
+                const bool two = kind == 1u;
+                x = (gather_window<kShift>(two ? g.x : e0, bq, bm, lds) & (two ? g.z : m)) |
+                    (gather_window<kShift>(two ? g.y : 0u, bq, bm, lds) & (two ? g.w : 0u));
             } else {
-                x = gather_piece(e1, bq, bm, lds);
+                x = gather_window<kShift>(e0, bq, bm, lds) & m;
             }
             if (kind == 2u) { // three or four pieces: byte by byte
                 const u32x4 g = *(const u32x4*)(tab + (e & 0xFFFFu));
@@ -926,6 +920,16 @@ __device__ __forceinline__ void gather_store_tile(const TileHeader& h, const Til
             }
         }
     }
+}
+
+template <bool kStream, bool kOdd, bool kCount>
+__device__ __forceinline__ void gather_store_tile(const TileHeader& h, const TileGather& gg, uint64_t t, uint32_t nd,
+                                                  uint32_t tid, uint32_t nthr, const uint8_t* lds)
+{
+    if (gg.q == 0)
+        gather_store_words<kStream, kOdd, false, kCount>(h, gg, t, nd, tid, nthr, lds);
+    else
+        gather_store_words<kStream, kOdd, true, kCount>(h, gg, t, nd, tid, nthr, lds);
 }
 
 // gather_store_tile where every word is one aligned word of the source (or
