@@ -228,8 +228,11 @@ std::vector<Plan> copy_plans(const llama_mapping_desc* src, const llama_blob* sr
             ps.push_back(zero_fill_plan(rq)); // the padding between aligned SoA sub-arrays
         return ps;
     }
-    if (src->kind != LLAMA_SPLIT && dst->kind != LLAMA_SPLIT)
-        return {make_plan(rq, options)};
+    if (src->kind != LLAMA_SPLIT && dst->kind != LLAMA_SPLIT) {
+        std::vector<Plan> one;
+        one.push_back(make_plan(rq, options));
+        return one;
+    }
     // a Split side: one copy per destination part and source part sharing
     // leaves (or one from every source part feeding a destination part), in
     // order on the stream; every plan is made before the first launch

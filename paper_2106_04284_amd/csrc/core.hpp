@@ -179,10 +179,15 @@ struct Plan {
     uint64_t tiles = 0;
     uint32_t flags_in = 0; // llama_copy_options.flags of the request
     uint64_t read_bytes = 0, write_bytes = 0;
-    TileArgs tile{};     // path == TILE
-    StreamArgs stream{}; // path == STREAM
-    NaiveArgs naive{};   // path == NAIVE
-    BoxArgs box{};       // path == BOX (box_naive: its element-wise baseline)
+    // one path's arguments (16 KiB of them side by side cost a copy more host
+    // time to clear and move than to plan)
+    union {
+        uint8_t args[4096] = {};
+        TileArgs tile;     // path == TILE
+        StreamArgs stream; // path == STREAM
+        NaiveArgs naive;   // path == NAIVE
+        BoxArgs box;       // path == BOX (box_naive: its element-wise baseline)
+    };
     bool box_naive = false;
     // a launch that follows this one: the zero fill of the padding between a
     // destination's aligned SoA sub-arrays (a STREAM plan of zero runs)

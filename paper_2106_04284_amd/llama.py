@@ -11,6 +11,7 @@ call raises an error.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -122,7 +123,9 @@ class HeatmapDesc(ctypes.Structure):
 
 _lib = None
 
-# name -> (restype, argtypes) of every entry point the binding uses
+# name -> (restype, argtypes) of every entry point the binding uses; blob
+# arrays, coordinates and leaf maps are void pointers, which take packed words
+# (_blobs, _words) and ctypes arrays alike
 _SIGNATURES = {
     "llama_last_error": (ctypes.c_char_p, []),
     "llama_status_string": (ctypes.c_char_p, [ctypes.c_int]),
@@ -142,17 +145,17 @@ _SIGNATURES = {
     "llama_plan_copy": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(MappingDesc),
                                        ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(CopyOptions),
                                        ctypes.POINTER(PlanInfo), ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32)]),
-    "llama_copy": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.POINTER(MappingDesc),
-                                  ctypes.POINTER(Blob), ctypes.c_void_p]),
-    "llama_copy_naive": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob),
-                                        ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.c_void_p]),
-    "llama_copy_ex": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.POINTER(MappingDesc),
-                                     ctypes.POINTER(Blob), ctypes.POINTER(CopyOptions), ctypes.c_void_p]),
-    "llama_copy_leaves": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.POINTER(MappingDesc),
-                                         ctypes.POINTER(Blob), ctypes.POINTER(ctypes.c_uint32),
+    "llama_copy": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.POINTER(MappingDesc),
+                                  ctypes.c_void_p, ctypes.c_void_p]),
+    "llama_copy_naive": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p,
+                                        ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.c_void_p]),
+    "llama_copy_ex": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.POINTER(MappingDesc),
+                                     ctypes.c_void_p, ctypes.POINTER(CopyOptions), ctypes.c_void_p]),
+    "llama_copy_leaves": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.POINTER(MappingDesc),
+                                         ctypes.c_void_p, ctypes.c_void_p,
                                          ctypes.POINTER(CopyOptions), ctypes.c_void_p]),
-    "llama_autotune": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.POINTER(MappingDesc),
-                                      ctypes.POINTER(Blob), ctypes.c_void_p, ctypes.c_uint32,
+    "llama_autotune": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.POINTER(MappingDesc),
+                                      ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint32,
                                       ctypes.POINTER(CopyOptions), ctypes.POINTER(ctypes.c_double)]),
     "llama_tune_lookup": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(MappingDesc),
                                          ctypes.POINTER(CopyOptions), ctypes.POINTER(ctypes.c_int)]),
@@ -178,15 +181,15 @@ _SIGNATURES = {
     "llama_batch_destroy": (ctypes.c_int, [ctypes.c_void_p]),
     "llama_copy_batch": (ctypes.c_int, [ctypes.c_size_t, ctypes.POINTER(CopyItem), ctypes.c_void_p]),
     "llama_copy_batch_noalloc": (ctypes.c_int, [ctypes.c_size_t, ctypes.POINTER(CopyItem), ctypes.c_void_p]),
-    "llama_copy_transfer": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.c_uint32,
-                                           ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.c_uint32,
+    "llama_copy_transfer": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.c_uint32,
+                                           ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.c_uint32,
                                            ctypes.c_uint64, ctypes.c_void_p]),
-    "llama_copy_box": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.POINTER(ctypes.c_uint64),
-                                      ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob), ctypes.POINTER(ctypes.c_uint64),
-                                      ctypes.POINTER(ctypes.c_uint64), ctypes.POINTER(CopyOptions), ctypes.c_void_p]),
-    "llama_copy_heatmap": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob),
-                                          ctypes.POINTER(MappingDesc), ctypes.POINTER(Blob),
-                                          ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(CopyOptions),
+    "llama_copy_box": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.c_void_p,
+                                      ctypes.POINTER(MappingDesc), ctypes.c_void_p, ctypes.c_void_p,
+                                      ctypes.c_void_p, ctypes.POINTER(CopyOptions), ctypes.c_void_p]),
+    "llama_copy_heatmap": (ctypes.c_int, [ctypes.POINTER(MappingDesc), ctypes.c_void_p,
+                                          ctypes.POINTER(MappingDesc), ctypes.c_void_p,
+                                          ctypes.c_void_p, ctypes.POINTER(CopyOptions),
                                           ctypes.POINTER(HeatmapDesc), ctypes.c_void_p]),
     "llama_heatmap_begin": (ctypes.c_int, [ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
                                            ctypes.c_void_p]),
@@ -337,22 +340,46 @@ class Mapping:
         return out
 
 
+_U64 = (1 << 64) - 1
+
+
+def _words(values, code="Q"):
+    """`values` packed as 64-bit (code "I": 32-bit) unsigned words."""
+    return array.array(code, values).tobytes()
+
+
 def _blobs(blobs):
-    arr = (Blob * max(len(blobs), 1))()
-    for k, b in enumerate(blobs):
+    """The llama_blob array of torch tensors or (pointer, size) tuples, as
+    packed words: a ctypes structure per blob costs four times the time, half
+    of a small copy's."""
+    words = []
+    for b in blobs:
         if isinstance(b, tuple):
             ptr, size = b
+            try:
+                words += ((ptr or 0) & _U64, size & _U64)
+            except TypeError:  # a ctypes pointer
+                e = Blob(ptr, size)
+                words += (e.ptr or 0, e.size)
         else:  # a torch tensor
             if not b.is_contiguous():
                 raise ValueError("blob tensors must be contiguous")
-            ptr, size = b.data_ptr(), b.numel() * b.element_size()
-        arr[k] = Blob(ptr, size)
-    return arr
+            words += (b.data_ptr(), b.nbytes)
+    return _words(words or (0, 0))
+
+
+def _blob_array(blobs):
+    """_blobs as a ctypes array, for structures that point at it."""
+    packed = _blobs(blobs)
+    return (Blob * (len(packed) // ctypes.sizeof(Blob))).from_buffer_copy(packed)
 
 
 def _stream(stream):
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            # torch.cuda.current_stream().cuda_stream without the Stream object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -404,9 +431,9 @@ def copy_box(src: Mapping, src_blobs, src_offset, dst: Mapping, dst_blobs, dst_o
     """llama_copy_box: the records of a box of the array dimensions, from
     src_offset + c in the source to dst_offset + c in the destination."""
     r = len(box)
-    so = (ctypes.c_uint64 * MAX_RANK)(*[int(x) for x in src_offset])
-    do = (ctypes.c_uint64 * MAX_RANK)(*[int(x) for x in dst_offset])
-    bx = (ctypes.c_uint64 * MAX_RANK)(*[int(x) for x in box])
+    if max(r, len(src_offset), len(dst_offset)) > MAX_RANK:
+        raise IndexError("invalid index")
+    so, do, bx = (_words([int(x) & _U64 for x in v] + [0] * (MAX_RANK - len(v))) for v in (src_offset, dst_offset, box))
     if len(src_offset) != r or len(dst_offset) != r:
         raise ValueError("offsets and box need one entry per dimension")
     o = _options(path, tile_records, threads, 0, flags)
@@ -418,7 +445,7 @@ def copy_leaves(src: Mapping, src_blobs, dst: Mapping, dst_blobs, source_leaf, s
                 tile_records=0, threads=0, wg_per_cu=0, flags=0):
     """llama_copy_leaves: destination leaf k takes source leaf source_leaf[k]
     (None: the leaf keeps its bytes); the records may differ."""
-    arr = (ctypes.c_uint32 * max(len(source_leaf), 1))(*[NO_LEAF if x is None else int(x) for x in source_leaf])
+    arr = _words([NO_LEAF if x is None else int(x) & NO_LEAF for x in source_leaf] or [0], "I")
     o = _options(path, tile_records, threads, wg_per_cu, flags)
     check(lib().llama_copy_leaves(ctypes.byref(src.desc), _blobs(src_blobs), ctypes.byref(dst.desc),
                                   _blobs(dst_blobs), arr, ctypes.byref(o), _stream(stream)))
@@ -584,7 +611,7 @@ class _Items:
         self.keep = []
         self.arr = (CopyItem * max(len(items), 1))()
         for k, (src, sblobs, dst, dblobs) in enumerate(items):
-            sb, db = _blobs(sblobs), _blobs(dblobs)
+            sb, db = _blob_array(sblobs), _blob_array(dblobs)
             self.keep += [src, dst, sb, db, sblobs, dblobs]  # the blob tensors live as long as the items
             self.arr[k] = CopyItem(ctypes.pointer(src.desc), ctypes.cast(sb, ctypes.POINTER(Blob)),
                                    ctypes.pointer(dst.desc), ctypes.cast(db, ctypes.POINTER(Blob)))
