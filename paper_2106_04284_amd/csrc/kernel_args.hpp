@@ -429,6 +429,8 @@ struct BoxHeader {
     uint32_t shift[LLAMA_MAX_RANK]; // tile t covers box coordinates [t q - shift, (t + 1) q - shift)
     uint64_t box[LLAMA_MAX_RANK];   // the copy's box (full copies: the extents)
     uint64_t num_units;
+    uint32_t first_unit;            // the launch's first tile
+    uint32_t pad;
 };
 
 // a full copy: records outside the extents within a destination run (Morton

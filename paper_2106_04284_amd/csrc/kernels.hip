@@ -1056,7 +1056,9 @@ __device__ __forceinline__ void tile_body(const TileHeader& h, Entries ent, uint
             load_fields<kOnce, kCount>(h, ent, i0, nv, wave, nwaves, lane, lds_base);
         }
     }
-    if (preserve && !dstore && h.dst.mode == kRecordMajor) {
+    // (a whole tile of records without gaps has no byte to keep: the lanes past
+    // the last record are the last tile's)
+    if (preserve && !dstore && h.dst.mode == kRecordMajor && (nv < nd || h.num_entries > h.num_leaves)) {
         const uint32_t len = uint32_t(((uint64_t(nd) + h.dst.lanes - 1) >> h.dst.log2_lanes) * h.dst.block);
         load_span<false, kCount>(h.dst.span_base + t * h.dst.tile_bytes, len, h.dst.lds_base, wave, nwaves, lane, lds_base);
     }
@@ -2156,18 +2158,16 @@ __global__ void __launch_bounds__(1024) box_kernel(const BoxArgs a)
             wt[k] = f == kBoxWordZero ? uint2{kMapNoValue, 0u} : uint2{a.e[f].src_off + ((e >> 8) << 2), a.e[f].size};
         }
     }
-    const uint32_t nt = uint32_t(a.h.num_units); // below 2^32 (checked by the planner)
-    uint32_t t = blockIdx.x, stride = gridDim.x;
-    if (!kCount && gridDim.x == nt) { // each XCD one contiguous eighth of the tiles
+    // one tile per workgroup and no loop over tiles: before a loop the compiler
+    // prepares every value that any branch of the body derives from the
+    // arguments (a copy of more than kMaxGrid tiles is launched in parts)
+    const uint32_t nt = gridDim.x;
+    uint32_t t = blockIdx.x;
+    if (!kCount) { // each XCD one contiguous eighth of the tiles
         const uint32_t b = blockIdx.x, x = b & 7u, k = b >> 3, q = nt >> 3, rem = nt & 7u;
         t = x * q + min(x, rem) + k;
-        stride = nt;
     }
-    for (uint64_t v = t; v < nt; v += stride) {
-        box_body<R, kMorton, kStaged, kSrcField, kCount>(a, uint32_t(v), lds);
-        if (v + stride < nt)
-            __syncthreads();
-    }
+    box_body<R, kMorton, kStaged, kSrcField, kCount>(a, a.h.first_unit + t, lds);
 }
 
 // The coordinate of linear index i on side s; false when no coordinate inside
@@ -2594,6 +2594,21 @@ void launch(const Plan& p, void* stream_ptr)
 }
 
 namespace {
+// The box kernel over all tiles, at most kMaxGrid per launch.
+void launch_box(const Plan& p, bool counted, hipStream_t stream)
+{
+    set_attributes();
+    const void* k = box_kernel_for(p.box, counted);
+    BoxArgs part = p.box;
+    for (uint64_t first = 0; first < p.workgroups; first += kMaxGrid) {
+        part.h.first_unit = uint32_t(first); // below 2^32 (checked by the planner)
+        void* args[] = {(void*)&part};
+        check_hip(hipLaunchKernel(k, dim3(uint32_t(std::min<uint64_t>(p.workgroups - first, kMaxGrid))), dim3(p.threads),
+                                  args, part.h.lds_bytes, stream),
+                  "hipLaunchKernel(box_kernel)");
+    }
+}
+
 void launch_one(const Plan& p, void* stream_ptr)
 {
     hipStream_t stream = (hipStream_t)stream_ptr;
@@ -2632,8 +2647,11 @@ void launch_one(const Plan& p, void* stream_ptr)
         } else if (p.path == LLAMA_PATH_BOX) {
             set_attributes();
             args[0] = (void*)&p.box;
-            k = p.box_naive ? (const void*)box_naive_kernel<true> : box_kernel_for(p.box, true);
-            lds = p.box_naive ? 0 : p.box.h.lds_bytes;
+            if (!p.box_naive) {
+                launch_box(p, true, stream);
+                return;
+            }
+            k = (const void*)box_naive_kernel<true>;
         } else {
             fail(LLAMA_E_INVALID_ARG, "unknown path");
         }
@@ -2680,11 +2698,7 @@ void launch_one(const Plan& p, void* stream_ptr)
             hipLaunchKernelGGL(box_naive_kernel<false>, dim3(grid), dim3(p.threads), 0, stream, p.box);
             break;
         }
-        set_attributes();
-        const void* k = box_kernel_for(p.box, false);
-        void* args[] = {(void*)&p.box};
-        check_hip(hipLaunchKernel(k, dim3(grid), dim3(p.threads), args, p.box.h.lds_bytes, stream),
-                  "hipLaunchKernel(box_kernel)");
+        launch_box(p, false, stream);
         break;
     }
     default:
