@@ -1572,6 +1572,26 @@ __device__ __forceinline__ void box_run(const BoxHeader& h, uint32_t order, cons
     }
 }
 
+// Bits 0, 2, 4, ... of x as bits 0, 1, 2, ...
+__device__ __forceinline__ uint32_t every_second_bit(uint32_t x)
+{
+    x &= 0x55555555u;
+    x = (x | (x >> 1)) & 0x33333333u;
+    x = (x | (x >> 2)) & 0x0F0F0F0Fu;
+    x = (x | (x >> 4)) & 0x00FF00FFu;
+    return (x | (x >> 8)) & 0x0000FFFFu;
+}
+
+// Bits 0, 3, 6, ... of x as bits 0, 1, 2, ...
+__device__ __forceinline__ uint32_t every_third_bit(uint32_t x)
+{
+    x &= 0x49249249u;
+    x = (x | (x >> 2)) & 0xC30C30C3u;
+    x = (x | (x >> 4)) & 0x0F00F00Fu;
+    x = (x | (x >> 8)) & 0xFF0000FFu;
+    return (x | (x >> 16)) & 0x000007FFu;
+}
+
 // Linear index of the absolute coordinate c on side s (its linearizer).
 template <int R>
 __device__ __forceinline__ uint64_t box_linear(const BoxSide& s, uint32_t r, const uint64_t* c)
@@ -1785,10 +1805,10 @@ __device__ __forceinline__ void box_granules(const BoxArgs& a, const BoxEntry& e
 // So the host provides strides and reciprocals, the waves take chunks of all
 // leaves in turn (a leaf is a division away), and a record's source is one
 // 4-byte entry for all leaves; it takes 670 and 680 now.  128^3 lattice-
-// Boltzmann cells out of a grid with a halo: SoA into aligned AoS 237 -> 149
-// us (4.4 TB/s), aligned AoS into SoA 161 -> 129 us (5.1 TB/s); 2^24
-// particles: row-major AoS into column-major SoA 353 -> 195 us (4.8 TB/s),
-// column-major SoA into Morton AoSoA32 628 -> 250 us (3.8 TB/s).
+// Boltzmann cells out of a grid with a halo: SoA into aligned AoS 237 -> 139
+// us (4.7 TB/s), aligned AoS into SoA 161 -> 129 us (5.1 TB/s); 2^24
+// particles: row-major AoS into column-major SoA 353 -> 188 us (5.0 TB/s),
+// column-major SoA into Morton AoSoA32 628 -> 211 us (4.4 TB/s).
 template <int R, bool kMorton, bool kStaged, bool kSrcField, bool kCount>
 __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* lds)
 {
@@ -1805,15 +1825,26 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
     uint32_t tc[R];
     uint64_t ls = S.base, ld = D.base;
     if (kMorton && (h.flags & kBoxUnitMorton)) {
-        // cube u of the destination's Morton order: deinterleave u
+        // cube u of the destination's Morton order: deinterleave u (two and three
+        // dimensions by halving the gaps, 30 scalar instructions in place of
+        // the 400 of a loop over the bits)
 #pragma unroll
         for (uint32_t d = 0; d < R; d++)
             tc[d] = 0;
-        for (uint32_t j = 0; j * r < 32; j++)
+        if (r == 2) {
+            tc[0] = every_second_bit(u >> 1);
+            tc[1] = every_second_bit(u);
+        } else if (R > 2 && r == 3) {
+            tc[0] = every_third_bit(u >> 2);
+            tc[1] = every_third_bit(u >> 1);
+            tc[R > 2 ? 2 : 0] = every_third_bit(u);
+        } else {
+            for (uint32_t j = 0; j * r < 32; j++)
 #pragma unroll
-            for (uint32_t d = 0; d < R; d++)
-                if (d < r && j * r + r - 1 - d < 32)
-                    tc[d] |= ((u >> (j * r + r - 1 - d)) & 1u) << j;
+                for (uint32_t d = 0; d < R; d++)
+                    if (d < r && j * r + r - 1 - d < 32)
+                        tc[d] |= ((u >> (j * r + r - 1 - d)) & 1u) << j;
+        }
     } else {
         uint32_t rem = u;
 #pragma unroll
@@ -1969,14 +2000,22 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
     if (inner && S.order != kOrderOne) {
         // every record of the tile is in the box: its place in the source's
         // order is a permutation of the bits of its place in the destination's
+        // (of bits, so the place of j is that of its low bits and that of its
+        // high bits together: the thread's bits once, the rest per step)
+        uint32_t own = tid;
+        const bool same = (h.flags & kBoxSameOrder) != 0, pow2 = (nthr & (nthr - 1u)) == 0;
+        auto place = [&](uint32_t j, uint32_t b0) -> uint32_t {
+            uint32_t js = 0;
+            uint64_t perm = h.perm >> (4u * b0);
+            for (uint32_t b = b0; b < h.qlog_sum; b++, perm >>= 4)
+                js |= ((j >> b) & 1u) << (uint32_t(perm) & 15u);
+            return js;
+        };
+        if (!same && pow2)
+            own = place(tid & (Q - 1u), 0);
+        const uint32_t lgt = 31u - uint32_t(__builtin_clz(nthr));
         for (uint32_t j = tid; j < Q; j += nthr) {
-            uint32_t js = j;
-            if (!(h.flags & kBoxSameOrder)) {
-                js = 0;
-                uint64_t perm = h.perm;
-                for (uint32_t b = 0; b < h.qlog_sum; b++, perm >>= 4)
-                    js |= ((j >> b) & 1u) << (uint32_t(perm) & 15u);
-            }
+            const uint32_t js = same ? j : pow2 ? own | place(uniform(j & ~(nthr - 1u)), lgt) : place(j, 0);
             map[j] = source_of(js >> S.run_log2, js & ((1u << S.run_log2) - 1u));
         }
     } else {
