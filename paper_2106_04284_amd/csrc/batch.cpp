@@ -95,8 +95,8 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
     } else {
         // Every workgroup of the launch reserves the same LDS and about five
         // fit a compute unit, so the bytes in flight per compute unit grow
-        // with the bytes per tile: take the largest tile whose plan fits
-        // kBatchLdsBytes (a standalone launch's tuned tile may be small
+        // with the bytes per tile: take the largest tile, within the bounds
+        // below, whose plan fits kBatchLdsBytes (a standalone launch's tuned tile may be small
         // because many of its workgroups fit a compute unit at once).
         // the tile found for a class of copies is remembered, so that a
         // repeated class costs one plan instead of a search

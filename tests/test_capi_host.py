@@ -771,3 +771,30 @@ def test_aligned_soa_host(orc):
     with pytest.raises(L.LlamaError) as e:
         L.copy_transfer(aos, [(1 << 40, aos.blob_size(0))], q, [(2 << 40, q.blob_size(0))], True, stream=0)
     assert e.value.status == L.E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("name,n,small", [("particle", 1000, True), ("particle", (1 << 30) // 28, True),
+                                          ("particle", (1 << 30) // 28 + 1, False), ("listing1", 5000, True),
+                                          ("lbm", 5000, False)])
+def test_small_direct_store_plan(name, n, small):
+    """Direct stores of records of up to 64 bytes into less than 1 GiB take
+    tiles of 256 records; larger records, larger copies and options that are
+    given do not."""
+    r = L.Record(W.RECORDS[name])
+    a, b = L.Mapping(r, "aos_packed", [n]), L.Mapping(r, "soa_multi", [n])
+    p = L.plan(a, b)
+    assert p["tile_mode"] == "direct_store" and (p["tile_records"] == 256) == small
+    for t, th in ((64, 64), (512, 256)):
+        q = L.plan(a, b, tile_records=t, threads=th)
+        assert (q["tile_records"], q["threads"], q["tile_mode"]) == (t, th, "direct_store")
+
+
+@pytest.mark.parametrize("off", [0, 1, 4, 12])
+def test_soa_source_loads_directly_at_any_address(off):
+    """A field-major source needs no place on the 16-byte grid for the direct
+    load: the single-blob leaves of an odd count plan like the multi-blob's."""
+    r = L.Record(W.MIXED)
+    n = 4096 + off
+    for kind in ("soa_single", "soa_multi"):
+        p = L.plan(L.Mapping(r, kind, [n]), L.Mapping(r, "aos_packed", [n]))
+        assert (p["path"], p["tile_mode"]) == ("tile", "direct_load")

@@ -346,3 +346,18 @@ def test_batch_autotune_keeps_result(L, orc):
         check(items, want)
     b.close()
 
+
+
+@pytest.mark.parametrize("nmax", [3, 17, 100, 300])
+def test_batch_of_small_items(L, orc, nmax):
+    """Tiles no larger than their items and, for items of up to 8 KiB, half
+    the threads: every pair of layouts, counts below, at and past a tile."""
+    for seed, (name, keep) in enumerate([("particle", False), ("mixed", False), ("listing1", True)]):
+        items, want = make_items(L, orc, 900 + seed + nmax, 60, nmax, records=(name,), keep=keep)
+        batch = L.Batch(items, flags=L.COPY_PRESERVE_PADDING if keep else 0)
+        assert nmax > 100 or batch.info()["threads"] == 128
+        for _ in range(2):
+            batch.launch()
+            torch.cuda.synchronize()
+            check(items, want)
+            refill(items, 0xCD)

@@ -276,7 +276,7 @@ def test_box_granules(L, orc, name, dst):
     rec = {"bytes": [("u8", 3)], "shorts": [("u16", 2), "u8"], "words": ["u32", "f32"], "doubles": ["f64", "u64"],
            "mixed": W.MIXED, "listing1": W.LISTING1}[name]
     ro, rg = orc.Record(rec), L.Record(rec)
-    g = random.Random(hash((name, dst)) & 0xFFFF)
+    g = random.Random(f"{name} {dst}")
     for k, (width, off) in enumerate([(1, 0), (3, 1), (15, 5), (16, 7), (17, 15), (64, 3), (127, 0), (130, 9), (257, 2)]):
         src = g.choice([("aos_packed", 0), ("aos_aligned", 0), ("soa_single", 0), ("soa_multi", 0), ("aosoa", 4)])
         sext, dext, so, do, box = [3, width + 3], [4, width + off + 1], [1, k % 4], [1, off], [2, width]
@@ -318,3 +318,26 @@ def test_box_wide_record(L):
     got = dd[0].cpu().numpy().reshape(3, 5, -1)
     leaves = [x.reshape(5, 3, -1).transpose(1, 0, 2) for x in src]  # column-major: the first index fastest
     assert np.array_equal(got, np.concatenate(leaves, axis=2))
+
+
+@pytest.mark.parametrize("ext", [[1500], [45, 70], [64, 64], [19, 30, 13], [16, 16, 16], [5, 9, 6, 7], [2, 3, 4, 5, 6]],
+                         ids=lambda e: "x".join(map(str, e)))
+@pytest.mark.parametrize("threads", [0, 64, 192, 256])
+def test_morton_tiles(L, orc, ext, threads):
+    """Morton origins and the order of a tile's records, rank by rank (two and
+    three dimensions have forms of their own), with thread counts that are
+    powers of two and one that is not, over several tiles."""
+    ro, rg = orc.Record(W.PARTICLE), L.Record(W.PARTICLE)
+    for k, (lin_s, lin_d) in enumerate([("col", "morton"), ("morton", "row"), ("row", "col"), ("morton", "col")]):
+        if len(ext) > 1 or "morton" in (lin_s, lin_d):
+            ms_o, md_o = (orc.Mapping(ro, kind, ext, lanes, linearizer=lin)
+                          for kind, lanes, lin in [("soa_multi", 0, lin_s), ("aosoa", 32, lin_d)])
+            ms, md = (L.Mapping(rg, kind, ext, lanes, linearizer=lin)
+                      for kind, lanes, lin in [("soa_multi", 0, lin_s), ("aosoa", 32, lin_d)])
+            src = [W.random_bytes(n, 11 * k + j) for j, n in enumerate(ms_o.blob_sizes())]
+            want = orc.copy(ms_o, src, md_o)
+            for tile in (0, 16, 256):
+                dd = md.alloc(fill=0xCD)
+                L.copy(ms, [torch.from_numpy(x).cuda() for x in src], md, dd, tile_records=tile, threads=threads)
+                torch.cuda.synchronize()
+                _check(dd, want, f"{lin_s} -> {lin_d} {ext} tile {tile}")

@@ -388,3 +388,36 @@ def test_aligned_soa_extents_and_linearizers(L, orc):
         torch.cuda.synchronize()
         for g, w in zip(dd, want):
             assert np.array_equal(g.cpu().numpy(), w), (lin_s, lin_d)
+
+
+# tiles whose records all exist take forms of their own (no test per record,
+# whole words per super-block of 1, 2 or 4 records, kept lanes not loaded):
+# counts around the tile's edges, several tiles, and blobs off the 16-byte grid
+WHOLE_TILE_CASES = [
+    ("particle", ("aos_packed", 0), ("soa_multi", 0)), ("mixed", ("aos_aligned", 0), ("soa_single", 0)),
+    ("listing1", ("aos_aligned", 0), ("aosoa", 64)), ("particle", ("soa_multi", 0), ("aosoa", 32)),
+    # SoA sources at any address load directly, a partial last granule with them
+    ("particle", ("soa_single", 0), ("aos_packed", 0)), ("mixed", ("soa_single", 0), ("aos_packed", 0)),
+    ("lbm", ("soa_multi", 0), ("aosoa", 8)),
+    # records of 1, 3, 5, 7 and 8 words, read as whole words; 2-byte pieces
+    ("w1", ("aosoa", 8), ("aos_packed", 0)), ("w3", ("aosoa", 4), ("aos_packed", 0)), ("w3", ("aosoa", 32), ("aosoa", 2)),
+    ("w5", ("aosoa", 8), ("aos_packed", 0)), ("w8", ("soa_multi", 0), ("aos_aligned", 0)),
+    ("particle", ("aosoa", 32), ("aos_packed", 0)), ("w5", ("aos_packed", 0), ("aosoa", 4)),
+    ("h3", ("aosoa", 8), ("aos_packed", 0)), ("h3", ("aos_aligned", 0), ("aosoa", 8))]
+WHOLE_TILE_RECORDS = {"w1": ["f32"], "w3": [("f32", 3)], "w5": ["f64", ("u32", 3)], "w8": ["f64", ("f32", 6)],
+                      "h3": [("u16", 2), "f32", "u16"]}
+
+
+@pytest.mark.parametrize("case", WHOLE_TILE_CASES, ids=[f"{c[0]}-{_name(c[1])}-{_name(c[2])}" for c in WHOLE_TILE_CASES])
+@pytest.mark.parametrize("tile", [16, 64, 256])
+@pytest.mark.parametrize("keep", [False, True])
+def test_whole_tiles(L, orc, case, tile, keep):
+    name, a, b = case
+    rec = WHOLE_TILE_RECORDS.get(name) or W.RECORDS[name]
+    for k, n in enumerate([tile - 1, tile, tile + 1, 3 * tile, 5 * tile + 7]):
+        for offsets in [(0, 0), (4, 8), (8, 4), (1, 3)]:
+            run_case(L, orc, rec, a, b, [n], seed=n + 7 * k, src_off=offsets[0], dst_off=offsets[1], keep=keep,
+                     path="tile", tile_records=tile, threads=[64, 128, 192, 256][k % 4])
+    if tile == 256:
+        for n in (1, 255, 256, 257, 2051):  # the planner's own tile and threads
+            run_case(L, orc, rec, a, b, [n], seed=n, keep=keep)
