@@ -213,9 +213,10 @@ void order_bits(const BoxHeader& h, uint32_t order, std::vector<uint32_t>& out)
 }
 
 // Builds the box plan for 2^qsum records per tile; false when its LDS does
-// not fit `budget`.
+// not fit `budget`.  leaf_slots: a field-major source's runs leaf by leaf
+// (kBoxLeafSlots).
 bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const uint64_t* box, bool full,
-              bool preserve, uint32_t qsum, uint32_t budget, Plan& p)
+              bool preserve, uint32_t qsum, uint32_t budget, bool leaf_slots, Plan& p)
 {
     const Side &S = rq.src, &D = rq.dst;
     const Record& r = rq.record;
@@ -296,7 +297,9 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
     const uint64_t Q = uint64_t(1) << h.qlog_sum;
     const uint64_t Rs = Q / Ws, Rd = Q / Wd;
     uint64_t lds = 0; // source runs first
-    if (ss.field_major) {
+    if (ss.field_major && leaf_slots) {
+        h.flags |= kBoxLeafSlots;
+    } else if (ss.field_major) {
         // A run's slot begins at its start index rounded down to A records,
         // whole granules of every leaf; it holds a run that starts up to A - 1
         // records later, and A more where a leaf begins off the 16-byte grid
@@ -332,7 +335,9 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
             // leaf f's runs, one slot of `gran` granules each
             e.src_addr = rq.src_ptr[S.blob[f]] + S.base[f];
             e.src_off = uint32_t(std::min<uint64_t>(lds, 1u << 30)) + uint32_t(e.src_addr & 15);
-            e.gran = a.src.gran * sz / 16;
+            // (leaf slots: from the granule of the run's first value to that of
+            // its last, wherever the first begins)
+            e.gran = leaf_slots ? uint32_t((16 - (1u << align_bits(sat)) + Ws * sz + 15) / 16) : a.src.gran * sz / 16;
             e.magic = e.gran > 1 ? magic_for(e.gran) : 0;
             // a single run of a few granules more than whole chunks loads them
             // with its last chunk (128 values of 8 bytes off the granule grid)
@@ -340,7 +345,9 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
             h.load_chunks = std::max(h.load_chunks, uint32_t((Rs * e.gran - more + 63) / 64));
             // an odd number of granules from leaf to leaf, so that the words of
             // a record in neighbouring leaves lie in different banks
-            lds += (Rs * e.gran | 1) * 16;
+            // (leaf slots, which serve where LDS is short: not for tiles of
+            // fewer records than leaves)
+            lds += (leaf_slots && Q < F ? Rs * e.gran : Rs * e.gran | 1) * 16;
         } else {
             e.src_off = uint32_t(S.base[f]);
         }
@@ -428,24 +435,6 @@ bool try_plan(const Request& rq, const uint64_t* so, const uint64_t* dof, const 
     return true;
 }
 
-// Whether the smallest tile's values, runs and records fit `budget` bytes of
-// LDS when every run's slot begins at its own 16-byte granule of each leaf.
-bool bytes_fit(const Request& rq, const uint64_t* so, const uint64_t* dof, const uint64_t* box, bool full, bool preserve,
-               uint32_t budget, Plan& p)
-{
-    if (!try_plan(rq, so, dof, box, full, preserve, 1, ~0u, p))
-        return false;
-    const BoxArgs& a = p.box;
-    const uint64_t Q = uint64_t(1) << a.h.qlog_sum, Ws = uint64_t(1) << a.src.run_log2;
-    const uint64_t Rs = Q / Ws, Rd = Q >> a.dst.run_log2;
-    uint64_t lds = Q * 16 + (Rs + Rd) * 8;
-    for (const Leaf& l : rq.record.leaves)
-        lds += Rs * round16(Ws * l.size + 16);
-    if ((a.h.flags & (kBoxStaged | kBoxGather)) == kBoxStaged)
-        lds += Rd * a.dst.gran * 16;
-    return lds <= budget;
-}
-
 } // namespace
 
 std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const uint64_t* dof, const uint64_t* box,
@@ -489,7 +478,7 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
     auto naive = [&] {
         // the element-wise baseline: the same descriptors, one thread per
         // record (of the box, or of the destination's indices)
-        if (!try_plan(rq, so, dof, box, full, preserve, 4, ~0u, p))
+        if (!try_plan(rq, so, dof, box, full, preserve, 4, ~0u, false, p))
             fail(LLAMA_E_UNSUPPORTED, "box plan");
         p.box_naive = true;
         p.lds_bytes = 0;
@@ -508,33 +497,50 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
     // most 40 KiB of LDS, so that four workgroups share a compute unit (listing
     // 1's record into aligned AoS, 1,024 records in 60 KiB: 603 us, 512 in 30
     // KiB: 336 us), and at least 64 records where 64 KiB hold them.
-    uint32_t qsum;
+    uint32_t first;
     const uint32_t budget = 64 * 1024;
     if (T) {
-        qsum = log2u(T);
+        first = log2u(T);
     } else {
         const uint64_t q = 24576 / std::max<uint64_t>(r.packed_size, 1);
         const bool across = S.kind != LLAMA_ONE && S.lin != D.lin;
-        qsum = std::min<uint32_t>(12, std::max<uint32_t>(6, across ? log2_ceil(q) : log2u(q)));
+        first = std::min<uint32_t>(12, std::max<uint32_t>(6, across ? log2_ceil(q) : log2u(q)));
         // (a small box in as many tiles as the chip has compute units)
-        while (qsum > 6 && (nbox >> qsum) < 256)
-            qsum--;
-        while (qsum > 6 && !try_plan(rq, so, dof, box, full, preserve, qsum, 40 * 1024, p))
-            qsum--;
+        while (first > 6 && (nbox >> first) < 256)
+            first--;
     }
-    while (!try_plan(rq, so, dof, box, full, preserve, qsum, budget, p)) {
-        if (qsum <= 1) {
-            // a record too wide for a tile of two: element-wise while its
-            // bytes alone fit, which a field-major source's slots of whole
-            // granules of every leaf exceed sooner (leaves of 1 byte next to
-            // leaves of kilobytes)
-            if (S.lanes != 0 || S.kind == LLAMA_ONE || !bytes_fit(rq, so, dof, box, full, preserve, budget, p))
-                fail(LLAMA_E_UNSUPPORTED, "the record does not fit a box tile's LDS");
-            naive();
-            return plans;
-        }
-        qsum--;
+    // log2 of the records asked for when the first tile of 2^first and fewer
+    // fits (its plan in p); 0: none does
+    auto search = [&](bool leaf_slots) {
+        auto fits = [&](uint32_t q, uint32_t lds) {
+            return try_plan(rq, so, dof, box, full, preserve, q, lds, leaf_slots, p);
+        };
+        uint32_t q = first;
+        while (!T && q > 6 && !fits(q, 40 * 1024))
+            q--;
+        while (q >= 1 && !fits(q, budget))
+            q--;
+        return q;
+    };
+    uint32_t q = search(false);
+    if (S.lanes == 0 && S.kind != LLAMA_ONE && q < first) {
+        // Slots of as many records in every leaf may take several times the
+        // LDS of the short runs in them.  Where loading the runs leaf by leaf
+        // holds at least four times the records it is taken (mixed records
+        // from single-blob SoA into Morton SoA: 200^3, 64 records 1,850 us, 512
+        // records 548; 33 x 40 x 37 x 41, 16 records 7,590, 256 records 623),
+        // for twice the records only when they were asked for (60 doubles and
+        // a byte in transposed order: 32 records in 40 KiB 260 us, 64 in 64
+        // KiB 289)
+        const Plan same = p;
+        const uint32_t leaf = search(true);
+        if (leaf && (!q || p.box.h.qlog_sum >= same.box.h.qlog_sum + (T ? 1 : 2)))
+            q = leaf;
+        else
+            p = same;
     }
+    if (!q)
+        fail(LLAMA_E_UNSUPPORTED, "the record does not fit a box tile's LDS");
     // fewer tiles than compute units fill: their latency counts, and 8 waves
     // share the entries (an 7 x 8 x 8 lattice-Boltzmann grid 14.4 -> 12.1 us,
     // 362 x 303 listing 1 records 25.3 -> 19.6)

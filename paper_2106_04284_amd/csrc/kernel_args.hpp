@@ -409,7 +409,8 @@ struct BoxHeader {
     uint32_t rank;
     uint32_t num_leaves;
     uint32_t num_entries; // leaves, then the gaps of an AoS destination
-    uint32_t flags;       // kBoxFull, kBoxPreserve, kBoxStaged, kBoxUnitMorton, kBoxGather, kBoxSameOrder
+    uint32_t flags;       // kBoxFull, kBoxPreserve, kBoxStaged, kBoxUnitMorton, kBoxGather, kBoxSameOrder,
+                          // kBoxLeafSlots
     uint32_t qlog[LLAMA_MAX_RANK]; // tile extents, log2
     uint32_t qlog_sum;             // log2 of the records of a tile
     uint32_t lds_bytes;
@@ -454,6 +455,13 @@ constexpr int kBoxMaxWords = 52;
 constexpr uint32_t kBoxWordZero = 0xFFu;
 // both orders number a tile's records alike (perm is the identity)
 constexpr uint32_t kBoxSameOrder = 32;
+// a field-major source whose runs are loaded leaf by leaf: a run's slot in a
+// leaf begins at the 16-byte granule of its first value there, so that a slot
+// holds no more than its run and one granule.  Otherwise a run's slots begin
+// at one record in every leaf, which makes a value's place the same number in
+// all of them, but takes up to 31 records beside the run's own where a leaf
+// has 1-byte values.
+constexpr uint32_t kBoxLeafSlots = 64;
 
 struct BoxArgs {
     BoxHeader h;

@@ -1711,17 +1711,27 @@ __device__ __forceinline__ void box_load_group(uint32_t base, uint32_t nspans, u
 // as value number l (bits 16-29) after byte p (bits 0-15):
 //   record-major source: the LDS byte of the record's block (its phase
 //                        included), and the record's lane;
-//   field-major source:  p = 0, l the record's place in every leaf's slots.
+//   field-major source:  p = 0, l the record's place in every leaf's slots;
+//   with slots leaf by leaf (kBoxLeafSlots) the run's start index modulo 16
+//   (bits 0-3), the element (bits 4-16) and the run (bits 17-30).
 // The same for every leaf, and four bytes: a granule of four consecutive
 // records reads its entries with two LDS instructions.
 constexpr uint32_t kMapSkip = 0xFFFFFFFFu, kMapHole = 0xFFFFFFFEu, kMapNoValue = 0x80000000u;
 
+// How a tile's source runs lie in LDS (the box kernel's template parameter).
+constexpr uint32_t kSrcBlocks = 0; // record-major: whole blocks
+constexpr uint32_t kSrcSlots = 1;  // field-major: slots of as many records in every leaf
+constexpr uint32_t kSrcLeafSlots = 2; // field-major: each leaf's slots at its own granules (kBoxLeafSlots)
+
 // LDS byte of an entry's value for the record map entry m; off: the leaf's
-// byte in a block (record-major), or of its first slot (field-major).
-template <bool kSrcField>
-__device__ __forceinline__ uint32_t box_pos(uint32_t m, uint32_t off, uint32_t size)
+// byte in a block (record-major), or of its first slot (field-major; bits 0-3
+// those of its address); slot: kSrcLeafSlots: the bytes of a slot.
+template <uint32_t kSrc>
+__device__ __forceinline__ uint32_t box_pos(uint32_t m, uint32_t off, uint32_t size, uint32_t slot)
 {
-    return off + (kSrcField ? 0u : m & 0xFFFFu) + (m >> 16) * size;
+    if constexpr (kSrc == kSrcLeafSlots)
+        return (off & ~15u) + (m >> 17) * slot + ((off + (m & 15u) * size) & 15u) + ((m >> 4) & 8191u) * size;
+    return off + (kSrc == kSrcSlots ? 0u : m & 0xFFFFu) + (m >> 16) * size;
 }
 
 // One leaf's values of a tile to a field-major or AoSoA destination, 16-byte
@@ -1736,7 +1746,7 @@ __device__ __forceinline__ uint32_t box_pos(uint32_t m, uint32_t off, uint32_t s
 // kSplit: source values aligned to 2^rd bytes only, read from the aligned
 // words that hold them (a misaligned LDS access takes 65 cycles per wave
 // against 4: the lanes one after another).
-template <typename T, bool kSrcField, bool kSplit, bool kCount>
+template <typename T, uint32_t kSrc, bool kSplit, bool kCount>
 __device__ __forceinline__ void box_granules(const BoxArgs& a, const BoxEntry& en, uint32_t idx, uint32_t Q, bool inner,
                                              uint32_t len_d, const uint32_t* map, const uint64_t* tab_d,
                                              const uint8_t* lds)
@@ -1755,7 +1765,7 @@ __device__ __forceinline__ void box_granules(const BoxArgs& a, const BoxEntry& e
         return;
     const uint32_t* mp = map + (k << wlog);
     auto value = [&](uint32_t m) -> T {
-        const uint32_t p = box_pos<kSrcField>(m, en.src_off, sizeof(T));
+        const uint32_t p = box_pos<kSrc>(m, en.src_off, sizeof(T), en.gran << 4);
         if constexpr (kSplit && sizeof(T) > 1)
             return read_split<T>(lds, p, rd);
         else
@@ -1809,9 +1819,10 @@ __device__ __forceinline__ void box_granules(const BoxArgs& a, const BoxEntry& e
 // us (4.7 TB/s), aligned AoS into SoA 161 -> 129 us (5.1 TB/s); 2^24
 // particles: row-major AoS into column-major SoA 353 -> 188 us (5.0 TB/s),
 // column-major SoA into Morton AoSoA32 628 -> 211 us (4.4 TB/s).
-template <int R, bool kMorton, bool kStaged, bool kSrcField, bool kCount>
+template <int R, bool kMorton, bool kStaged, uint32_t kSrc, bool kCount>
 __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* lds)
 {
+    constexpr bool kSrcField = kSrc != kSrcBlocks;
     const BoxHeader& h = a.h;
     const BoxSide &S = a.src, &D = a.dst;
     const uint32_t r = h.rank;
@@ -1951,9 +1962,15 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
             if (k < Rs) {
                 const uint64_t st = tab_s[k];
                 const uint32_t w = run_len(S, st, len_s);
-                const uint32_t rel = (uint32_t(st) & S.amask) * en.size + (uint32_t(en.src_addr) & 15u);
+                // the slot's first granule is that of the run's first value
+                // (kSrcLeafSlots), else of its start index rounded down
+                const uint64_t first = en.src_addr + st * en.size;
+                const uint32_t rel = kSrc == kSrcLeafSlots ? uint32_t(first) & 15u
+                                                           : (uint32_t(st) & S.amask) * en.size + (uint32_t(en.src_addr) & 15u);
                 const uint32_t g0 = rel >> 4, g1 = w ? (rel + w * en.size + 15u) >> 4 : 0u;
-                const uint64_t ga = (en.src_addr & ~uint64_t(15)) + (st & ~uint64_t(S.amask)) * en.size + uint64_t(gi) * 16u;
+                const uint64_t ga = (kSrc == kSrcLeafSlots
+                                         ? first & ~uint64_t(15)
+                                         : (en.src_addr & ~uint64_t(15)) + (st & ~uint64_t(S.amask)) * en.size) + uint64_t(gi) * 16u;
                 const uint32_t la = uniform(lds_base + (en.src_off & ~15u) + sub * 1024u);
                 if (gi >= g0 && gi < g1)
                     lds_dma16<false, kCount>(ga, la);
@@ -1989,6 +2006,8 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
         if (!kSrcField && S.order == kOrderOne)
             return S.lds_base + (uint32_t(S.blob) & 15u);
         const uint64_t ss = tab_s[ks];
+        if constexpr (kSrc == kSrcLeafSlots)
+            return (uint32_t(ss) & 15u) | (es << 4) | (ks << 17);
         if constexpr (kSrcField)
             return (ks * S.gran + (uint32_t(ss) & S.amask) + es) << 16;
         const uint32_t l0 = uint32_t(ss) & ((1u << S.log2_lanes) - 1u), i = l0 + es; // records from the first block on
@@ -2075,8 +2094,13 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
                 if (wi >= 0 && rr < w) {
                     const uint32_t m = map[(k << wlog) + rr];
                     const uint2 L = wt[wi];
-                    if (!((m | L.x) & kMapNoValue)) // a hole of a full copy, or a gap: zero
-                        v[c] = *(const uint32_t*)(lds + box_pos<kSrcField>(m, L.x, L.y));
+                    if (!((m | L.x) & kMapNoValue)) { // else a hole of a full copy, or a gap: zero
+                        if constexpr (kSrc == kSrcLeafSlots)
+                            v[c] = *(const uint32_t*)(lds + ((L.x >> 18) << 2) +
+                                                      box_pos<kSrc>(m, L.x & 0x3FFFFu, L.y & 0xFFFFu, (L.y >> 16) << 4));
+                        else
+                            v[c] = *(const uint32_t*)(lds + box_pos<kSrc>(m, L.x, L.y, 0u));
+                    }
                 }
                 if (++wi == int32_t(h.words)) {
                     wi = 0;
@@ -2110,16 +2134,16 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
             const bool all = inner && S.order != kOrderOne;
             if ((en.dst >> 15) & 1u) {
                 switch (lgper) {
-                case 3: box_granules<uint16_t, kSrcField, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
-                case 2: box_granules<uint32_t, kSrcField, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
-                default: box_granules<uint64_t, kSrcField, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 3: box_granules<uint16_t, kSrc, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 2: box_granules<uint32_t, kSrc, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                default: box_granules<uint64_t, kSrc, true, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
                 }
             } else {
                 switch (lgper) {
-                case 4: box_granules<uint8_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
-                case 3: box_granules<uint16_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
-                case 2: box_granules<uint32_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
-                default: box_granules<uint64_t, kSrcField, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 4: box_granules<uint8_t, kSrc, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 3: box_granules<uint16_t, kSrc, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                case 2: box_granules<uint32_t, kSrc, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
+                default: box_granules<uint64_t, kSrc, false, kCount>(a, en, rec, Q, all, len_d, map, tab_d, lds); break;
                 }
             }
             continue;
@@ -2128,7 +2152,7 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
         const bool zero = (en.dst & 1u) || m == kMapHole;
         if (m == kMapSkip || (zero && preserve))
             continue;
-        const uint32_t sp = zero ? 0u : box_pos<kSrcField>(m, en.src_off, en.size);
+        const uint32_t sp = zero ? 0u : box_pos<kSrc>(m, en.src_off, en.size, en.gran << 4);
         const uint64_t i = tab_d[rec >> wlog] + (rec & wmask);
         if constexpr (kStaged) {
             const uint32_t kd = rec >> wlog, ed = rec & wmask;
@@ -2185,18 +2209,21 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
     }
 }
 
-template <int R, bool kMorton, bool kStaged, bool kSrcField, bool kCount>
+template <int R, bool kMorton, bool kStaged, uint32_t kSrc, bool kCount>
 __global__ void __launch_bounds__(1024) box_kernel(const BoxArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     if (kStaged && (a.h.flags & kBoxGather)) {
         // per word of the destination record its source: the arguments of
-        // box_pos (bit 31 of the first: a gap); the first tile's barriers
-        // publish them
+        // box_pos (bit 31 of the first: a gap); kSrcLeafSlots: the first slot
+        // and the word of the value (bits 18-23), and the value's bytes and a
+        // slot's granules (bits 16-31).  The tile's barriers publish them
         uint2* wt = (uint2*)(lds + a.h.wtab);
         for (uint32_t k = threadIdx.x; k < a.h.words; k += blockDim.x) {
             const uint32_t e = a.words[k], f = e & 0xFFu;
-            wt[k] = f == kBoxWordZero ? uint2{kMapNoValue, 0u} : uint2{a.e[f].src_off + ((e >> 8) << 2), a.e[f].size};
+            wt[k] = f == kBoxWordZero          ? uint2{kMapNoValue, 0u}
+                    : kSrc == kSrcLeafSlots ? uint2{a.e[f].src_off | ((e >> 8) << 18), a.e[f].size | (a.e[f].gran << 16)}
+                                            : uint2{a.e[f].src_off + ((e >> 8) << 2), a.e[f].size};
         }
     }
     // one tile per workgroup and no loop over tiles: before a loop the compiler
@@ -2208,7 +2235,7 @@ __global__ void __launch_bounds__(1024) box_kernel(const BoxArgs a)
         const uint32_t b = blockIdx.x, x = b & 7u, k = b >> 3, q = nt >> 3, rem = nt & 7u;
         t = x * q + min(x, rem) + k;
     }
-    box_body<R, kMorton, kStaged, kSrcField, kCount>(a, a.h.first_unit + t, lds);
+    box_body<R, kMorton, kStaged, kSrc, kCount>(a, a.h.first_unit + t, lds);
 }
 
 // The coordinate of linear index i on side s; false when no coordinate inside
@@ -2517,22 +2544,24 @@ const void* const kTileSplitDstKernels[4] = {(const void*)tile_kernel<kSD>, (con
 const void* const kTileVirtualCountKernels[kTileModes] = {TILE_KERNELS(tile_count_kernel, kV, nullptr)};
 #undef TILE_KERNELS
 
-// box_kernel<R, Morton, staged, field-major source, counted>: index
-// (0: rank <= 4, row and column orders; 1: rank <= 4; 2: any rank) * 8 +
-// staged * 4 + field-major * 2 + counted
-#define BOX_KERNELS(R, M)                                                                           \
-    (const void*)box_kernel<R, M, false, false, false>, (const void*)box_kernel<R, M, false, false, true>, \
-    (const void*)box_kernel<R, M, false, true, false>, (const void*)box_kernel<R, M, false, true, true>,   \
-    (const void*)box_kernel<R, M, true, false, false>, (const void*)box_kernel<R, M, true, false, true>,   \
-    (const void*)box_kernel<R, M, true, true, false>, (const void*)box_kernel<R, M, true, true, true>
-const void* const kBoxKernels[24] = {BOX_KERNELS(4, false), BOX_KERNELS(4, true), BOX_KERNELS(8, true)};
+// box_kernel<R, Morton, staged, source slots, counted>: index
+// (0: rank <= 4, row and column orders; 1: rank <= 4; 2: any rank) * 12 +
+// staged * 6 + source slots * 2 + counted
+#define BOX_SOURCES(R, M, S)                                                                              \
+    (const void*)box_kernel<R, M, S, kSrcBlocks, false>, (const void*)box_kernel<R, M, S, kSrcBlocks, true>, \
+    (const void*)box_kernel<R, M, S, kSrcSlots, false>, (const void*)box_kernel<R, M, S, kSrcSlots, true>,   \
+    (const void*)box_kernel<R, M, S, kSrcLeafSlots, false>, (const void*)box_kernel<R, M, S, kSrcLeafSlots, true>
+#define BOX_KERNELS(R, M) BOX_SOURCES(R, M, false), BOX_SOURCES(R, M, true)
+const void* const kBoxKernels[36] = {BOX_KERNELS(4, false), BOX_KERNELS(4, true), BOX_KERNELS(8, true)};
 #undef BOX_KERNELS
+#undef BOX_SOURCES
 
 const void* box_kernel_for(const BoxArgs& b, bool counted)
 {
     auto morton = [](const BoxSide& s) { return s.order == kOrderMorton || s.order == kOrderPoint; };
-    return kBoxKernels[(b.h.rank > 4 ? 16 : morton(b.src) || morton(b.dst) ? 8 : 0) + ((b.h.flags & kBoxStaged) ? 4 : 0) +
-                       (b.src.mode == kFieldMajor ? 2 : 0) + (counted ? 1 : 0)];
+    const uint32_t slots = b.src.mode != kFieldMajor ? kSrcBlocks : (b.h.flags & kBoxLeafSlots) ? kSrcLeafSlots : kSrcSlots;
+    return kBoxKernels[(b.h.rank > 4 ? 24 : morton(b.src) || morton(b.dst) ? 12 : 0) + ((b.h.flags & kBoxStaged) ? 6 : 0) +
+                       slots * 2 + (counted ? 1 : 0)];
 }
 
 bool g_attr_set = false;

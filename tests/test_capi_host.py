@@ -798,3 +798,47 @@ def test_soa_source_loads_directly_at_any_address(off):
     for kind in ("soa_single", "soa_multi"):
         p = L.plan(L.Mapping(r, kind, [n]), L.Mapping(r, "aos_packed", [n]))
         assert (p["path"], p["tile_mode"]) == ("tile", "direct_load")
+
+
+_WIDE = [("f64", 60), "u8"]
+
+
+@pytest.mark.parametrize("rec,src,lin,dst,to,ext,tile", [
+    ("mixed", "soa_single", "row", ("soa_multi", 0), "morton", [200, 200, 200], 512),
+    ("mixed", "soa_multi", "row", ("aos_packed", 0), "morton", [33, 40, 37, 41], 256),
+    ("lbm", "soa_multi", "row", ("aos_aligned", 0), "morton", [33, 40, 37, 41], 256),
+    ("listing1", "soa_single", "row", ("soa_multi", 0), "morton", [33, 40, 37, 41], 256),
+    ("wide", "soa_multi", "row", ("aos_packed", 0), "morton", [512, 512], 16),
+    ("wide", "soa_multi", "row", ("soa_multi", 0), "morton", [64, 64, 64], 64),
+    ("wide", "soa_multi", "row", ("aos_packed", 0), "col", [700, 600], 32)])
+def test_box_tiles_of_short_field_major_runs(rec, src, lin, dst, to, ext, tile):
+    """A field-major source in short runs keeps its tile: the LDS holds each
+    leaf's values and one granule more per run, by hand for the mixed record's
+    512 (64 runs of 8): f64 5 granules (8 bytes into one at most), f32 and i32
+    3, u8 2, an odd number of granules per leaf, 4 bytes of map per record and
+    8 per run on both sides.  Twice the records alone change nothing."""
+    r = L.Record(W.RECORDS.get(rec, _WIDE))
+    p = L.plan(L.Mapping(r, src, ext, linearizer=lin), L.Mapping(r, dst[0], ext, dst[1], linearizer=to))
+    assert (p["path"], p["tile_records"]) == ("box", tile) and p["lds_bytes"] > 0
+    if (rec, to, len(ext)) == ("mixed", "morton", 3):
+        # single-blob leaves of 200^3 records start on the 16-byte grid: f64
+        # values lie 8 bytes into a granule at most, f32 and i32 12, u8 15
+        granules = [(8 + 8 * 8 + 15) // 16] * 3 + [(12 + 8 * 4 + 15) // 16] * 6 + [(15 + 8 + 15) // 16]
+        assert p["lds_bytes"] == sum((64 * g | 1) * 16 for g in granules) + 512 * 4 + 64 * 8 + 8
+
+
+def test_box_path_runs_tiles_for_wide_records():
+    """A tile that was asked for is run: records per tile that fit leaf by
+    leaf only, and path BOX for a 1-byte leaf beside leaves of kilobytes (the
+    element-wise kernel takes no LDS)."""
+    r = L.Record(_WIDE)
+    a, b = L.Mapping(r, "soa_multi", [700, 600]), L.Mapping(r, "aos_packed", [700, 600], linearizer="col")
+    assert L.plan(a, b, tile_records=64)["tile_records"] == 64
+    r = L.Record(["u8"] * 4)
+    for j, size in enumerate([1, 4096, 4096, 4096]):
+        r.nodes[j] = L.Field(size, 1, 1, 0)
+    a, b = L.Mapping(r, "soa_multi", [3, 5], linearizer="col"), L.Mapping(r, "aos_packed", [3, 5])
+    for path in ("auto", "box"):
+        p = L.plan(a, b, path=path)
+        assert p["path"] == "box" and p["lds_bytes"] > 0 and p["tile_records"] >= 2
+    assert L.plan(a, b, path="naive")["lds_bytes"] == 0

@@ -341,3 +341,51 @@ def test_morton_tiles(L, orc, ext, threads):
                 L.copy(ms, [torch.from_numpy(x).cuda() for x in src], md, dd, tile_records=tile, threads=threads)
                 torch.cuda.synchronize()
                 _check(dd, want, f"{lin_s} -> {lin_d} {ext} tile {tile}")
+
+
+@pytest.mark.parametrize("name,kind,dst,ext,tile", [
+    ("mixed", "soa_single", ("soa_multi", 0), [9, 17, 11], 512), ("mixed", "soa_multi", ("aos_packed", 0), [5, 4, 7, 3], 256),
+    ("listing1", "soa_single", ("aosoa", 32), [5, 4, 7, 3], 256), ("lbm", "soa_multi", ("aos_aligned", 0), [6, 4, 5, 4], 256),
+    ("wide", "soa_multi", ("aos_packed", 0), [9, 13], 16), ("wide", "soa_single", ("aosoa", 8), [4, 9, 5], 64),
+    ("wide", "soa_multi", ("soa_single", 0), [3, 5, 4], 64)])
+@pytest.mark.parametrize("off", [0, 4, 1])
+def test_box_leaf_slots(L, orc, name, kind, dst, ext, tile, off):
+    """Runs loaded leaf by leaf (field-major sources whose runs are short for
+    their narrowest leaf): whole copies into Morton order and boxes, run starts
+    at every place of a granule, tiles cut by the extents, blobs on and off the
+    16-byte grid, the padding of aligned records zeroed and kept."""
+    rec = W.RECORDS.get(name, [("f64", 60), "u8"])
+    ro, rg = orc.Record(rec), L.Record(rec)
+    rank = len(ext)
+
+    def place(arrays):  # device blobs `off` bytes off the 16-byte grid
+        out = []
+        for x in arrays:
+            t = torch.empty(x.size + 32, dtype=torch.uint8, device="cuda")[off:off + x.size]
+            t.copy_(torch.from_numpy(x))
+            out.append(t)
+        return out
+    for k, (ls, ld) in enumerate([("row", "morton"), ("col", "morton")]):
+        ms_o, ms = orc.Mapping(ro, kind, ext, linearizer=ls), L.Mapping(rg, kind, ext, linearizer=ls)
+        md_o = orc.Mapping(ro, dst[0], ext, dst[1], linearizer=ld)
+        md = L.Mapping(rg, dst[0], ext, dst[1], linearizer=ld)
+        assert L.plan(ms, md, tile_records=tile)["tile_records"] == tile
+        src = [W.random_bytes(n, 5 * k + j) for j, n in enumerate(ms_o.blob_sizes())]
+        canary = [W.random_bytes(n, 60 + 5 * k + j) for j, n in enumerate(md_o.blob_sizes())]
+        for flags in (0, L.COPY_PRESERVE_PADDING):
+            want = orc.copy(ms_o, src, md_o, [c.copy() for c in canary], keep_padding=True) if flags \
+                else orc.copy(ms_o, src, md_o)
+            sd, dd = place(src), place(canary)
+            L.copy(ms, sd, md, dd, tile_records=tile, flags=flags)
+            torch.cuda.synchronize()
+            _check(dd, want, f"{name} {kind} {ls} -> {dst} {ld} flags {flags}")
+        big = [e + 3 for e in ext]
+        so, box = [d % 3 for d in range(rank)], [max(e - 2, 1) for e in ext]
+        do = [(d + 1) % 4 for d in range(rank)]
+        mb_o, mb = orc.Mapping(ro, dst[0], big, dst[1], linearizer=ld), L.Mapping(rg, dst[0], big, dst[1], linearizer=ld)
+        canary = [W.random_bytes(n, 90 + j) for j, n in enumerate(mb_o.blob_sizes())]
+        want = orc.copy_box(ms_o, src, so, mb_o, [c.copy() for c in canary], do, box)
+        sd, dd = place(src), place(canary)
+        L.copy_box(ms, sd, so, mb, dd, do, box, tile_records=tile)
+        torch.cuda.synchronize()
+        _check(dd, want, f"{name} {kind} {ls} box -> {dst} {ld}")
