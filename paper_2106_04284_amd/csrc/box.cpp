@@ -496,9 +496,9 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
     // for 2^24 of them from row-major AoSoA8 into column-major AoSoA64), at
     // most 40 KiB of LDS, so that four workgroups share a compute unit (listing
     // 1's record into aligned AoS, 1,024 records in 60 KiB: 603 us, 512 in 30
-    // KiB: 336 us), and at least 64 records where 64 KiB hold them.
+    // KiB: 336 us), else at most 64 KiB.
     uint32_t first;
-    const uint32_t budget = 64 * 1024;
+    const uint32_t budget = 64 * 1024, share = 40 * 1024;
     if (T) {
         first = log2u(T);
     } else {
@@ -516,10 +516,26 @@ std::vector<Plan> make_box_plans(const Request& rq, const uint64_t* so, const ui
             return try_plan(rq, so, dof, box, full, preserve, q, lds, leaf_slots, p);
         };
         uint32_t q = first;
-        while (!T && q > 6 && !fits(q, 40 * 1024))
-            q--;
+        if (!T && q > 6 && fits(q, share))
+            return q;
         while (q >= 1 && !fits(q, budget))
             q--;
+        if (T || q <= 6)
+            return q;
+        // fewer records in `share`, where that takes no more than 1.5 times the
+        // LDS per record: a source of long lane blocks loads as many blocks
+        // for a part of their records (2^23 records from Morton AoSoA into
+        // rows: listing 1's, 1,024 lanes, into SoA: 1,024 records in 47 KiB
+        // 160 us, 64 in 43 KiB 1,411; particles, 512 lanes, into AoS: 1,024 in
+        // 47 KiB 169, 256 in 30 KiB 251)
+        const uint64_t lds = p.lds_bytes, records = uint64_t(1) << p.box.h.qlog_sum;
+        for (uint32_t s = q; s >= 6; s--)
+            if (fits(s, share)) {
+                if (p.lds_bytes * records * 2 <= (lds * 3) << p.box.h.qlog_sum)
+                    return s;
+                break;
+            }
+        fits(q, budget);
         return q;
     };
     uint32_t q = search(false);

@@ -842,3 +842,18 @@ def test_box_path_runs_tiles_for_wide_records():
         p = L.plan(a, b, path=path)
         assert p["path"] == "box" and p["lds_bytes"] > 0 and p["tile_records"] >= 2
     assert L.plan(a, b, path="naive")["lds_bytes"] == 0
+
+
+@pytest.mark.parametrize("name,lanes,dst,tile", [
+    ("listing1", 1024, ("soa_multi", "row"), 1024), ("listing1", 1024, ("aos_packed", "morton"), 256),
+    ("mixed", 512, ("aos_packed", "row"), 256), ("particle", 1024, ("aos_packed", "col"), 1024),
+    ("particle", 512, ("aos_packed", "row"), 1024), ("listing1", 0, ("aos_aligned", "col"), 512)])
+def test_box_tiles_of_long_lane_blocks(name, lanes, dst, tile):
+    """A tile is made smaller for its LDS only where its LDS falls with its
+    records: not from lane blocks longer than the tile, which are loaded whole
+    for any part of their records."""
+    r = L.Record(W.RECORDS[name])
+    ext = [4096, 2048]
+    src = L.Mapping(r, "aosoa", ext, lanes, linearizer="morton") if lanes else L.Mapping(r, "soa_multi", ext)
+    p = L.plan(src, L.Mapping(r, dst[0], ext, linearizer=dst[1]))
+    assert (p["path"], p["tile_records"]) == ("box", tile)
