@@ -591,8 +591,9 @@ typedef struct {
  *    wave slots allow, at most 8); path must be 0, flags takes the
  *    LLAMA_COPY_* bits.  Every workgroup reserves
  *    the largest item's LDS, so without a fixed tile size each tiled item
- *    takes the largest tile of at most 256 records, and no larger than the
- *    item, whose plan fits 32 KB of LDS (the tuning cache, which is measured
+ *    takes the largest tile whose plan fits 32 KB of LDS, of at most 12.5 KB
+ *    of source and 16 records per thread (256 records in any case), and no
+ *    larger than the item (the tuning cache, which is measured
  *    on standalone launches, is not used).  Without a thread count, a batch
  *    whose items all have tiles of up to 8 KB runs 128 threads per workgroup.
  *  - Items whose record does not fit the tiled kernel are refused with

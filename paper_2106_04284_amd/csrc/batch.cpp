@@ -111,14 +111,23 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
             if (it != g_tile_memo.end())
                 start = it->second;
         }
-        // no more than 256 records (250 arrays of particle and mixed records,
-        // 7.9 GB: 1,560 us with up to 1,024, 1,543 with 512, 1,524 with 256;
-        // 200 arrays of up to 3 10^5 records 227.6 with 512, 224.0 with 256),
-        // and no more than
-        // the item has: a tile of 1,024 for the 256 records of a particle-in-
-        // cell frame kept four times the LDS it used and took the partial
-        // tile's path (4,096 frames, SoA into AoSoA32: 28.6 us, then 14.4)
-        while (start > 16 && (start > 256 || start / 2 >= rq.dst.npad))
+        // By default no more than kBatchTileBytes of source, but 256 records
+        // (250 arrays of particle and mixed records, 7.9 GB: 1,560 us with up
+        // to 1,024 records, 1,543 with 512, 1,524 with 256; 20 arrays of 10^6
+        // {u8, u16}, AoS into SoA: 69 us with 256 records and 128 threads, 25
+        // with 4,096 and 256; of {f32, f32}: 82, and 60 with 1,024), and no
+        // more than 16 records per thread: the LDS moves go value by value
+        // ({u8, u16}, 666 arrays of 3,000, SoA into AoS with 128 threads: 9.6
+        // us with 4,096 records, 8.4 with 2,048).  A given LDS budget
+        // (autotuning) alone sets the tile.
+        if (!lds_budget)
+            while (start > 256 && (start * rq.record.packed_size > kBatchTileBytes || start > 16 * threads))
+                start /= 2;
+        // No more than the item has: a tile of 1,024 for the 256 records of a
+        // particle-in-cell frame kept four times the LDS it used and took the
+        // partial tile's path (4,096 frames, SoA into AoSoA32: 28.6 us, then
+        // 14.4)
+        while (start > 16 && start / 2 >= rq.dst.npad)
             start /= 2;
         bool found = false;
         uint32_t T = start;
@@ -521,16 +530,23 @@ void autotune_batch(Batch* b, void* stream_ptr, int reps, double* best_gbs)
         const uint32_t budgets[] = {8 * 1024, 16 * 1024, kBatchLdsBytes, 48 * 1024};
         const uint32_t threads[] = {128, 256, 512};
         const uint32_t grids[] = {0, 2, 4, 8, 17};
-        for (uint32_t bud : budgets)
-            for (uint32_t th : threads)
+        for (uint32_t th : threads) {
+            std::vector<uint64_t> planned; // the tiles of the last budget that was timed
+            for (uint32_t bud : budgets) {
+                BatchTable t;
+                try {
+                    for (const Request& rq : b->work)
+                        t.add(rq, th, b->tile_records, b->flags, bud);
+                } catch (const Error&) {
+                    continue; // an item does not fit this budget
+                }
+                std::vector<uint64_t> tiles;
+                for (const BatchItem& it : t.items)
+                    tiles.push_back(it.kind == kItemTile ? (uint64_t(it.h.flags) << 8) | it.h.log2_tile : ~uint64_t(0));
+                if (tiles == planned)
+                    continue; // a larger budget changed no item's tile
+                planned = tiles;
                 for (uint32_t wg : grids) {
-                    BatchTable t;
-                    try {
-                        for (const Request& rq : b->work)
-                            t.add(rq, th, b->tile_records, b->flags, bud);
-                    } catch (const Error&) {
-                        continue; // an item does not fit this budget
-                    }
                     b->threads = th;
                     b->lds_budget = bud;
                     install_table(b, t, wg == 17 ? 0 : wg, wg == 17);
@@ -542,6 +558,8 @@ void autotune_batch(Batch* b, void* stream_ptr, int reps, double* best_gbs)
                         best = {bud, th, wg == 17 ? 0 : wg, wg == 17};
                     }
                 }
+            }
+        }
         // re-plan with the fastest
         BatchTable t;
         for (const Request& rq : b->work)

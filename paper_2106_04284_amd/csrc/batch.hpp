@@ -78,6 +78,10 @@ constexpr bool kBatchByModeDefault = true;
 // tile size: five workgroups fit one compute unit
 constexpr uint32_t kBatchLdsBytes = kHardLdsBytes / 5 - 64;
 
+// source bytes that a batch item's tile may hold, unless the caller fixes the
+// tile size or an LDS budget (tiles of up to 256 records may hold more)
+constexpr uint32_t kBatchTileBytes = 12800;
+
 // How a table runs: one workgroup per work unit when its items share one LDS
 // class, else a persistent grid (see create_batch).
 bool batch_per_unit(const BatchTable& t);
@@ -92,7 +96,7 @@ constexpr uint64_t kBatchMaxGrid = uint64_t(1) << 24;
 uint32_t batch_grid(uint64_t units, uint32_t wg_per_cu);
 
 // the plan of a batch item (see BatchTable::add)
-// (lds_budget 0: kBatchLdsBytes)
+// (lds_budget 0: kBatchLdsBytes, and tiles of kBatchTileBytes)
 Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget = 0);
 
 // validates the items and plans them into one work table (nothing on the device)

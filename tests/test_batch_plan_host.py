@@ -1,0 +1,98 @@
+"""Host-side tests of batch plans (no GPU): the tile and the threads that the
+items of a batch take, read from the work table before anything is uploaded.
+A helper compiled here against the library's own headers calls the planner."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2106_04284_amd import build as B
+from paper_2106_04284_amd import llama as L
+from paper_2106_04284_amd import workloads as W
+
+HELPER = r"""
+#include "batch.hpp"
+using namespace llama;
+static uint32_t tile_of(uint32_t kind, const TileHeader& h) { return kind == kItemTile ? 1u << h.log2_tile : 0u; }
+extern "C" int batch_table(size_t n, const llama_copy_item* items, const llama_copy_options* o, uint32_t* threads,
+                           uint32_t* tiles)
+{
+    try {
+        const BatchTable t = build_batch_table(n, items, o, *threads);
+        for (size_t k = 0; k < n && k < t.items.size(); k++)
+            tiles[k] = tile_of(t.items[k].kind, t.items[k].h);
+        return 0;
+    } catch (const Error& e) {
+        return e.status;
+    }
+}
+extern "C" int batch_tile(const llama_copy_item* it, uint32_t threads, uint32_t budget, uint32_t* tile)
+{
+    try {
+        const Plan p = batch_plan(make_request(it->src, it->src_blobs, it->dst, it->dst_blobs, true), threads, 0, 0, budget);
+        *tile = p.path == LLAMA_PATH_TILE ? 1u << p.tile.h.log2_tile : 0u;
+        return 0;
+    } catch (const Error& e) {
+        return e.status;
+    }
+}
+"""
+
+RECORDS = dict(W.RECORDS, small=["u8", "u16"], pair=["f32", "f32"], vec3=[("f32", 3)], vec4=[("f32", 4)])
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    L.lib()
+    d = tmp_path_factory.mktemp("batch_plan")
+    src, so = d / "helper.cpp", d / "helper.so"
+    src.write_text(HELPER)
+    subprocess.run(["g++"] + B.CXX_FLAGS + ["-O1", "-shared", str(src), "-o", str(so), B.LIB,
+                                            "-Wl,-rpath," + os.path.dirname(B.LIB)], check=True)
+    return ctypes.CDLL(str(so))
+
+
+def _items(rec, src, dst, counts):
+    r, at, out = L.Record(RECORDS[rec]), 1 << 40, []
+    for n in counts:
+        sides = []
+        for kind, lanes in (src, dst):
+            m = L.Mapping(r, kind, [n], lanes)
+            blobs = []
+            for size in m.blob_sizes():
+                blobs.append((at, size))
+                at += (size + 511) // 256 * 256
+            sides += [m, blobs]
+        out.append(tuple(sides))
+    return L._Items(out)
+
+
+def _tile(planner, rec, src, dst, n, threads=256, budget=0):
+    items, tile = _items(rec, src, dst, [n]), ctypes.c_uint32()
+    assert planner.batch_tile(items.arr, threads, budget, ctypes.byref(tile)) == 0
+    return tile.value
+
+
+A, S, Q32 = ("aos_packed", 0), ("soa_multi", 0), ("aosoa", 32)
+
+
+@pytest.mark.parametrize("src,dst", [(A, S), (S, A), (Q32, S), (S, Q32)])
+def test_batch_tiles_by_bytes(planner, src, dst):
+    """The default tile holds at most 12,800 source bytes, or 256 records, and
+    16 records per thread, and no more than the item."""
+    for rec, tile in [("small", 4096), ("pair", 1024), ("vec3", 1024), ("vec4", 512), ("particle", 256)]:
+        assert _tile(planner, rec, src, dst, 10 ** 6) == tile, rec
+    assert _tile(planner, "small", src, dst, 10 ** 6, threads=128) == 2048
+    assert _tile(planner, "small", src, dst, 10 ** 6, threads=64) == 1024
+    assert _tile(planner, "particle", src, dst, 10 ** 6, threads=64) == 256
+    for n, tile in [(100, 128), (300, 512), (1000, 1024), (1025, 2048)]:
+        assert _tile(planner, "small", src, dst, n) == tile, n
+
+
+def test_batch_tiles_of_a_given_budget(planner):
+    """A given LDS budget alone bounds the tile (the autotuner's candidates):
+    particles in one region of 28 bytes per record, one 16-byte granule of
+    room and the leaf table."""
+    assert [_tile(planner, "particle", A, S, 10 ** 6, budget=k * 1024) for k in (8, 16, 31, 48)] == [256, 512, 1024, 1024]
+    assert [_tile(planner, "mixed", A, S, 10 ** 6, budget=k * 1024) for k in (16, 31, 64)] == [256, 512, 1024]
