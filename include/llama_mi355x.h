@@ -595,7 +595,9 @@ typedef struct {
  *    of source and 16 records per thread (256 records in any case), and no
  *    larger than the item (the tuning cache, which is measured
  *    on standalone launches, is not used).  Without a thread count, a batch
- *    whose items all have tiles of up to 8 KB runs 128 threads per workgroup.
+ *    whose items all hold at most 128 KB (their destination's records, AoSoA
+ *    tail lanes included, times the packed record) runs 128 threads per
+ *    workgroup, else 256.
  *  - Items whose record does not fit the tiled kernel are refused with
  *    LLAMA_E_UNSUPPORTED.
  *  - A batch belongs to the device that was current at creation.

@@ -360,15 +360,16 @@ BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama
     }
     check_batch_overlap(rqs);
 
-    // Small items alone (tiles of up to 8 KiB, such as frames) run with half
-    // the threads: a workgroup's own cost, finding its item and reading its
-    // header, is per wave (4,096 frames of 256 particles: 14.4 us with 256
-    // threads, 12.8 with 128; arrays of 10^3 .. 3 10^6 records are 0.5% slower)
+    // Small items alone run with half the threads: a workgroup's own cost,
+    // finding its item and reading its header, is per wave (4,096 frames of
+    // 256 particles, SoA into AoSoA32: 14.4 us with 256 threads, 12.8 with
+    // 128; 2,000 arrays of 1,000 particles, AoS into SoA: 34.8 and 28.3; 666
+    // of 3,000: 29.0 and 26.5; 20 arrays of 10^6: 203.8 and 205.4)
     if (!(opt && opt->threads) && n > 0) {
         uint64_t widest = 0;
         for (const Request& rq : rqs)
-            widest = std::max<uint64_t>(widest, std::min<uint64_t>(rq.dst.npad, 512) * rq.record.packed_size);
-        if (widest <= 8192)
+            widest = std::max<uint64_t>(widest, rq.dst.npad * rq.record.packed_size);
+        if (widest <= kBatchSmallItemBytes)
             threads = 128;
     }
 

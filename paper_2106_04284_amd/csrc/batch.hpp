@@ -82,6 +82,10 @@ constexpr uint32_t kBatchLdsBytes = kHardLdsBytes / 5 - 64;
 // tile size or an LDS budget (tiles of up to 256 records may hold more)
 constexpr uint32_t kBatchTileBytes = 12800;
 
+// a batch whose items all hold at most this many bytes (destination records,
+// packed) runs 128 threads per workgroup unless the caller gives a count
+constexpr uint64_t kBatchSmallItemBytes = 128 * 1024;
+
 // How a table runs: one workgroup per work unit when its items share one LDS
 // class, else a persistent grid (see create_batch).
 bool batch_per_unit(const BatchTable& t);

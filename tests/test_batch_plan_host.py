@@ -96,3 +96,22 @@ def test_batch_tiles_of_a_given_budget(planner):
     room and the leaf table."""
     assert [_tile(planner, "particle", A, S, 10 ** 6, budget=k * 1024) for k in (8, 16, 31, 48)] == [256, 512, 1024, 1024]
     assert [_tile(planner, "mixed", A, S, 10 ** 6, budget=k * 1024) for k in (16, 31, 64)] == [256, 512, 1024]
+
+
+@pytest.mark.parametrize("rec,size", [("small", 3), ("pair", 8), ("vec4", 16), ("particle", 28), ("mixed", 49)])
+def test_batch_threads_by_item(planner, rec, size):
+    """128 threads where every item is small (at most 128 KiB of records),
+    whatever its tiles; one larger item, or a count that is given, decides."""
+    def threads(counts, given=None):
+        items, th = _items(rec, A, S, counts), ctypes.c_uint32()
+        tiles = (ctypes.c_uint32 * len(counts))()
+        o = L.CopyOptions(0, 0, given, 0, 0) if given else None
+        assert planner.batch_table(ctypes.c_size_t(len(counts)), items.arr, ctypes.byref(o) if o else None,
+                                   ctypes.byref(th), tiles) == 0
+        assert all(0 < t <= max(256, 16 * th.value) for t in tiles)
+        return th.value
+    edge = 128 * 1024 // size
+    assert threads([100, edge]) == 128
+    assert threads([100, edge + 1]) == 256
+    assert threads([10 ** 6] * 3) == 256
+    assert threads([100], given=256) == 256 and threads([10 ** 6], given=64) == 64
