@@ -592,7 +592,8 @@ typedef struct {
  *    LLAMA_COPY_* bits.  Every workgroup reserves
  *    the largest item's LDS, so without a fixed tile size each tiled item
  *    takes the largest tile whose plan fits 32 KB of LDS, of at most 12.5 KB
- *    of source and 16 records per thread (256 records in any case), and no
+ *    of source (a tile loaded into registers: 100 bytes per thread) and 16
+ *    records per thread, but 256 records in any case, and no
  *    larger than the item (the tuning cache, which is measured
  *    on standalone launches, is not used).  Without a thread count, a batch
  *    whose items all hold at most 128 KB (their destination's records, AoSoA

@@ -98,12 +98,12 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // with the bytes per tile: take the largest tile, within the bounds
         // below, whose plan fits kBatchLdsBytes (a standalone launch's tuned tile may be small
         // because many of its workgroups fit a compute unit at once).
-        // the tile found for a class of copies is remembered, so that a
+        // The tile found for a class of copies is remembered, so that a
         // repeated class costs one plan instead of a search
         TuneKey k = tune_key(rq);
         k.bucket = 0;
         const auto key =
-            std::make_tuple(k.leaves, k.src_kind, k.src_lanes, k.dst_kind, k.dst_lanes, threads, flags | (budget << 8));
+            std::make_tuple(k.leaves, k.src_kind, k.src_lanes, k.dst_kind, k.dst_lanes, threads, flags | (lds_budget << 8));
         uint32_t start = 4096;
         {
             std::lock_guard<std::mutex> lock(g_tile_memo_mutex);
@@ -118,11 +118,19 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // with 4,096 and 256; of {f32, f32}: 82, and 60 with 1,024), and no
         // more than 16 records per thread: the LDS moves go value by value
         // ({u8, u16}, 666 arrays of 3,000, SoA into AoS with 128 threads: 9.6
-        // us with 4,096 records, 8.4 with 2,048).  A given LDS budget
-        // (autotuning) alone sets the tile.
-        if (!lds_budget)
-            while (start > 256 && (start * rq.record.packed_size > kBatchTileBytes || start > 16 * threads))
-                start /= 2;
+        // us with 4,096 records, 8.4 with 2,048).  A direct load, whose
+        // threads hold the tile in registers, takes up to 100 bytes per thread
+        // (20 arrays of 10^6, SoA into AoS, 256 threads: listing 1's record
+        // 276 us with 256 records, 183 with 512, 160 with 1,024; the mixed
+        // record 397 with 256, 370 with 512).  A given LDS budget (autotuning)
+        // alone sets the tile.
+        auto bytes_fit = [&](uint32_t T, bool direct_load) {
+            const uint64_t bytes = T * rq.record.packed_size;
+            return lds_budget || T <= 256 ||
+                   (T <= 16 * threads && (bytes <= kBatchTileBytes || (direct_load && bytes <= 100 * threads)));
+        };
+        while (!bytes_fit(start, true))
+            start /= 2;
         // No more than the item has: a tile of 1,024 for the 256 records of a
         // particle-in-cell frame kept four times the LDS it used and took the
         // partial tile's path (4,096 frames, SoA into AoSoA32: 28.6 us, then
@@ -141,7 +149,7 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
             // lost 15%
             const uint32_t lds = p.tile.h.lds_bytes * ((p.tile.h.flags & kTileGatherStore) ? 2u : 1u);
             found = p.path == LLAMA_PATH_STREAM || p.path == LLAMA_PATH_EMPTY ||
-                    (p.path == LLAMA_PATH_TILE &&
+                    (p.path == LLAMA_PATH_TILE && bytes_fit(T, (p.tile.h.flags & kTileDirectLoad) != 0) &&
                      (lds <= budget || (T == 16 && p.tile.h.lds_bytes <= budget)));
         }
         if (!found)

@@ -79,7 +79,8 @@ constexpr bool kBatchByModeDefault = true;
 constexpr uint32_t kBatchLdsBytes = kHardLdsBytes / 5 - 64;
 
 // source bytes that a batch item's tile may hold, unless the caller fixes the
-// tile size or an LDS budget (tiles of up to 256 records may hold more)
+// tile size or an LDS budget (tiles of up to 256 records and direct loads may
+// hold more, see batch_plan)
 constexpr uint32_t kBatchTileBytes = 12800;
 
 // a batch whose items all hold at most this many bytes (destination records,

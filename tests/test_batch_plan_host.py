@@ -90,6 +90,17 @@ def test_batch_tiles_by_bytes(planner, src, dst):
         assert _tile(planner, "small", src, dst, n) == tile, n
 
 
+def test_batch_tiles_of_direct_loads(planner):
+    """A tile loaded into registers may hold 100 bytes per thread (512 mixed
+    records are 98 per thread of 256); other modes keep 12,800."""
+    for threads, tile in [(256, 1024), (128, 512)]:
+        assert _tile(planner, "listing1", S, A, 10 ** 6, threads) == tile
+    assert _tile(planner, "listing1", A, S, 10 ** 6) == 512
+    for threads, tile in [(256, 512), (128, 256)]:
+        assert _tile(planner, "mixed", S, A, 10 ** 6, threads) == tile
+    assert _tile(planner, "mixed", A, S, 10 ** 6) == 256
+
+
 def test_batch_tiles_of_a_given_budget(planner):
     """A given LDS budget alone bounds the tile (the autotuner's candidates):
     particles in one region of 28 bytes per record, one 16-byte granule of
