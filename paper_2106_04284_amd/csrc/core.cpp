@@ -1173,7 +1173,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
     const uint64_t recs = gb * Ld; // records per super-block
     const uint64_t gwords = gb * rq.dst.block / 4;
     const bool more_lanes = src_advance(recs) == 0;
-    bool gather = !direct && !preserve && !(p.flags_in & kPlanNoDirect) && a.dst.mode == kRecordMajor &&
+    bool gather = !direct && !preserve && !(p.flags_in & (kPlanNoDirect | kPlanNoGather)) && a.dst.mode == kRecordMajor &&
                   recs <= kGatherMaxLanes && recs <= T && (gb * rq.dst.block) % 4 == 0 && gwords >= 2 &&
                   gwords <= kGatherMaxWords && rq.dst_ptr[0] % 16 == 0 && a.dst.tile_bytes % 16 == 0 &&
                   (a.dst.tile_bytes / 4) * gwords < (uint64_t(1) << 32);
@@ -1314,7 +1314,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         const uint64_t base = (uint64_t(sb) + 15) & ~uint64_t(15); // the table, 16-byte aligned
         const uint64_t table_bytes = (table.size() * 4 + 15) / 16 * 16;
         const uint64_t room = uint64_t(kTileMaxEntries - a.num_entries - C) * (sizeof(TileEntry) / 4);
-        if (pieces_ok && !(p.flags_in & kPlanNoGather) && cost * 100 <= gwords * kGatherMaxReadsPct &&
+        if (pieces_ok && cost * 100 <= gwords * kGatherMaxReadsPct &&
             table.size() <= room && table.size() < (1u << 16) &&
             base + table_bytes <= std::min<uint64_t>(lds_limit, kHardLdsBytes)) {
             a.flags |= kTileGatherStore;
@@ -1668,6 +1668,27 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             p.threads = threads ? threads : nthreads(t);
             ok = fill_tile(rq, t, kMaxLdsBytes, p);
         }
+        if (ok && !threads && !(p.tile.h.flags & (kTileDirectLoad | kTileDirectStore | kTileGatherStore)) &&
+            (p.tile.h.src.mode == kFieldMajor || rq.src.lanes >= 8)) {
+            // a source in granules of one leaf loads directly when every
+            // thread holds at most kDirectLoadSlots of them: try enough
+            // threads for that, before the bytes per thread below add more
+            // (24 leaves of 1 to 8 bytes, 96 bytes, from SoA into AoSoA32, 4
+            // 10^6 records: 330 us loaded directly, 341 staged)
+            uint32_t slots = 0;
+            for (const Leaf& l : rq.record.leaves)
+                slots += uint32_t((uint64_t(t) * l.size / 16 + 63) / 64 * 64);
+            uint32_t want = (slots + kDirectLoadSlots * 64 - 1) / (kDirectLoadSlots * 64) * 64;
+            if (want > p.threads && want <= 1024) {
+                Plan q = p;
+                q.threads = want;
+                q.flags_in |= kPlanNoGather; // (no thread count makes this tile gather)
+                if (fill_tile(rq, t, kMaxLdsBytes, q) && (q.tile.h.flags & kTileDirectLoad)) {
+                    q.flags_in = p.flags_in;
+                    p = q;
+                }
+            }
+        }
         if (ok && !threads && !(p.tile.h.flags & (kTileDirectStore | kTileGatherStore))) {
             // staging and direct load spend more instructions per byte: about
             // 48 source bytes per thread (listing 1's record from AoSoA16 into
@@ -1676,21 +1697,6 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             // packed AoS, 2^21 records: 67.2 and 62.1)
             p.threads = std::max(p.threads, wide_threads(rq, t, 48));
             rotate_stores(p, t);
-        }
-        if (ok && !threads && !(p.tile.h.flags & (kTileDirectLoad | kTileDirectStore))) {
-            // a source in granules of one leaf loads directly when every
-            // thread holds at most kDirectLoadSlots of them: try enough
-            // threads for that
-            uint32_t slots = 0;
-            for (const Leaf& l : rq.record.leaves)
-                slots += uint32_t((uint64_t(t) * l.size / 16 + 63) / 64 * 64);
-            uint32_t want = (slots + kDirectLoadSlots * 64 - 1) / (kDirectLoadSlots * 64) * 64;
-            if (want > p.threads && want <= 1024) {
-                Plan q = p;
-                q.threads = want;
-                if (fill_tile(rq, t, kMaxLdsBytes, q) && (q.tile.h.flags & kTileDirectLoad))
-                    p = q;
-            }
         }
         if (ok && (p.tile.h.flags & kTileGatherStore) && rq.dst.lanes >= 32 && p.tile.h.src.mode == kFieldMajor) {
             // into AoSoA lane runs of 32 records or more from a field-major

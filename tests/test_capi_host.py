@@ -857,3 +857,17 @@ def test_box_tiles_of_long_lane_blocks(name, lanes, dst, tile):
     src = L.Mapping(r, "aosoa", ext, lanes, linearizer="morton") if lanes else L.Mapping(r, "soa_multi", ext)
     p = L.plan(src, L.Mapping(r, dst[0], ext, linearizer=dst[1]))
     assert (p["path"], p["tile_records"]) == ("box", tile)
+
+
+def test_direct_load_tried_before_threads_are_added():
+    """A 96-byte record of 1- to 8-byte leaves from SoA into lane runs: 128
+    records are 24 slot groups of 64 granules, more than two waves hold and no
+    more than three, so the tile loads directly, whatever threads it then gets."""
+    rec = ["f32", "u8", "f64", "u16", "i32", "f32", "u8", "f64"] * 3
+    groups = sum((128 * size // 16 + 63) // 64 for size in (4, 1, 8, 2, 4, 4, 1, 8)) * 3
+    assert 2 * 8 < groups <= 3 * 8
+    r = L.Record(rec)
+    for src in ("soa_single", "soa_multi"):
+        for lanes in (32, 64):
+            p = L.plan(L.Mapping(r, src, [10 ** 6]), L.Mapping(r, "aosoa", [10 ** 6], lanes))
+            assert (p["path"], p["tile_mode"], p["tile_records"]) == ("tile", "direct_load", 128)
