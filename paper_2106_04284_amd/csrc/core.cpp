@@ -1127,6 +1127,8 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
                  (aligned || (split_ok && sz >= 2 && sz <= 8));
         split_src = split_src || !aligned;
     }
+    if (!direct && (p.flags_in & kPlanDirectStoreOnly))
+        return false;
     if (!rq.dst_stride.empty() && (!direct || a.dst.mode != kRecordMajor))
         return false; // a scattered destination is stored by the direct-store tile only
     if (direct) {
@@ -1455,8 +1457,7 @@ uint32_t default_tile(const Request& rq)
     return uint32_t(T);
 }
 
-// Default threads of a direct store or gather store: about 112 source bytes
-// per thread (128 threads for a 14 KiB particle tile), a multiple of 64 in
+// Threads for about `bytes_per_thread` source bytes each, a multiple of 64 in
 // 64 .. 256.
 uint32_t wide_threads(const Request& rq, uint32_t T, uint32_t bytes_per_thread)
 {
@@ -1465,6 +1466,8 @@ uint32_t wide_threads(const Request& rq, uint32_t T, uint32_t bytes_per_thread)
     return uint32_t(std::min<uint64_t>(std::max<uint64_t>(th, 64), kDefaultThreads));
 }
 
+// Default threads of a direct store or gather store: about 112 source bytes
+// per thread (128 threads for a 14 KiB particle tile).
 uint32_t default_threads(const Request& rq, uint32_t T)
 {
     return wide_threads(rq, T, 112);
@@ -1648,17 +1651,29 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
         // four records per thread in the LDS remap
         auto nthreads = [&](uint32_t t) { return default_threads(rq, t); };
         uint32_t t = T ? T : default_tile(rq);
-        // direct store of a small record (at most 64 bytes) into less than 1
-        // GiB: 256 records, a granule or two per thread (2^23 particles from
-        // AoS into SoA 88.6 us with 128 records and one wave, 85.7 with 256 of
-        // each; 10^6 listing 1 records 20.5 us with 512 records and 128
-        // threads, 16.3 so).  Only a field-major destination or one of long
+        // Direct store of a small record (at most 64 bytes) into less than 1
+        // GiB: the most records that hold 8 KiB, but at least 256, and as many
+        // waves as get 28 source bytes (1.75 granules) per thread each; with
+        // fewer, the last round of granules leaves most of a wave idle.  2^23
+        // particles from AoS into SoA: 88.6 us with 128 records and one wave,
+        // 80 with 256 records and 4 waves.  AoS into SoA of 192 MB, records x
+        // threads: {u8, u16} 70.8 with 1,024 x 64, 162 with 256 x 64, 73.0
+        // with 2,048 x 192; {f32 x 3} 70.8 with 256 x 64, 71.2 with 256 x 128,
+        // 69.4 with 512 x 192, 70.2 with 512 x 256 (and 134 for 360 MB,
+        // against 128.6); {f32 x 6} 73.1 with 128 x 64, 74.1 with 256 x 256,
+        // 70.9 with 256 x 192.  Only a field-major destination or one of long
         // lane runs can take it.
         bool small_store = false;
         if (!T && !threads && rq.record.packed_size <= 64 && total_bytes(rq.dst.blob_size) < kStreamStoreBytes &&
             (rq.dst.lanes == 0 || rq.dst.lanes >= 32) && rq.src.lanes <= 256 && rq.dst.lanes <= 256) {
-            p.threads = wide_threads(rq, 256, 28);
-            small_store = fill_tile(rq, 256, kMaxLdsBytes, p) && (p.tile.h.flags & kTileDirectStore);
+            const uint64_t size = std::max<uint64_t>(rq.record.packed_size, 1);
+            uint32_t t2 = 256;
+            while (t2 < 4096 && 2 * t2 * size <= 8192)
+                t2 *= 2;
+            p.threads = uint32_t(std::min<uint64_t>(std::max<uint64_t>(t2 * size / (28 * 64), 1) * 64, kDefaultThreads));
+            p.flags_in |= kPlanDirectStoreOnly;
+            small_store = fill_tile(rq, t2, kMaxLdsBytes, p);
+            p.flags_in &= ~kPlanDirectStoreOnly;
         }
         if (!small_store)
             p.threads = threads ? threads : nthreads(t);

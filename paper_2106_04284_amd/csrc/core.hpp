@@ -226,6 +226,8 @@ constexpr uint32_t kPlanNoDirect = LLAMA_COPY_NO_DIRECT;
 constexpr uint32_t kPlanNoSplit = LLAMA_COPY_NO_SPLIT;
 constexpr uint32_t kPlanPreserve = LLAMA_COPY_PRESERVE_PADDING;
 constexpr uint32_t kPlanNoGather = LLAMA_COPY_NO_GATHER;
+// within the planner: a tile that the direct store does not take is not planned
+constexpr uint32_t kPlanDirectStoreOnly = 1u << 31;
 constexpr uint32_t kCopyFlags =
     LLAMA_COPY_NO_DIRECT | LLAMA_COPY_NO_SPLIT | LLAMA_COPY_PRESERVE_PADDING | LLAMA_COPY_NO_GATHER; // every bit
 // the flags that change only speed, which the tuner may choose and cache

@@ -871,3 +871,19 @@ def test_direct_load_tried_before_threads_are_added():
         for lanes in (32, 64):
             p = L.plan(L.Mapping(r, src, [10 ** 6]), L.Mapping(r, "aosoa", [10 ** 6], lanes))
             assert (p["path"], p["tile_mode"], p["tile_records"]) == ("tile", "direct_load", 128)
+
+
+@pytest.mark.parametrize("rec,tile,threads", [
+    (["u8", "u8"], 4096, 256), (["u8", "u16"], 2048, 192), ([("u16", 3)], 1024, 192), (["f32", "f32"], 1024, 256),
+    ([("u16", 5)], 512, 128), ([("f32", 3)], 512, 192), ([("f64", 2)], 512, 256), (["f64", "f64", "u16"], 256, 128),
+    (W.LISTING1, 256, 192), ([("f32", 6)], 256, 192), (W.PARTICLE, 256, 256), (W.MIXED, 256, 256)])
+def test_small_direct_store_tiles_by_bytes(rec, tile, threads):
+    """A direct store of a small record takes the most records that hold 8 KiB,
+    256 at least, and the waves that get 28 bytes per thread each."""
+    r = L.Record(rec)
+    for n in (10 ** 6, 10 ** 7):
+        p = L.plan(L.Mapping(r, "aos_packed", [n]), L.Mapping(r, "soa_multi", [n]))
+        assert (p["tile_mode"], p["tile_records"], p["threads"]) == ("direct_store", tile, threads)
+    size = r.info()[1]
+    assert tile == 256 or tile * size <= 8192 < 2 * tile * size or tile == 4096
+    assert threads * 28 <= tile * size < (threads + 64) * 28 or (threads == 256 and tile * size >= 256 * 28)
