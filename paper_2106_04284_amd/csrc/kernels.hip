@@ -592,12 +592,19 @@ __device__ __forceinline__ void direct_store_width(const TileHeader& h, uint32_t
         } u;
         if (!kSplit && whole_reads) {
             u.v = *(const u32x4*)(lds + p);
+        } else if (kSplit && sizeof(T) == 2 && e.w != 0) {
+            // 2-byte values aligned to their size: a branch per granule in
+            // place of one per value ({u8, u16} from AoS into SoA, 8 10^6
+            // records: 12.7 -> 11.6 us)
+#pragma unroll
+            for (uint32_t j = 0; j < per; j++)
+                u.t[j] = *(const T*)(lds + p + (j >> slg) * sk + ((j & sm) << lg));
         } else {
 #pragma unroll
             for (uint32_t j = 0; j < per; j++) {
                 const uint32_t q = p + (j >> slg) * sk + ((j & sm) << lg);
                 if constexpr (kSplit && sizeof(T) >= 2 && sizeof(T) <= 8)
-                    u.t[j] = read_split<T>(lds, q, e.w);
+                    u.t[j] = read_split<T>(lds, q, sizeof(T) == 2 ? 0u : e.w);
                 else
                     u.t[j] = *(const T*)(lds + q);
             }

@@ -421,3 +421,25 @@ def test_whole_tiles(L, orc, case, tile, keep):
     if tile == 256:
         for n in (1, 255, 256, 257, 2051):  # the planner's own tile and threads
             run_case(L, orc, rec, a, b, [n], seed=n, keep=keep)
+
+
+_SMALL = {"u8u16": ["u8", "u16"], "u16u8f32u8": ["u16", "u8", "f32", "u8"], "u16x3": [("u16", 3)], "u8u8": ["u8", "u8"],
+          "f32x3": [("f32", 3)], "f64f64u16": ["f64", "f64", "u16"]}
+
+
+@pytest.mark.parametrize("name", list(_SMALL))
+@pytest.mark.parametrize("src", [("aos_packed", 0), ("aos_aligned", 0), ("aosoa", 8), ("aosoa", 32), ("soa_single", 0)],
+                         ids=lambda x: _name(x))
+def test_small_record_direct_stores(L, orc, name, src):
+    """Records of a few bytes through the direct store: counts below, at and
+    past the tile of its plan, with 2-byte values on and off their own
+    alignment in one record, and blobs on and off the 16-byte grid."""
+    rec = _SMALL[name]
+    r = L.Record(rec)
+    for dst in (("soa_multi", 0), ("soa_single", 0), ("aosoa", 64)):
+        if src[0] == "soa_single" and dst[0] != "aosoa":
+            continue
+        tile = L.plan(L.Mapping(r, src[0], [10 ** 6], src[1]), L.Mapping(r, dst[0], [10 ** 6], dst[1]))["tile_records"]
+        for k, n in enumerate((1, tile - 1, tile, tile + 1, 3 * tile + 17, 5 * tile)):
+            for offs in ((0, 0), (4, 0), (2, 1)):
+                run_case(L, orc, rec, src, dst, [n], 17 * k + offs[0], src_off=offs[0], dst_off=offs[1])
