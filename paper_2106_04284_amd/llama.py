@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import array
 import ctypes
+import operator
 import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -356,8 +357,8 @@ def _blobs(blobs):
     for b in blobs:
         if isinstance(b, tuple):
             ptr, size = b
-            try:
-                words += ((ptr or 0) & _U64, size & _U64)
+            try:  # any integer type (a NumPy one overflows in the mask itself)
+                words += (operator.index(ptr or 0) & _U64, operator.index(size) & _U64)
             except TypeError:  # a ctypes pointer
                 e = Blob(ptr, size)
                 words += (e.ptr or 0, e.size)

@@ -887,3 +887,24 @@ def test_small_direct_store_tiles_by_bytes(rec, tile, threads):
     size = r.info()[1]
     assert tile == 256 or tile * size <= 8192 < 2 * tile * size or tile == 4096
     assert threads * 28 <= tile * size < (threads + 64) * 28 or (threads == 256 and tile * size >= 256 * 28)
+
+
+def test_blob_arrays_take_any_integers():
+    """Blob (pointer, size) pairs of Python, NumPy (signed and unsigned) and
+    ctypes values pack to the same words as the ctypes structure; what the
+    structure refuses is refused."""
+    want = bytes(L.Blob(4096, 64))
+    for i in (int, np.int64, np.uint64, np.int32, np.uint32, np.intp):
+        assert L._blobs([(i(4096), i(64))]) == want, i
+    assert L._blobs([(ctypes.c_void_p(4096), 64)]) == want
+    assert L._blobs([(None, 0)]) == L._blobs([]) == bytes(16)
+    assert L._blobs([(np.int64(-4096), 64)]) == bytes(L.Blob(2 ** 64 - 4096, 64))
+    arr = (ctypes.c_uint8 * 64)()
+    assert L._blobs([(ctypes.cast(arr, ctypes.c_void_p), np.int64(64))]) == bytes(L.Blob(ctypes.addressof(arr), 64))
+    for bad in ((4096.0, 64), (4096, 64.0), ("x", 64)):
+        with pytest.raises(TypeError):
+            L._blobs([bad])
+    m = L.Mapping(L.Record(W.PARTICLE), "aos_packed", [10])
+    with pytest.raises(L.LlamaError) as e:  # through the C ABI: a blob that is too small
+        L.copy(m, [(np.int64(4096), np.int64(8))], m, [(np.int64(1 << 20), np.int64(280))], stream=0)
+    assert e.value.status == L.E_BLOB_TOO_SMALL
