@@ -379,8 +379,12 @@ def _stream(stream):
     if stream is None:
         import torch
         if torch.cuda.is_initialized():
-            # torch.cuda.current_stream().cuda_stream without the Stream object
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            # torch.cuda.current_stream().cuda_stream without the Stream
+            # object, where this torch has the two calls
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

@@ -908,3 +908,21 @@ def test_blob_arrays_take_any_integers():
     with pytest.raises(L.LlamaError) as e:  # through the C ABI: a blob that is too small
         L.copy(m, [(np.int64(4096), np.int64(8))], m, [(np.int64(1 << 20), np.int64(280))], stream=0)
     assert e.value.status == L.E_BLOB_TOO_SMALL
+
+
+def test_stream_without_torchs_private_calls(monkeypatch):
+    """The current stream comes from torch's public interface where the two
+    private calls that skip the Stream object are missing."""
+    torch = pytest.importorskip("torch")
+
+    class Current:
+        cuda_stream = 4711
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Current)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 42 + d, raising=False)
+    assert L._stream(None) == 42
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert L._stream(None) == 4711
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert L._stream(None) == 4711 and L._stream(5) == 5 and L._stream(Current) == 4711
