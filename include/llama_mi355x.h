@@ -467,7 +467,8 @@ typedef struct {
     uint32_t path;          /* llama_path chosen */
     uint32_t tile_records;  /* TILE: records per tile */
     uint32_t threads;       /* threads per workgroup */
-    uint32_t lds_bytes;     /* TILE: LDS bytes per workgroup */
+    uint32_t lds_bytes;     /* TILE: LDS bytes of a workgroup's tile (the launch of a copy far larger than
+                               the caches may set more aside, to bound the workgroups resident) */
     uint64_t workgroups;    /* workgroups launched */
     uint32_t runs;          /* STREAM: contiguous runs (zero runs included) */
     uint32_t wg_per_cu;     /* TILE: persistent workgroups per compute unit (0: one per tile) */

@@ -1423,6 +1423,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
 void tile_grid(Plan& p, uint32_t wg_per_cu)
 {
     p.wg_per_cu = wg_per_cu;
+    p.lds_launch = 0;
     // A copy far larger than the caches (kTileStreamStores) runs best with
     // about 64 KiB of tiles in flight per compute unit: more only queues in
     // front of the memory, and the lines in flight crowd the 4 MiB of L2 that
@@ -1440,7 +1441,7 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
         ((f & kTileGatherWhole) || ((f & kTileDirectStore) && !(f & kTileSplitSrc)))) {
         const uint64_t tile = p.read_bytes * (uint64_t(1) << p.tile.h.log2_tile) / std::max<uint64_t>(p.tile.h.n, 1);
         const uint32_t groups = uint32_t(std::max<uint64_t>((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), 4));
-        p.lds_bytes = std::max(p.tile.h.lds_bytes, kHardLdsBytes / groups / 512 * 512);
+        p.lds_launch = kHardLdsBytes / groups / 512 * 512;
     }
     p.workgroups = wg_per_cu ? std::min<uint64_t>(p.tiles, uint64_t(device_cu_count()) * wg_per_cu) : p.tiles;
 }

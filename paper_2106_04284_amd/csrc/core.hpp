@@ -175,6 +175,7 @@ struct Plan {
     uint32_t threads = 256;
     uint64_t workgroups = 0;
     uint32_t lds_bytes = 0;
+    uint32_t lds_launch = 0; // LDS the launch sets aside beyond lds_bytes, to bound the workgroups resident (tile_grid)
     uint32_t wg_per_cu = 0;
     uint64_t tiles = 0;
     uint32_t flags_in = 0; // llama_copy_options.flags of the request

@@ -2758,7 +2758,8 @@ void launch_one(const Plan& p, void* stream_ptr)
         if (!k)
             fail(LLAMA_E_INVALID_ARG, "no kernel variant for this combination of gathered parts");
         void* args[] = {(void*)&p.tile};
-        check_hip(hipLaunchKernel(k, dim3(grid), dim3(p.threads), args, p.lds_bytes, stream), "hipLaunchKernel(tile_kernel)");
+        check_hip(hipLaunchKernel(k, dim3(grid), dim3(p.threads), args, std::max(p.lds_bytes, p.lds_launch), stream),
+                  "hipLaunchKernel(tile_kernel)");
         break;
     }
     case LLAMA_PATH_STREAM:

@@ -926,3 +926,20 @@ def test_stream_without_torchs_private_calls(monkeypatch):
     assert L._stream(None) == 4711
     monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
     assert L._stream(None) == 4711 and L._stream(5) == 5 and L._stream(Current) == 4711
+
+
+@pytest.mark.parametrize("src,dst", [(("aos_packed", 0), ("soa_multi", 0)), (("soa_multi", 0), ("aos_packed", 0)),
+                                     (("soa_single", 0), ("aosoa", 32)), (("aosoa", 32), ("aos_packed", 0))])
+def test_plan_reports_the_tiles_own_lds(src, dst):
+    """The LDS in a plan is what its tile takes, also where the launch sets
+    more aside (destinations of 1 GiB and more): the same tile of a smaller
+    copy reports as much."""
+    r = L.Record(W.PARTICLE)
+
+    def plan(n, **kw):
+        return L.plan(L.Mapping(r, src[0], [n], src[1]), L.Mapping(r, dst[0], [n], dst[1]), **kw)
+    big = plan(1 << 26)
+    small = plan(1 << 20, tile_records=big["tile_records"], threads=big["threads"])
+    assert big["stream_stores"] and not small["stream_stores"]
+    assert (big["tile_mode"], big["lds_bytes"]) == (small["tile_mode"], small["lds_bytes"])
+    assert big["lds_bytes"] < (big["tile_records"] + 1) * 28 + 7 * 64
