@@ -1669,9 +1669,18 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             (rq.dst.lanes == 0 || rq.dst.lanes >= 32) && rq.src.lanes <= 256 && rq.dst.lanes <= 256) {
             const uint64_t size = std::max<uint64_t>(rq.record.packed_size, 1);
             uint32_t t2 = 256;
-            while (t2 < 4096 && 2 * t2 * size <= 8192)
-                t2 *= 2;
-            p.threads = uint32_t(std::min<uint64_t>(std::max<uint64_t>(t2 * size / (28 * 64), 1) * 64, kDefaultThreads));
+            if (rq.src.lanes && rq.src.kind != LLAMA_AOS_ALIGNED && rq.src.block > rq.src.lanes * size) {
+                // a packed source of other leaves too (a part of a Split, a
+                // copy between differing records), which are loaded as well:
+                // 256 records and the threads rounded up (8 10^6 particles
+                // into SoA without their mass 80.9 us with 256, 81.5 with 192)
+                p.threads = wide_threads(rq, 256, 28);
+            } else {
+                while (t2 < 4096 && 2 * t2 * size <= 8192)
+                    t2 *= 2;
+                p.threads =
+                    uint32_t(std::min<uint64_t>(std::max<uint64_t>(t2 * size / (28 * 64), 1) * 64, kDefaultThreads));
+            }
             p.flags_in |= kPlanDirectStoreOnly;
             small_store = fill_tile(rq, t2, kMaxLdsBytes, p);
             p.flags_in &= ~kPlanDirectStoreOnly;

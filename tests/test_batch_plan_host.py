@@ -1,6 +1,7 @@
-"""Host-side tests of batch plans (no GPU): the tile and the threads that the
-items of a batch take, read from the work table before anything is uploaded.
-A helper compiled here against the library's own headers calls the planner."""
+"""Host-side tests of plans that the C ABI does not show (no GPU): the tile and
+the threads that the items of a batch take, read from the work table before
+anything is uploaded, and those of copies between differing records.  A helper
+compiled here against the library's own headers calls the planner."""
 import ctypes
 import os
 import subprocess
@@ -32,6 +33,22 @@ extern "C" int batch_tile(const llama_copy_item* it, uint32_t threads, uint32_t 
     try {
         const Plan p = batch_plan(make_request(it->src, it->src_blobs, it->dst, it->dst_blobs, true), threads, 0, 0, budget);
         *tile = p.path == LLAMA_PATH_TILE ? 1u << p.tile.h.log2_tile : 0u;
+        return 0;
+    } catch (const Error& e) {
+        return e.status;
+    }
+}
+"""
+
+HELPER += r"""
+extern "C" int leaves_tile(const llama_mapping_desc* src, const llama_mapping_desc* dst, const uint32_t* leaf,
+                           uint32_t* out)
+{
+    try {
+        const std::vector<Plan> p = leaves_plans(src, nullptr, dst, nullptr, leaf, nullptr, false);
+        out[0] = p.size() == 1 && p[0].path == LLAMA_PATH_TILE && (p[0].tile.h.flags & kTileDirectStore);
+        out[1] = 1u << p[0].tile.h.log2_tile;
+        out[2] = p[0].threads;
         return 0;
     } catch (const Error& e) {
         return e.status;
@@ -126,3 +143,14 @@ def test_batch_threads_by_item(planner, rec, size):
     assert threads([100, edge + 1]) == 256
     assert threads([10 ** 6] * 3) == 256
     assert threads([100], given=256) == 256 and threads([10 ** 6], given=64) == 64
+
+
+@pytest.mark.parametrize("src,threads", [(A, 256), (Q32, 256), (("aos_aligned", 0), 192)])
+def test_differing_records_keep_their_threads(planner, src, threads):
+    """A particle's fields without the mass: a packed source brings the mass
+    along, 28 bytes for the 24 that are stored."""
+    a = L.Mapping(L.Record(W.PARTICLE if src[0] != "aos_aligned" else [("f32", 6)]), src[0], [10 ** 6], src[1])
+    b = L.Mapping(L.Record([("f32", 6)]), "soa_multi", [10 ** 6])
+    out = (ctypes.c_uint32 * 3)()
+    assert planner.leaves_tile(ctypes.byref(a.desc), ctypes.byref(b.desc), (ctypes.c_uint32 * 6)(*range(6)), out) == 0
+    assert list(out) == [1, 256, threads]
