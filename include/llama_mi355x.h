@@ -594,12 +594,15 @@ typedef struct {
  *    the largest item's LDS, so without a fixed tile size each tiled item
  *    takes the largest tile whose plan fits 32 KB of LDS, of at most 12.5 KB
  *    of source (a tile loaded into registers: 100 bytes per thread) and 16
- *    records per thread, but 256 records in any case, and no
- *    larger than the item (the tuning cache, which is measured
- *    on standalone launches, is not used).  Without a thread count, a batch
- *    whose items all hold at most 128 KB (their destination's records, AoSoA
- *    tail lanes included, times the packed record) runs 128 threads per
- *    workgroup, else 256.
+ *    records per thread, with which the batch still has 1,024 work units (512
+ *    where a tile is stored from registers without an LDS region); but
+ *    256 records in any case, and no larger than the item (the tuning cache,
+ *    which is measured on standalone launches, is not used).  Without a thread
+ *    count, a batch whose items all hold at most 128 KB (their destination's
+ *    records, AoSoA tail lanes included, times the packed record) runs 128
+ *    threads per workgroup, else 256; a batch of fewer than 1,536 units of 256
+ *    records runs 128 only where the first 512 records of every item hold at
+ *    most 8 KB.
  *  - Items whose record does not fit the tiled kernel are refused with
  *    LLAMA_E_UNSUPPORTED.
  *  - A batch belongs to the device that was current at creation.

@@ -79,11 +79,34 @@ void reap_retired()
 // the largest tile that fitted kBatchLdsBytes, per class of copies (leaf
 // hash, source kind and lanes, destination kind and lanes, threads, flags)
 std::mutex g_tile_memo_mutex;
-std::map<std::tuple<uint64_t, uint32_t, uint64_t, uint32_t, uint64_t, uint32_t, uint32_t>, uint32_t> g_tile_memo;
+std::map<std::tuple<TuneKey, uint32_t, uint32_t>, uint32_t> g_tile_memo;
 
 } // namespace
 
-Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget)
+void BatchUnits::add(const Request& rq)
+{
+    for (uint32_t k = 4; k <= 12; k++)
+        at[k] += (rq.dst.npad + (uint64_t(1) << k) - 1) >> k;
+    widest = std::max<uint64_t>(widest, rq.dst.npad * rq.record.packed_size);
+    widest_tile = std::max<uint64_t>(widest_tile, std::min<uint64_t>(rq.dst.npad, 512) * rq.record.packed_size);
+}
+
+// Small items alone run with half the threads: a workgroup's own cost, finding
+// its item and reading its header, is per wave (4,096 frames of 256 particles,
+// SoA into AoSoA32: 14.4 us with 256 threads, 12.8 with 128; 2,000 arrays of
+// 1,000 particles, AoS into SoA: 34.8 and 28.3; 666 of 3,000: 29.0 and 26.5; 20
+// arrays of 10^6: 203.8 and 205.4).  A batch that does not fill the chip waits
+// for its slowest tile, and keeps 256 threads unless its tiles are small (150
+// arrays of 1,000 particles, SoA into AoS: 4.3 us with 256 threads, 4.7 with 128;
+// 300: 6.1 and 6.4; 500: 8.9 and 8.2).
+uint32_t BatchUnits::threads() const
+{
+    const bool small = at[8] >= kBatchThreadUnits ? widest <= kBatchSmallItemBytes : widest_tile <= 8192;
+    return small && at[4] > 0 ? 128 : kDefaultThreads;
+}
+
+Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget,
+                const BatchUnits* sizes)
 {
     const uint32_t budget = lds_budget ? lds_budget : kBatchLdsBytes;
     if (rq.src.kind == LLAMA_ONE)
@@ -99,11 +122,16 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // below, whose plan fits kBatchLdsBytes (a standalone launch's tuned tile may be small
         // because many of its workgroups fit a compute unit at once).
         // The tile found for a class of copies is remembered, so that a
-        // repeated class costs one plan instead of a search
+        // repeated class costs one plan instead of a search; the larger tiles
+        // that the batch's units allow are part of the class
+        auto units_fit = [&](uint32_t T, bool direct_store) {
+            return !sizes || sizes->at[__builtin_ctz(T)] >= (direct_store ? kBatchStoreUnits : kBatchTileUnits);
+        };
         TuneKey k = tune_key(rq);
         k.bucket = 0;
-        const auto key =
-            std::make_tuple(k.leaves, k.src_kind, k.src_lanes, k.dst_kind, k.dst_lanes, threads, flags | (lds_budget << 8));
+        for (uint32_t T = 512; T <= 4096 && !lds_budget; T *= 2)
+            k.bucket += uint32_t(units_fit(T, true)) + 5 * uint32_t(units_fit(T, false));
+        const auto key = std::make_tuple(k, threads, flags | (lds_budget << 8));
         uint32_t start = 4096;
         {
             std::lock_guard<std::mutex> lock(g_tile_memo_mutex);
@@ -122,14 +150,21 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // threads hold the tile in registers, takes up to 100 bytes per thread
         // (20 arrays of 10^6, SoA into AoS, 256 threads: listing 1's record
         // 276 us with 256 records, 183 with 512, 160 with 1,024; the mixed
-        // record 397 with 256, 370 with 512).  A given LDS budget (autotuning)
-        // alone sets the tile.
-        auto bytes_fit = [&](uint32_t T, bool direct_load) {
+        // record 397 with 256, 370 with 512).  A batch that would have too few
+        // units keeps smaller tiles: they run side by side, and the longest
+        // decides (SoA into AoS, arrays of 10^4: 60 of {f32 x 3} 5.7 us in
+        // 2,400 units, 6.2 in 600, 100 of them 8.0 in 4,000, 7.6 in 1,000; 30
+        // of mixed records 12.5 in 1,200, 13.9 in 600), except direct stores,
+        // whose 256 threads have little to do in 256 records (300 arrays of
+        // 1,000 of listing 1's, AoS into SoA: 11.2 us in 1,200 units, 8.8 in
+        // 600).  A given LDS budget (autotuning) alone sets the tile.
+        auto bytes_fit = [&](uint32_t T, uint32_t mode) {
             const uint64_t bytes = T * rq.record.packed_size;
             return lds_budget || T <= 256 ||
-                   (T <= 16 * threads && (bytes <= kBatchTileBytes || (direct_load && bytes <= 100 * threads)));
+                   (T <= 16 * threads && units_fit(T, (mode & kTileDirectStore) != 0) &&
+                    (bytes <= kBatchTileBytes || ((mode & kTileDirectLoad) && bytes <= 100 * threads)));
         };
-        while (!bytes_fit(start, true))
+        while (!bytes_fit(start, kTileDirectStore | kTileDirectLoad))
             start /= 2;
         // No more than the item has: a tile of 1,024 for the 256 records of a
         // particle-in-cell frame kept four times the LDS it used and took the
@@ -149,7 +184,7 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
             // lost 15%
             const uint32_t lds = p.tile.h.lds_bytes * ((p.tile.h.flags & kTileGatherStore) ? 2u : 1u);
             found = p.path == LLAMA_PATH_STREAM || p.path == LLAMA_PATH_EMPTY ||
-                    (p.path == LLAMA_PATH_TILE && bytes_fit(T, (p.tile.h.flags & kTileDirectLoad) != 0) &&
+                    (p.path == LLAMA_PATH_TILE && bytes_fit(T, p.tile.h.flags) &&
                      (lds <= budget || (T == 16 && p.tile.h.lds_bytes <= budget)));
         }
         if (!found)
@@ -164,9 +199,10 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
     return p;
 }
 
-void BatchTable::add(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget)
+void BatchTable::add(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget,
+                     const BatchUnits* sizes)
 {
-    add_plan(batch_plan(rq, threads, tile_records, flags, lds_budget));
+    add_plan(batch_plan(rq, threads, tile_records, flags, lds_budget, sizes));
 }
 
 void BatchTable::add_plan(const Plan& p)
@@ -341,7 +377,7 @@ uint32_t batch_grid(uint64_t units, uint32_t wg_per_cu)
 }
 
 BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama_copy_options* opt,
-                             uint32_t& threads, std::vector<Request>* work)
+                             uint32_t& threads, std::vector<Request>* work, BatchUnits* sizes)
 {
     reap_retired();
     if (n > 0 && !items)
@@ -368,18 +404,13 @@ BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama
     }
     check_batch_overlap(rqs);
 
-    // Small items alone run with half the threads: a workgroup's own cost,
-    // finding its item and reading its header, is per wave (4,096 frames of
-    // 256 particles, SoA into AoSoA32: 14.4 us with 256 threads, 12.8 with
-    // 128; 2,000 arrays of 1,000 particles, AoS into SoA: 34.8 and 28.3; 666
-    // of 3,000: 29.0 and 26.5; 20 arrays of 10^6: 203.8 and 205.4)
-    if (!(opt && opt->threads) && n > 0) {
-        uint64_t widest = 0;
-        for (const Request& rq : rqs)
-            widest = std::max<uint64_t>(widest, rq.dst.npad * rq.record.packed_size);
-        if (widest <= kBatchSmallItemBytes)
-            threads = 128;
-    }
+    BatchUnits units;
+    for (const Request& rq : rqs)
+        units.add(rq);
+    if (!(opt && opt->threads))
+        threads = units.threads();
+    if (sizes)
+        *sizes = units;
 
     // An item with a Split side becomes its part copies, which write disjoint
     // bytes and so may run side by side; one that would write part of the
@@ -389,7 +420,7 @@ BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama
     for (size_t k = 0; k < n; k++) {
         try {
             if (items[k].src->kind != LLAMA_SPLIT && items[k].dst->kind != LLAMA_SPLIT) {
-                t.add(rqs[k], threads, T, opt ? opt->flags : 0u);
+                t.add(rqs[k], threads, T, opt ? opt->flags : 0u, 0, &units);
                 if (work)
                     work->push_back(rqs[k]);
                 continue;
@@ -400,7 +431,7 @@ BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama
                     fail(LLAMA_E_UNSUPPORTED, "its part copies write parts of the records of a record-major "
                                               "destination part in turn; copy it with llama_copy");
             for (const SubCopy& c : parts) {
-                t.add(c.rq, threads, T, opt ? opt->flags : 0u);
+                t.add(c.rq, threads, T, opt ? opt->flags : 0u, 0, &units);
                 if (work)
                     work->push_back(c.rq);
             }
@@ -457,7 +488,7 @@ Batch* create_batch(size_t n, const llama_copy_item* items, const llama_copy_opt
 {
     uint32_t threads = 0;
     std::unique_ptr<Batch> b(new Batch());
-    const BatchTable t = build_batch_table(n, items, opt, threads, &b->work);
+    const BatchTable t = build_batch_table(n, items, opt, threads, &b->work, &b->sizes);
     b->flags = opt ? opt->flags : 0u;
     b->tile_records = opt ? opt->tile_records : 0u;
     b->threads = threads;
@@ -545,7 +576,7 @@ void autotune_batch(Batch* b, void* stream_ptr, int reps, double* best_gbs)
                 BatchTable t;
                 try {
                     for (const Request& rq : b->work)
-                        t.add(rq, th, b->tile_records, b->flags, bud);
+                        t.add(rq, th, b->tile_records, b->flags, bud, &b->sizes);
                 } catch (const Error&) {
                     continue; // an item does not fit this budget
                 }
@@ -572,7 +603,7 @@ void autotune_batch(Batch* b, void* stream_ptr, int reps, double* best_gbs)
         // re-plan with the fastest
         BatchTable t;
         for (const Request& rq : b->work)
-            t.add(rq, best.threads, b->tile_records, b->flags, best.budget);
+            t.add(rq, best.threads, b->tile_records, b->flags, best.budget, &b->sizes);
         b->threads = best.threads;
         b->lds_budget = best.budget;
         install_table(b, t, best.wg, best.by_mode);

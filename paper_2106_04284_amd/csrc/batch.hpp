@@ -16,6 +16,17 @@ struct BatchRange {
     uint32_t lds_bytes = 0; // the range's largest item
 };
 
+// How many work units the items of a batch make at each tile size, before any
+// is planned: what decides between fewer, larger tiles and more, smaller ones.
+struct BatchUnits {
+    uint64_t at[13] = {}; // by log2 of the tile's records, 4 .. 12
+    uint64_t widest = 0;       // most bytes of an item (destination records, packed)
+    uint64_t widest_tile = 0;  // ... of its first 512 records
+    void add(const Request& rq);
+    // threads per workgroup where none are given
+    uint32_t threads() const;
+};
+
 struct Batch {
     int device = 0;
     // non-empty: one launch per mode range (a table sorted by mode), else one
@@ -25,6 +36,7 @@ struct Batch {
     uint32_t flags = 0;        // LLAMA_COPY_* bits of the batch
     uint32_t tile_records = 0; // fixed tile size (0: each item's own)
     uint32_t lds_budget = 0;   // LDS a tiled item's plan may take (without a fixed tile size)
+    BatchUnits sizes;          // of `work`
     uint32_t threads = 0;
     uint32_t wg_per_cu = 0; // persistent: workgroups per compute unit; 0: one workgroup per work unit
     uint32_t grid = 0;
@@ -55,7 +67,7 @@ struct BatchTable {
     // plans `rq` with `threads` per workgroup and adds it; fails with
     // LLAMA_E_UNSUPPORTED for a record the tiled kernel cannot hold
     void add(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags = 0,
-             uint32_t lds_budget = 0);
+             uint32_t lds_budget = 0, const BatchUnits* sizes = nullptr);
     // adds an item planned by batch_plan
     void add_plan(const Plan& p);
     // reorders the items by tile mode (stable) and returns the mode ranges
@@ -86,6 +98,10 @@ constexpr uint32_t kBatchTileBytes = 12800;
 // a batch whose items all hold at most this many bytes (destination records,
 // packed) runs 128 threads per workgroup unless the caller gives a count
 constexpr uint64_t kBatchSmallItemBytes = 128 * 1024;
+// work units that a batch must have left for tiles of more than 256 records
+// (direct stores: fewer), and from which half the threads pay for small items
+// (see batch_plan, BatchUnits::threads)
+constexpr uint64_t kBatchTileUnits = 1024, kBatchStoreUnits = 512, kBatchThreadUnits = 1536;
 
 // How a table runs: one workgroup per work unit when its items share one LDS
 // class, else a persistent grid (see create_batch).
@@ -101,12 +117,14 @@ constexpr uint64_t kBatchMaxGrid = uint64_t(1) << 24;
 uint32_t batch_grid(uint64_t units, uint32_t wg_per_cu);
 
 // the plan of a batch item (see BatchTable::add)
-// (lds_budget 0: kBatchLdsBytes, and tiles of kBatchTileBytes)
-Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget = 0);
+// (lds_budget 0: kBatchLdsBytes, and tiles of kBatchTileBytes; sizes: the units
+// of all its items, NULL: many)
+Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget = 0,
+                const BatchUnits* sizes = nullptr);
 
 // validates the items and plans them into one work table (nothing on the device)
 BatchTable build_batch_table(size_t n, const llama_copy_item* items, const llama_copy_options* opt,
-                             uint32_t& threads, std::vector<Request>* work = nullptr);
+                             uint32_t& threads, std::vector<Request>* work = nullptr, BatchUnits* sizes = nullptr);
 // llama_batch_autotune: times candidate LDS budgets, thread counts and grids
 // on the batch's own blobs, keeps those whose output hashes like the current
 // plan's, and re-plans the batch with the fastest

@@ -218,11 +218,14 @@ void Server::launch_slot(Slot& s, std::vector<Pending>& group)
             launch(make_plan(c.rq, nullptr), s.stream);
     } else if (cfg.policy == LLAMA_SERVE_BATCHED) {
         BatchTable t;
+        BatchUnits sizes;
+        for (const Pending& p : group)
+            sizes.add(p.rq);
         for (Pending& p : group) {
             if (p.parts.empty())
-                t.add(p.rq, cfg.threads, 0);
+                t.add(p.rq, cfg.threads, 0, 0, 0, &sizes);
             for (const SubCopy& c : p.parts) // disjoint bytes: side by side
-                t.add(c.rq, cfg.threads, 0);
+                t.add(c.rq, cfg.threads, 0, 0, 0, &sizes);
         }
         if (t.units > 0) {
             // one launch per tile mode, each mode's own compiled body, like a

@@ -139,10 +139,35 @@ def test_batch_threads_by_item(planner, rec, size):
         assert all(0 < t <= max(256, 16 * th.value) for t in tiles)
         return th.value
     edge = 128 * 1024 // size
-    assert threads([100, edge]) == 128
-    assert threads([100, edge + 1]) == 256
+    many = [100] * 2100  # units enough for the size of the items to decide
+    assert threads(many + [edge]) == 128
+    assert threads(many + [edge + 1]) == 256
     assert threads([10 ** 6] * 3) == 256
     assert threads([100], given=256) == 256 and threads([10 ** 6], given=64) == 64
+
+
+def test_small_batches_keep_small_tiles(planner):
+    """A batch that would have fewer than 1,024 units (direct stores: 512) keeps
+    256 records per tile, and 256 threads unless the first 512 records of its
+    items are at most 8 KiB; the same items in a larger batch take the larger
+    tile, whichever batch was planned first."""
+    def table(rec, counts, src=S, dst=A):
+        items, th = _items(rec, src, dst, counts), ctypes.c_uint32()
+        tiles = (ctypes.c_uint32 * len(counts))()
+        assert planner.batch_table(ctypes.c_size_t(len(counts)), items.arr, None, ctypes.byref(th), tiles) == 0
+        return set(tiles), th.value
+    for _ in range(2):
+        assert table("vec3", [1024] * 800) == ({512}, 128)     # 3,200 units of 256, 1,600 of 512, 800 of 1,024
+        assert table("vec3", [1024] * 1024) == ({1024}, 128)
+        assert table("vec3", [1024] * 500) == ({256}, 128) and table("vec3", [1024] * 512) == ({512}, 128)
+        assert table("vec3", [1024] * 500, A, S) == ({512}, 128)   # a direct store: 1,000 units of 512, 500 of 1,024
+        assert table("vec3", [1024] * 512, A, S) == ({1024}, 128)
+        assert table("listing1", [10 ** 4] * 50) == ({256}, 256)   # 1,000 units of 512
+        assert table("listing1", [10 ** 4] * 60) == ({512}, 256)
+        assert table("listing1", [10 ** 4] * 25, A, S) == ({256}, 256)
+        assert table("listing1", [10 ** 4] * 26, A, S) == ({512}, 256)
+        assert table("particle", [1000] * 150) == ({256}, 256)     # 600 units, 28,000 bytes each
+        assert table("particle", [256] * 150) == ({256}, 128)      # 7,168 bytes each
 
 
 @pytest.mark.parametrize("src,threads", [(A, 256), (Q32, 256), (("aos_aligned", 0), 192)])
