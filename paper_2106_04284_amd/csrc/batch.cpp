@@ -83,12 +83,31 @@ std::map<std::tuple<TuneKey, uint32_t, uint32_t>, uint32_t> g_tile_memo;
 
 } // namespace
 
+namespace {
+TuneKey class_key(const Request& rq)
+{
+    TuneKey k = tune_key(rq);
+    k.bucket = 0;
+    return k;
+}
+} // namespace
+
 void BatchUnits::add(const Request& rq)
 {
-    for (uint32_t k = 4; k <= 12; k++)
-        at[k] += (rq.dst.npad + (uint64_t(1) << k) - 1) >> k;
+    Units& mine = at[class_key(rq)];
+    for (uint32_t k = 4; k <= 12; k++) {
+        const uint64_t units = (rq.dst.npad + (uint64_t(1) << k) - 1) >> k;
+        mine[k] += units;
+        all[k] += units;
+    }
     widest = std::max<uint64_t>(widest, rq.dst.npad * rq.record.packed_size);
     widest_tile = std::max<uint64_t>(widest_tile, std::min<uint64_t>(rq.dst.npad, 512) * rq.record.packed_size);
+}
+
+const BatchUnits::Units& BatchUnits::of(const Request& rq) const
+{
+    const auto it = at.find(class_key(rq));
+    return it == at.end() ? all : it->second;
 }
 
 // Small items alone run with half the threads: a workgroup's own cost, finding
@@ -101,8 +120,8 @@ void BatchUnits::add(const Request& rq)
 // 300: 6.1 and 6.4; 500: 8.9 and 8.2).
 uint32_t BatchUnits::threads() const
 {
-    const bool small = at[8] >= kBatchThreadUnits ? widest <= kBatchSmallItemBytes : widest_tile <= 8192;
-    return small && at[4] > 0 ? 128 : kDefaultThreads;
+    const bool small = all[8] >= kBatchThreadUnits ? widest <= kBatchSmallItemBytes : widest_tile <= 8192;
+    return small && all[4] > 0 ? 128 : kDefaultThreads;
 }
 
 Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint32_t flags, uint32_t lds_budget,
@@ -123,12 +142,12 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // because many of its workgroups fit a compute unit at once).
         // The tile found for a class of copies is remembered, so that a
         // repeated class costs one plan instead of a search; the larger tiles
-        // that the batch's units allow are part of the class
+        // that the units of the batch's copies of the class allow are part of it
+        const BatchUnits::Units* units = sizes ? &sizes->of(rq) : nullptr;
         auto units_fit = [&](uint32_t T, bool direct_store) {
-            return !sizes || sizes->at[__builtin_ctz(T)] >= (direct_store ? kBatchStoreUnits : kBatchTileUnits);
+            return !units || (*units)[__builtin_ctz(T)] >= (direct_store ? kBatchStoreUnits : kBatchTileUnits);
         };
-        TuneKey k = tune_key(rq);
-        k.bucket = 0;
+        TuneKey k = class_key(rq);
         for (uint32_t T = 512; T <= 4096 && !lds_budget; T *= 2)
             k.bucket += uint32_t(units_fit(T, true)) + 5 * uint32_t(units_fit(T, false));
         const auto key = std::make_tuple(k, threads, flags | (lds_budget << 8));
@@ -150,14 +169,17 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // threads hold the tile in registers, takes up to 100 bytes per thread
         // (20 arrays of 10^6, SoA into AoS, 256 threads: listing 1's record
         // 276 us with 256 records, 183 with 512, 160 with 1,024; the mixed
-        // record 397 with 256, 370 with 512).  A batch that would have too few
-        // units keeps smaller tiles: they run side by side, and the longest
-        // decides (SoA into AoS, arrays of 10^4: 60 of {f32 x 3} 5.7 us in
+        // record 397 with 256, 370 with 512).  A class of copies that would
+        // have too few units keeps smaller tiles: they run side by side, and the
+        // longest decides (SoA into AoS, arrays of 10^4: 60 of {f32 x 3} 5.7 us in
         // 2,400 units, 6.2 in 600, 100 of them 8.0 in 4,000, 7.6 in 1,000; 30
         // of mixed records 12.5 in 1,200, 13.9 in 600), except direct stores,
         // whose 256 threads have little to do in 256 records (300 arrays of
         // 1,000 of listing 1's, AoS into SoA: 11.2 us in 1,200 units, 8.8 in
-        // 600).  A given LDS budget (autotuning) alone sets the tile.
+        // 600); of the class, because a mode's launch waits for its last tile
+        // (46 arrays of particle and mixed records in every pair of layouts: 107
+        // us, 110 with the batch's units counted).  A given LDS budget
+        // (autotuning) alone sets the tile.
         auto bytes_fit = [&](uint32_t T, uint32_t mode) {
             const uint64_t bytes = T * rq.record.packed_size;
             return lds_budget || T <= 256 ||

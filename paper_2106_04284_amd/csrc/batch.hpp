@@ -1,6 +1,8 @@
 // Batches of copies run by one persistent kernel.
 #pragma once
 
+#include <array>
+#include <map>
 #include <memory>
 #include <vector>
 
@@ -19,10 +21,16 @@ struct BatchRange {
 // How many work units the items of a batch make at each tile size, before any
 // is planned: what decides between fewer, larger tiles and more, smaller ones.
 struct BatchUnits {
-    uint64_t at[13] = {}; // by log2 of the tile's records, 4 .. 12
-    uint64_t widest = 0;       // most bytes of an item (destination records, packed)
-    uint64_t widest_tile = 0;  // ... of its first 512 records
+    using Units = std::array<uint64_t, 13>; // by log2 of the tile's records, 4 .. 12
+    // per class of copies (as the tuning cache's, without the size): a mode's
+    // launch holds whole classes
+    std::map<TuneKey, Units> at;
+    Units all{};
+    uint64_t widest = 0;      // most bytes of an item (destination records, packed)
+    uint64_t widest_tile = 0; // ... of its first 512 records
     void add(const Request& rq);
+    // the units of rq's class (of a Split's part: of the whole batch)
+    const Units& of(const Request& rq) const;
     // threads per workgroup where none are given
     uint32_t threads() const;
 };
@@ -98,9 +106,9 @@ constexpr uint32_t kBatchTileBytes = 12800;
 // a batch whose items all hold at most this many bytes (destination records,
 // packed) runs 128 threads per workgroup unless the caller gives a count
 constexpr uint64_t kBatchSmallItemBytes = 128 * 1024;
-// work units that a batch must have left for tiles of more than 256 records
-// (direct stores: fewer), and from which half the threads pay for small items
-// (see batch_plan, BatchUnits::threads)
+// work units that a class of a batch's copies must have left for tiles of more
+// than 256 records (direct stores: fewer), and that a batch must have for half
+// the threads to pay for small items (see batch_plan, BatchUnits::threads)
 constexpr uint64_t kBatchTileUnits = 1024, kBatchStoreUnits = 512, kBatchThreadUnits = 1536;
 
 // How a table runs: one workgroup per work unit when its items share one LDS
