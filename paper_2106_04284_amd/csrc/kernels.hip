@@ -1969,15 +1969,15 @@ __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* 
             if (k < Rs) {
                 const uint64_t st = tab_s[k];
                 const uint32_t w = run_len(S, st, len_s);
-                // the slot's first granule is that of the run's first value
-                // (kSrcLeafSlots), else of its start index rounded down
-                const uint64_t first = en.src_addr + st * en.size;
-                const uint32_t rel = kSrc == kSrcLeafSlots ? uint32_t(first) & 15u
-                                                           : (uint32_t(st) & S.amask) * en.size + (uint32_t(en.src_addr) & 15u);
+                // the slot's first granule is that of its start index rounded
+                // down, or (kSrcLeafSlots) that of the run's first value
+                uint32_t rel = (uint32_t(st) & S.amask) * en.size + (uint32_t(en.src_addr) & 15u);
+                if constexpr (kSrc == kSrcLeafSlots)
+                    rel = uint32_t(en.src_addr + st * en.size) & 15u;
                 const uint32_t g0 = rel >> 4, g1 = w ? (rel + w * en.size + 15u) >> 4 : 0u;
-                const uint64_t ga = (kSrc == kSrcLeafSlots
-                                         ? first & ~uint64_t(15)
-                                         : (en.src_addr & ~uint64_t(15)) + (st & ~uint64_t(S.amask)) * en.size) + uint64_t(gi) * 16u;
+                uint64_t ga = (en.src_addr & ~uint64_t(15)) + (st & ~uint64_t(S.amask)) * en.size + uint64_t(gi) * 16u;
+                if constexpr (kSrc == kSrcLeafSlots)
+                    ga = ((en.src_addr + st * en.size) & ~uint64_t(15)) + uint64_t(gi) * 16u;
                 const uint32_t la = uniform(lds_base + (en.src_off & ~15u) + sub * 1024u);
                 if (gi >= g0 && gi < g1)
                     lds_dma16<false, kCount>(ga, la);
