@@ -1669,11 +1669,15 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             (rq.dst.lanes == 0 || rq.dst.lanes >= 32) && rq.src.lanes <= 256 && rq.dst.lanes <= 256) {
             const uint64_t size = std::max<uint64_t>(rq.record.packed_size, 1);
             uint32_t t2 = 256;
-            if (rq.src.lanes && rq.src.kind != LLAMA_AOS_ALIGNED && rq.src.block > rq.src.lanes * size) {
-                // a packed source of other leaves too (a part of a Split, a
-                // copy between differing records), which are loaded as well:
-                // 256 records and the threads rounded up (8 10^6 particles
-                // into SoA without their mass 80.9 us with 256, 81.5 with 192)
+            auto other_leaves = [&](const Side& s) {
+                return s.lanes && s.kind != LLAMA_AOS_ALIGNED && s.block > s.lanes * size;
+            };
+            if (other_leaves(rq.src) || other_leaves(rq.dst)) {
+                // a packed side with other leaves too (a part of a Split, a
+                // copy between differing records): 256 records and the threads
+                // rounded up (8 10^6 particles into SoA without their mass
+                // 80.9 us with 256, 81.5 with 192; 24 10^6 without mass into
+                // particles, AoSoA32, 205.5 and 208.3)
                 p.threads = wide_threads(rq, 256, 28);
             } else {
                 while (t2 < 4096 && 2 * t2 * size <= 8192)

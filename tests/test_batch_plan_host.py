@@ -170,12 +170,16 @@ def test_small_batches_keep_small_tiles(planner):
         assert table("particle", [256] * 150) == ({256}, 128)      # 7,168 bytes each
 
 
-@pytest.mark.parametrize("src,threads", [(A, 256), (Q32, 256), (("aos_aligned", 0), 192)])
-def test_differing_records_keep_their_threads(planner, src, threads):
-    """A particle's fields without the mass: a packed source brings the mass
-    along, 28 bytes for the 24 that are stored."""
-    a = L.Mapping(L.Record(W.PARTICLE if src[0] != "aos_aligned" else [("f32", 6)]), src[0], [10 ** 6], src[1])
-    b = L.Mapping(L.Record([("f32", 6)]), "soa_multi", [10 ** 6])
+@pytest.mark.parametrize("src,dst,threads", [
+    (("particle",) + A, ("fields",) + S, 256), (("particle",) + Q32, ("fields",) + S, 256),
+    (("fields", "soa_multi", 0), ("particle",) + Q32, 256), (("fields", "aos_aligned", 0), ("fields",) + S, 192)])
+def test_differing_records_keep_their_threads(planner, src, dst, threads):
+    """A particle's fields without the mass, from and into particles: a packed
+    side that holds the mass too is sized as before, 256 threads; without one,
+    24 bytes of 256 records feed 192."""
+    records = {"particle": W.PARTICLE, "fields": [("f32", 6)]}
+    a, b = (L.Mapping(L.Record(records[r]), kind, [10 ** 6], lanes) for r, kind, lanes in (src, dst))
+    leaf = (ctypes.c_uint32 * 7)(*range(6), L.NO_LEAF)
     out = (ctypes.c_uint32 * 3)()
-    assert planner.leaves_tile(ctypes.byref(a.desc), ctypes.byref(b.desc), (ctypes.c_uint32 * 6)(*range(6)), out) == 0
+    assert planner.leaves_tile(ctypes.byref(a.desc), ctypes.byref(b.desc), leaf, out) == 0
     assert list(out) == [1, 256, threads]
