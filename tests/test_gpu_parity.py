@@ -443,3 +443,17 @@ def test_small_record_direct_stores(L, orc, name, src):
         for k, n in enumerate((1, tile - 1, tile, tile + 1, 3 * tile + 17, 5 * tile)):
             for offs in ((0, 0), (4, 0), (2, 1)):
                 run_case(L, orc, rec, src, dst, [n], 17 * k + offs[0], src_off=offs[0], dst_off=offs[1])
+
+
+@pytest.mark.parametrize("tile,threads", [(0, 0), (16, 64), (256, 192), (512, 256), (1024, 128), (2048, 512)])
+def test_field_loads_of_uneven_leaves(L, orc, tile, threads):
+    """Leaf spans of one to sixteen 1 KiB chunks side by side, loaded by one to
+    eight waves that share the chunks of all leaves: every chunk is loaded,
+    whole tiles and the last one, spans on and off the 16-byte grid."""
+    rec = ["u8", "f64", "u16", "u8", "f32", "f64", "u8"]
+    for k, (src, dst) in enumerate([(("soa_multi", 0), ("aos_aligned", 0)), (("soa_single", 0), ("aosoa", 8)),
+                                    (("soa_multi", 0), ("aos_packed", 0)), (("soa_multi", 0), ("soa_single", 0))]):
+        for n, off in ((5000, 0), (4096, 4), (2047, 1), (15, 2)):
+            run_case(L, orc, rec, src, dst, [n], 31 * k + n, src_off=off, tile_records=tile, threads=threads)
+            run_case(L, orc, rec, src, dst, [n], 37 * k + n, src_off=off, tile_records=tile, threads=threads,
+                     flags=L_NO_DIRECT)
