@@ -357,11 +357,14 @@ def _blobs(blobs):
     for b in blobs:
         if isinstance(b, tuple):
             ptr, size = b
-            try:  # any integer type (a NumPy one overflows in the mask itself)
-                words += (operator.index(ptr or 0) & _U64, operator.index(size) & _U64)
-            except TypeError:  # a ctypes pointer
-                e = Blob(ptr, size)
-                words += (e.ptr or 0, e.size)
+            try:
+                words += ((ptr or 0) & _U64, size & _U64)
+            except (TypeError, OverflowError):
+                try:  # a NumPy integer, which overflows in the mask itself
+                    words += (operator.index(ptr or 0) & _U64, operator.index(size) & _U64)
+                except TypeError:  # a ctypes pointer
+                    e = Blob(ptr, size)
+                    words += (e.ptr or 0, e.size)
         else:  # a torch tensor
             if not b.is_contiguous():
                 raise ValueError("blob tensors must be contiguous")
