@@ -76,8 +76,9 @@ void reap_retired()
     (void)hipGetLastError();
 }
 
-// the largest tile that fitted kBatchLdsBytes, per class of copies (leaf
-// hash, source kind and lanes, destination kind and lanes, threads, flags)
+// the tile taken per class of copies (leaf sizes and alignments, kinds and
+// lanes of both sides, and the larger tiles that the class's units allow), the
+// threads, and the flags with the LDS budget
 std::mutex g_tile_memo_mutex;
 std::map<std::tuple<TuneKey, uint32_t, uint32_t>, uint32_t> g_tile_memo;
 
@@ -138,8 +139,9 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // Every workgroup of the launch reserves the same LDS and about five
         // fit a compute unit, so the bytes in flight per compute unit grow
         // with the bytes per tile: take the largest tile, within the bounds
-        // below, whose plan fits kBatchLdsBytes (a standalone launch's tuned tile may be small
-        // because many of its workgroups fit a compute unit at once).
+        // below, whose plan fits kBatchLdsBytes (a standalone launch's tuned
+        // tile may be small because many of its workgroups fit a compute unit
+        // at once).
         // The tile found for a class of copies is remembered, so that a
         // repeated class costs one plan instead of a search; the larger tiles
         // that the units of the batch's copies of the class allow are part of it

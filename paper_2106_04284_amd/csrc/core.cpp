@@ -1217,8 +1217,10 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         // super-block 0).  A piece is one entry: p0, the source byte that the
         // word's byte 0 lines up with, its run and the word bytes it gives.
         // A word of one piece (or none: padding) is its own table entry; a
-        // word of two pieces points to a pair of entries; a word of three or
-        // four to the sources of its 4 bytes, placed after the word entries.
+        // word of two pieces points to a group of four words, the two entries
+        // and the byte masks of what they give; a word of three or four to a
+        // group of the sources of its 4 bytes.  The groups follow the word
+        // entries.
         std::vector<uint32_t> table(gwords), quads, pairs;
         bool pieces_ok = true;
         for (uint64_t w = 0; w < gwords && pieces_ok; w++) {
@@ -1649,7 +1651,6 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             fail(LLAMA_E_UNSUPPORTED, "the STREAM path needs long runs congruent modulo 4 on both sides");
     }
     if (want == LLAMA_PATH_AUTO || want == LLAMA_PATH_TILE) {
-        // four records per thread in the LDS remap
         auto nthreads = [&](uint32_t t) { return default_threads(rq, t); };
         uint32_t t = T ? T : default_tile(rq);
         // Direct store of a small record (at most 64 bytes) into less than 1

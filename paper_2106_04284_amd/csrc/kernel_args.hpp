@@ -83,8 +83,9 @@ constexpr uint32_t kMoveSplit = 1u << 3;
 //                     (16-byte aligned) give its bytes one by one, entry k the
 //                     LDS byte p0 of byte k in super-block 0 and its run in
 //                     the same bits (bit 31: a zero byte).
-// The word entries are padded to a multiple of 4; the groups of four follow.  Records without values (tail lanes of the last AoSoA
-// block) are cleared in the source region before the tile's words are read.
+// The word entries are padded to a multiple of 4; the groups of four follow.
+// Records without values (tail lanes of the last AoSoA block) are cleared in
+// the source region before the tile's words are read.
 // The table follows the entries: in the argument block at entry num_entries
 // (reinterpreted as 32-bit words), in a batch after the item's entries; in
 // LDS it sits at dst.lds_base, 16-byte aligned.  A piece of super-block b lies
@@ -379,12 +380,14 @@ struct BoxSide {
     uint32_t morton_bits; // bits per dimension of the Morton index
     uint32_t run_log2; // log2 of a run's records (unclipped)
     uint32_t gran;     // record-major source, staged destination: 16-byte granules of a run's LDS slot;
-                       // field-major source: records of a run's slot (of every leaf)
+                       // field-major source: records of a run's slot (of every leaf; kBoxLeafSlots:
+                       // not used, each leaf has its own BoxEntry::gran)
     uint32_t magic;    // ceil(2^32 / gran): g / gran == mulhi(g, magic) for the granule counts of a tile
     uint32_t lds_base; // LDS byte of run 0
     uint32_t table;    // LDS byte of the run table (one 64-bit start index per run)
     uint32_t amask;    // field-major source: a run's slot starts at its start index with these bits
                        // cleared, a whole number of 16-byte granules into every leaf
+                       // (kBoxLeafSlots: not used, a slot starts at the leaf's own granule)
     uint32_t pad;
 };
 

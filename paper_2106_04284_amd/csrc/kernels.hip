@@ -1825,17 +1825,18 @@ __device__ __forceinline__ void box_granules(const BoxArgs& a, const BoxEntry& e
 // kMorton: a side may be in Morton order; else both are row- or column-major
 // (or One), and every index is a base plus coordinates times strides.
 //
-// What a tile costs beside its memory accesses decides this kernel: with
-// 64-bit origin arithmetic, run walks and value stores it spent about 1,000
-// scalar and 900 vector instructions per wave on ten 1 KiB accesses, which
-// kept the compute units' scalar and vector issue busy for most of the copy.
-// So the host provides strides and reciprocals, the waves take chunks of all
-// leaves in turn (a leaf is a division away), and a record's source is one
-// 4-byte entry for all leaves; it takes 670 and 680 now.  128^3 lattice-
-// Boltzmann cells out of a grid with a halo: SoA into aligned AoS 237 -> 139
-// us (4.7 TB/s), aligned AoS into SoA 161 -> 129 us (5.1 TB/s); 2^24
-// particles: row-major AoS into column-major SoA 353 -> 188 us (5.0 TB/s),
-// column-major SoA into Morton AoSoA32 628 -> 211 us (4.4 TB/s).
+// What a tile costs beside its memory accesses decides this kernel: origin
+// arithmetic, run walks and value stores per tile kept the compute units'
+// scalar and vector issue busy for most of the copy.  So the host provides
+// strides and reciprocals, the waves take chunks of all leaves in turn (a leaf
+// is a division away), a record's source is one 4-byte entry for all leaves,
+// and a workgroup takes one tile.  Scalar and vector instructions per wave
+// and time, before and now: 128^3 lattice-Boltzmann cells out of a grid with
+// a halo, SoA into aligned AoS 1,084 and 1,433, 237 us -> 655 and 728, 139 us
+// (4.7 TB/s); aligned AoS into SoA 986 and 828, 161 us -> 575 and 416, 129 us
+// (5.1 TB/s); 2^24 particles, row-major AoS into column-major SoA 1,221 and
+// 1,038, 353 us -> 793 and 699, 188 us (5.0 TB/s); column-major SoA into
+// Morton AoSoA32 3,076 and 2,278, 628 us -> 1,095 and 725, 211 us (4.4 TB/s).
 template <int R, bool kMorton, bool kStaged, uint32_t kSrc, bool kCount>
 __device__ __forceinline__ void box_body(const BoxArgs& a, uint32_t u, uint8_t* lds)
 {
