@@ -1442,7 +1442,15 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
     if ((f & kTileStreamStores) && wg_per_cu == 0 &&
         ((f & kTileGatherWhole) || ((f & kTileDirectStore) && !(f & kTileSplitSrc)))) {
         const uint64_t tile = p.read_bytes * (uint64_t(1) << p.tile.h.log2_tile) / std::max<uint64_t>(p.tile.h.n, 1);
-        const uint32_t groups = uint32_t(std::max<uint64_t>((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), 4));
+        // A gathered source finds each granule's part by a walk over the
+        // chunks of its block, so its waves also compute: at least 6 groups,
+        // 8 from 4 chunks on (2^26 particles into AoS, AoSoA32 positions and
+        // SoA velocities and mass, 5 chunks: 763 us with 5, 655 with 6, 625
+        // with 8 to 11; two AoSoA32 halves, 2 chunks: 666, 618, 629; 2^23
+        // lattice-Boltzmann cells into aligned AoS, half of the leaves SoA, 11
+        // chunks: 663, 565, 463).
+        const uint64_t least = !(f & kTileVirtualSrc) ? 4 : p.tile.h.slots <= 3 ? 6 : 8;
+        const uint32_t groups = uint32_t(std::max((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), least));
         p.lds_launch = kHardLdsBytes / groups / 512 * 512;
     }
     p.workgroups = wg_per_cu ? std::min<uint64_t>(p.tiles, uint64_t(device_cu_count()) * wg_per_cu) : p.tiles;

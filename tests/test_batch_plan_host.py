@@ -56,6 +56,26 @@ extern "C" int leaves_tile(const llama_mapping_desc* src, const llama_mapping_de
 }
 """
 
+HELPER += r"""
+extern "C" int gathered(const llama_mapping_desc* src, const llama_mapping_desc* dst, uint32_t* out)
+{
+    try {
+        const Request rq = make_request(src, nullptr, dst, nullptr, false, true);
+        const std::vector<SubCopy> c = split_copies(src, dst, rq, true, nullptr);
+        if (c.empty() || !c[0].plan)
+            return -1;
+        const Plan& p = *c[0].plan;
+        out[0] = (p.tile.h.flags & kTileVirtualSrc) != 0;
+        out[1] = p.tile.h.slots;
+        out[2] = p.lds_bytes;
+        out[3] = p.lds_launch;
+        return 0;
+    } catch (const Error& e) {
+        return e.status;
+    }
+}
+"""
+
 RECORDS = dict(W.RECORDS, small=["u8", "u16"], pair=["f32", "f32"], vec3=[("f32", 3)], vec4=[("f32", 4)])
 
 
@@ -183,3 +203,22 @@ def test_differing_records_keep_their_threads(planner, src, dst, threads):
     out = (ctypes.c_uint32 * 3)()
     assert planner.leaves_tile(ctypes.byref(a.desc), ctypes.byref(b.desc), leaf, out) == 0
     assert list(out) == [1, 256, threads]
+
+
+@pytest.mark.parametrize("rec,first,count,a,b,dst,least", [
+    ("particle", 0, 3, ("aosoa", 32), ("aosoa", 32), A, 6),       # 2 chunks
+    ("particle", 0, 5, ("aosoa", 32), ("soa_multi", 0), A, 6),    # 3
+    ("particle", 0, 4, ("aosoa", 32), ("soa_multi", 0), A, 8),    # 4
+    ("particle", 0, 3, ("aosoa", 32), ("soa_multi", 0), ("aosoa", 8), 8),
+    ("lbm", 0, 10, ("soa_multi", 0), ("aosoa", 32), ("aos_aligned", 0), 8)])
+def test_gathered_sources_keep_workgroups(planner, rec, first, count, a, b, dst, least):
+    """The LDS that a large copy sets aside beyond its tile's own leaves a
+    gathered source 6 workgroups per compute unit, 8 from 4 chunks on."""
+    n = (5 << 28) // L.Record(RECORDS[rec]).info()[1]  # 1.25 GiB
+    src = L.Mapping(L.Record(RECORDS[rec]), "split", [n], split=(first, count, a, b))
+    to = L.Mapping(L.Record(RECORDS[rec]), dst[0], [n], dst[1])
+    out = (ctypes.c_uint32 * 4)()
+    assert planner.gathered(ctypes.byref(src.desc), ctypes.byref(to.desc), out) == 0
+    gathered, chunks, own, aside = out
+    assert gathered and (chunks <= 3) == (least == 6)
+    assert 0 < own <= 160 * 1024 // least and aside <= 160 * 1024 // least
