@@ -1127,6 +1127,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
                  (aligned || (split_ok && sz >= 2 && sz <= 8));
         split_src = split_src || !aligned;
     }
+    bool off_grid = false; // a direct store whose spans begin off the 16-byte grid
     if (!direct && (p.flags_in & kPlanDirectStoreOnly))
         return false;
     if (!rq.dst_stride.empty() && (!direct || a.dst.mode != kRecordMajor))
@@ -1141,6 +1142,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         for (size_t f = 0; f < F; f++) { // the width is the leaf size; the phase replaces the split bits
             TileEntry& e = ta.e[f];
             const uint32_t phase = a.dst.mode == kFieldMajor ? uint32_t((e.dst_addr & 15) / e.size) : 0u;
+            off_grid = off_grid || phase != 0;
             // the source alignment (kTileSplitSrc)
             const uint32_t rd = log2_move(uint64_t(e.src_pos) | e.size | src_rm_bits);
             e.move = (e.move & ~(7u | kMoveSplit | (0xFFu << 20))) | log2_exact(e.size) | (phase << 20) |
@@ -1409,7 +1411,14 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         if (granules)
             a.flags |= kTileReadsGranules;
     }
-    if (total_bytes(rq.dst.blob_size) >= kStreamStoreBytes)
+    // Direct stores off the 16-byte grid stay plain: each reaches into two lines
+    // of which its neighbours write the rest, and the L2 merges them unless
+    // the lines leave it at once (AoS into single-blob SoA of an odd number of
+    // records, 1.3 GB: particles 519 us with streaming stores, 461 with plain
+    // ones; 48-byte records 588 and 529; lattice-Boltzmann cells 566 and 501).
+    // Two leaves do not fill the L2 with open lines (two floats, 1.7 GB: 557
+    // and 568).
+    if (total_bytes(rq.dst.blob_size) >= kStreamStoreBytes && !(off_grid && F > 2))
         a.flags |= kTileStreamStores;
     if (total_bytes(rq.src.blob_size) >= kStreamLoadBytes)
         a.flags |= kTileStreamLoads;
@@ -1426,7 +1435,7 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
 {
     p.wg_per_cu = wg_per_cu;
     p.lds_launch = 0;
-    // A copy far larger than the caches (kTileStreamStores) runs best with
+    // A copy far larger than the caches (1 GiB written) runs best with
     // about 64 KiB of tiles in flight per compute unit: more only queues in
     // front of the memory, and the lines in flight crowd the 4 MiB of L2 that
     // 32 units share.  LDS set aside beyond a tile's own keeps the other
@@ -1439,9 +1448,15 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
     // pieces needs every wave (the 49-byte mixed record from SoA into aligned
     // AoS, 1.3 GB: 428 us with 10 groups, 529 with 5).
     const uint32_t f = p.tile.h.flags;
-    if ((f & kTileStreamStores) && wg_per_cu == 0 &&
+    // Plain stores off the 16-byte grid (fill_tile) need them too where a tile
+    // of up to 16 KiB has 256 threads (mixed records from aligned AoS into
+    // single-blob SoA, 1.9 GB: 677 us with 4 groups, 650 with 8 and more; 128
+    // particles per tile and wave: 461 with 18, 493 with 32; lattice-Boltzmann
+    // cells, 20 KiB: 501 with 4, 546 with 8).
+    const uint64_t tile = p.read_bytes * (uint64_t(1) << p.tile.h.log2_tile) / std::max<uint64_t>(p.tile.h.n, 1);
+    const bool merging = !(f & (kTileStreamStores | kTileGatherWhole)) && p.threads >= kDefaultThreads && tile <= 16384;
+    if (p.write_bytes >= kStreamStoreBytes && wg_per_cu == 0 && !merging &&
         ((f & kTileGatherWhole) || ((f & kTileDirectStore) && !(f & kTileSplitSrc)))) {
-        const uint64_t tile = p.read_bytes * (uint64_t(1) << p.tile.h.log2_tile) / std::max<uint64_t>(p.tile.h.n, 1);
         // A gathered source finds each granule's part by a walk over the
         // chunks of its block, so its waves also compute: at least 6 groups,
         // 8 from 4 chunks on (2^26 particles into AoS, AoSoA32 positions and
@@ -1801,6 +1816,18 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
                 if (fill_tile(rq, 2 * t, kHardLdsBytes, q) && (q.tile.h.flags & kTileDirectStore) &&
                     q.lds_bytes <= kMaxLdsBytes)
                     p = q;
+            }
+        }
+        if (ok && !T && !threads && p.write_bytes >= kStreamStoreBytes && (p.tile.h.flags & kTileDirectStore) &&
+            !(p.tile.h.flags & kTileStreamStores)) {
+            // plain stores off the 16-byte grid: 256 threads for tiles of 8 KiB
+            // and more (AoS into single-blob SoA, 1.3 GB: mixed records 518 us
+            // with 128 threads, 472 with 256, 48-byte records 529 and 482;
+            // 16-byte records, tiles of 4 KiB, 592 and 597 with 64 and 128)
+            const uint32_t tile = 1u << p.tile.h.log2_tile;
+            if (tile * rq.record.packed_size >= 8192) {
+                p.threads = kDefaultThreads;
+                rotate_stores(p, tile);
             }
         }
         if (ok) {

@@ -943,3 +943,23 @@ def test_plan_reports_the_tiles_own_lds(src, dst):
     assert big["stream_stores"] and not small["stream_stores"]
     assert (big["tile_mode"], big["lds_bytes"]) == (small["tile_mode"], small["lds_bytes"])
     assert big["lds_bytes"] < (big["tile_records"] + 1) * 28 + 7 * 64
+
+
+@pytest.mark.parametrize("rec,off_grid,threads", [
+    (W.PARTICLE, (False, 64), 64), (W.MIXED, (False, 256), 128), (["f32"] * 12, (False, 256), 128),
+    (["f32"] * 4, (False, 64), 64), (["f32"] * 2, (True, 64), 64)])
+def test_large_direct_stores_off_the_grid(rec, off_grid, threads):
+    """Direct stores of 1 GiB and more stream only where every leaf's span
+    starts on the 16-byte grid (or two leaves are open at most); plain ones run
+    256 threads for tiles of 8 KiB and more."""
+    r = L.Record(rec)
+    n = (5 << 28) // r.info()[1] // 64 * 64
+
+    def plan(n, **o):
+        return L.plan(L.Mapping(r, "aos_packed", [n]), L.Mapping(r, "soa_single", [n]), **o)
+    p, q = plan(n), plan(n + 1)
+    assert p["tile_mode"] == q["tile_mode"] == "direct_store" and p["tile_records"] == q["tile_records"]
+    assert (p["stream_stores"], p["threads"]) == (True, threads)
+    assert (q["stream_stores"], q["threads"]) == off_grid
+    assert plan(n + 1, threads=128)["threads"] == 128  # a count that is given stands
+    assert not plan(n // 8)["stream_stores"] and not plan(n // 8 + 1)["stream_stores"]
