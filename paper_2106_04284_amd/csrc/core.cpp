@@ -1464,7 +1464,11 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
         // with 8 to 11; two AoSoA32 halves, 2 chunks: 666, 618, 629; 2^23
         // lattice-Boltzmann cells into aligned AoS, half of the leaves SoA, 11
         // chunks: 663, 565, 463).
-        const uint64_t least = !(f & kTileVirtualSrc) ? 4 : p.tile.h.slots <= 3 ? 6 : 8;
+        // Direct stores spend more on each granule still: 12 (2^26 listing 1
+        // records, 1.2 GB, all but one leaf AoSoA32, into SoA: 533 us with 7
+        // groups, 459 with 12 and more; mixed records, 8 chunks: 994 with 5,
+        // 572 with 8, 506 with 12).
+        const uint64_t least = !(f & kTileVirtualSrc) ? 4 : (f & kTileDirectStore) ? 12 : p.tile.h.slots <= 3 ? 6 : 8;
         const uint32_t groups = uint32_t(std::max((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), least));
         p.lds_launch = kHardLdsBytes / groups / 512 * 512;
     }

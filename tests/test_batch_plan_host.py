@@ -222,3 +222,17 @@ def test_gathered_sources_keep_workgroups(planner, rec, first, count, a, b, dst,
     gathered, chunks, own, aside = out
     assert gathered and (chunks <= 3) == (least == 6)
     assert 0 < own <= 160 * 1024 // least and aside <= 160 * 1024 // least
+
+
+@pytest.mark.parametrize("rec,first,count,a,b", [
+    ("listing1", 1, 6, ("aosoa", 32), ("soa_single", 0)), ("mixed", 4, 3, ("aosoa", 64), ("soa_multi", 0))])
+def test_gathered_direct_stores_keep_workgroups(planner, rec, first, count, a, b):
+    """... and a gathered source that is stored directly 12."""
+    n = (5 << 28) // L.Record(RECORDS[rec]).info()[1] // 64 * 64
+    src = L.Mapping(L.Record(RECORDS[rec]), "split", [n], split=(first, count, a, b))
+    to = L.Mapping(L.Record(RECORDS[rec]), "soa_multi", [n])
+    out = (ctypes.c_uint32 * 4)()
+    assert planner.gathered(ctypes.byref(src.desc), ctypes.byref(to.desc), out) == 0
+    gathered, chunks, own, aside = out
+    assert gathered and chunks >= 2
+    assert 0 < own <= 160 * 1024 // 10 and 0 < aside <= 160 * 1024 // 12
