@@ -1700,19 +1700,20 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             auto other_leaves = [&](const Side& s) {
                 return s.lanes && s.kind != LLAMA_AOS_ALIGNED && s.block > s.lanes * size;
             };
-            if (other_leaves(rq.src) || other_leaves(rq.dst)) {
-                // a packed side with other leaves too (a part of a Split, a
-                // copy between differing records): 256 records and the threads
-                // rounded up (8 10^6 particles into SoA without their mass
-                // 80.9 us with 256, 81.5 with 192; 24 10^6 without mass into
-                // particles, AoSoA32, 205.5 and 208.3)
-                p.threads = wide_threads(rq, 256, 28);
-            } else {
-                while (t2 < 4096 && 2 * t2 * size <= 8192)
-                    t2 *= 2;
-                p.threads =
-                    uint32_t(std::min<uint64_t>(std::max<uint64_t>(t2 * size / (28 * 64), 1) * 64, kDefaultThreads));
-            }
+            // a packed side with other leaves too (a part of a Split, a copy
+            // between differing records): 256 records, and the threads rounded
+            // up from 20 bytes on and where most of a source record is other
+            // leaves (8 10^6 particles into SoA without their mass 80.9 us with
+            // 256, 81.5 with 192; five of six floats, 900 MB, 446 with 192, 458
+            // with 128; three of seven from AoSoA8 451 with 128, 459 with 64;
+            // but two of three, 300 MB, 172 with 128, 155 with 64, and four of
+            // six, gathered, 157 with 192, 145 with 128)
+            const bool others = other_leaves(rq.src) || other_leaves(rq.dst);
+            while (!others && t2 < 4096 && 2 * t2 * size <= 8192)
+                t2 *= 2;
+            const bool up = others && (size >= 20 || (rq.src.lanes && rq.src.block > 2 * size * rq.src.lanes));
+            const uint64_t waves = (t2 * size + (up ? 28 * 64 - 1 : 0)) / (28 * 64);
+            p.threads = uint32_t(std::min<uint64_t>(std::max<uint64_t>(waves, 1) * 64, kDefaultThreads));
             p.flags_in |= kPlanDirectStoreOnly;
             small_store = fill_tile(rq, t2, kMaxLdsBytes, p);
             p.flags_in &= ~kPlanDirectStoreOnly;

@@ -236,3 +236,22 @@ def test_gathered_direct_stores_keep_workgroups(planner, rec, first, count, a, b
     gathered, chunks, own, aside = out
     assert gathered and chunks >= 2
     assert 0 < own <= 160 * 1024 // 10 and 0 < aside <= 160 * 1024 // 12
+
+
+def _part_of(planner, rec, kind, lanes, leaves):
+    """Mode, tile and threads of the copy of some leaves of `rec` into SoA."""
+    a = L.Mapping(L.Record(rec), kind, [10 ** 6], lanes)
+    b = L.Mapping(L.Record([rec[k] for k in leaves]), "soa_multi", [10 ** 6])
+    out = (ctypes.c_uint32 * 3)()
+    assert planner.leaves_tile(ctypes.byref(a.desc), ctypes.byref(b.desc), (ctypes.c_uint32 * len(leaves))(*leaves), out) == 0
+    return list(out)
+
+
+@pytest.mark.parametrize("rec,leaves,threads", [
+    (["f32"] * 3, [0, 1], 64), (["f32"] * 6, [1, 2, 3, 4], 128), (["f32"] * 6, [0, 1, 2, 3, 4], 192),
+    (["f32"] * 7, range(3), 128), (["f32"] * 7, range(6), 256)])
+def test_narrow_parts_take_few_threads(planner, rec, leaves, threads):
+    """Some leaves of a packed record into SoA: 256 records, and 28 bytes of the
+    leaves per thread in whole waves, rounded up from 20 bytes on and where most
+    of the record is other leaves."""
+    assert _part_of(planner, rec, "aos_packed", 0, list(leaves)) == [1, 256, threads]
