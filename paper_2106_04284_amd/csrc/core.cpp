@@ -1709,7 +1709,12 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             // but two of three, 300 MB, 172 with 128, 155 with 64, and four of
             // six, gathered, 157 with 192, 145 with 128)
             const bool others = other_leaves(rq.src) || other_leaves(rq.dst);
-            while (!others && t2 < 4096 && 2 * t2 * size <= 8192)
+            // (8 KiB of the source's records, which lie in LDS with their
+            // padding and other leaves: one i32 of the aligned mixed record,
+            // 300 MB, 175 us with 256 records, 184 with 1,024 in 57 KiB;
+            // listing 1's aligned part without a leaf 144 with 256, 167 with 512)
+            const uint64_t row = rq.src.lanes ? std::max(size, rq.src.block / rq.src.lanes) : size;
+            while (!others && t2 < 4096 && 2 * t2 * row <= 8192)
                 t2 *= 2;
             const bool up = others && (size >= 20 || (rq.src.lanes && rq.src.block > 2 * size * rq.src.lanes));
             const uint64_t waves = (t2 * size + (up ? 28 * 64 - 1 : 0)) / (28 * 64);

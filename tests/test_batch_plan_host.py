@@ -255,3 +255,12 @@ def test_narrow_parts_take_few_threads(planner, rec, leaves, threads):
     leaves per thread in whole waves, rounded up from 20 bytes on and where most
     of the record is other leaves."""
     assert _part_of(planner, rec, "aos_packed", 0, list(leaves)) == [1, 256, threads]
+
+
+@pytest.mark.parametrize("rec,leaves", [
+    (["f64"] * 3 + ["f32"] * 4 + ["i32"] * 2 + ["u8"], [7]), (["f64"] * 3 + ["f32"] * 6 + ["u8"], [3, 4]),
+    (["u16", "f32", "f32", "f64"] + ["bool"] * 3, [4, 5, 6]), (["u16", "f32", "f32", "f64"] + ["bool"] * 3, [0, 1])])
+def test_parts_of_aligned_records_keep_256(planner, rec, leaves):
+    """Some leaves of an aligned record: the tile is 8 KiB of whole records."""
+    mode, tile, _ = _part_of(planner, rec, "aos_aligned", 0, leaves)
+    assert (mode, tile) == (1, 256)
