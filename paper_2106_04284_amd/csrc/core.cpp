@@ -1714,9 +1714,20 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
             // 300 MB, 175 us with 256 records, 184 with 1,024 in 57 KiB;
             // listing 1's aligned part without a leaf 144 with 256, 167 with 512)
             const uint64_t row = rq.src.lanes ? std::max(size, rq.src.block / rq.src.lanes) : size;
-            while (!others && t2 < 4096 && 2 * t2 * row <= 8192)
+            // Two and more 1-byte leaves in records of whole words keep 256:
+            // the lanes of a wave then read 4 leaves, often bytes of one word,
+            // where more records would have them read one leaf at steps of 16
+            // records, most of them in the same banks (250 MB from AoS: four
+            // u8 145 us with 256, 217 with 2,048; eight 217 and 423; an f32 and
+            // two u8, aligned, 113 and 166)
+            uint64_t bytes1 = 0;
+            for (const Leaf& l : rq.record.leaves)
+                bytes1 += l.size == 1;
+            const bool words = bytes1 >= 2 && rq.src.lanes && rq.src.lanes < 16 && row % 4 == 0;
+            while (!others && !words && t2 < 4096 && 2 * t2 * row <= 8192)
                 t2 *= 2;
-            const bool up = others && (size >= 20 || (rq.src.lanes && rq.src.block > 2 * size * rq.src.lanes));
+            const bool up = others ? size >= 20 || (rq.src.lanes && rq.src.block >= 2 * size * rq.src.lanes)
+                                   : words && 2 * bytes1 > size;
             const uint64_t waves = (t2 * size + (up ? 28 * 64 - 1 : 0)) / (28 * 64);
             p.threads = uint32_t(std::min<uint64_t>(std::max<uint64_t>(waves, 1) * 64, kDefaultThreads));
             p.flags_in |= kPlanDirectStoreOnly;

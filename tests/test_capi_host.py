@@ -963,3 +963,15 @@ def test_large_direct_stores_off_the_grid(rec, off_grid, threads):
     assert (q["stream_stores"], q["threads"]) == off_grid
     assert plan(n + 1, threads=128)["threads"] == 128  # a count that is given stands
     assert not plan(n // 8)["stream_stores"] and not plan(n // 8 + 1)["stream_stores"]
+
+
+@pytest.mark.parametrize("rec,kind,tile,threads", [
+    (["u8"] * 4, "aos_packed", 256, 64), (["u8"] * 8, "aos_packed", 256, 128), (["u8"] * 16, "aos_packed", 256, 192),
+    (["f32", "u8", "u8"], "aos_aligned", 256, 64), (["f32"] + ["u8"] * 4, "aos_packed", 256, 64),
+    (["f32", "u8", "u8"], "aos_packed", 1024, 192), (["f64", "u8"], "aos_aligned", 512, 128), (["u8"] * 3, "aos_packed", 2048, 192)])
+def test_byte_leaves_of_whole_words_keep_256(rec, kind, tile, threads):
+    """Direct stores of two and more 1-byte leaves from records of whole 4-byte
+    words keep 256 records; other records take 8 KiB of them."""
+    r = L.Record(rec)
+    p = L.plan(L.Mapping(r, kind, [10 ** 7]), L.Mapping(r, "soa_multi", [10 ** 7]))
+    assert (p["tile_mode"], p["tile_records"], p["threads"]) == ("direct_store", tile, threads)
