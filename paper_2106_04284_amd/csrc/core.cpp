@@ -1468,7 +1468,16 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
         // records, 1.2 GB, all but one leaf AoSoA32, into SoA: 533 us with 7
         // groups, 459 with 12 and more; mixed records, 8 chunks: 994 with 5,
         // 572 with 8, 506 with 12).
-        const uint64_t least = !(f & kTileVirtualSrc) ? 4 : (f & kTileDirectStore) ? 12 : p.tile.h.slots <= 3 ? 6 : 8;
+        // Direct stores of leaves under 4 bytes read their values one by one:
+        // 8 (listing 1's records from aligned AoS into SoA, 1.8 GB: 1,002 us
+        // with 5 groups, 951 with 6, 915 with 8, 913 with 10 and more; the
+        // mixed record 664 with 4 and 5, 656 with 8).
+        bool narrow = false;
+        for (uint32_t k = 0; k < p.tile.h.num_leaves && (f & kTileDirectStore); k++)
+            narrow = narrow || p.tile.e[k].size < 4;
+        const uint64_t least = (f & kTileVirtualSrc) ? ((f & kTileDirectStore) ? 12 : p.tile.h.slots <= 3 ? 6 : 8)
+                               : narrow              ? 8
+                                                     : 4;
         const uint32_t groups = uint32_t(std::max((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), least));
         p.lds_launch = kHardLdsBytes / groups / 512 * 512;
     }

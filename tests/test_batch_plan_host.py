@@ -76,6 +76,21 @@ extern "C" int gathered(const llama_mapping_desc* src, const llama_mapping_desc*
 }
 """
 
+HELPER += r"""
+extern "C" int aside(const llama_mapping_desc* src, const llama_mapping_desc* dst, uint32_t* out)
+{
+    try {
+        const Plan p = make_plan(make_request(src, nullptr, dst, nullptr, false, false), nullptr);
+        out[0] = p.path == LLAMA_PATH_TILE && (p.tile.h.flags & kTileDirectStore);
+        out[1] = p.lds_bytes;
+        out[2] = p.lds_launch;
+        return 0;
+    } catch (const Error& e) {
+        return e.status;
+    }
+}
+"""
+
 RECORDS = dict(W.RECORDS, small=["u8", "u16"], pair=["f32", "f32"], vec3=[("f32", 3)], vec4=[("f32", 4)])
 
 
@@ -264,3 +279,14 @@ def test_parts_of_aligned_records_keep_256(planner, rec, leaves):
     """Some leaves of an aligned record: the tile is 8 KiB of whole records."""
     mode, tile, _ = _part_of(planner, rec, "aos_aligned", 0, leaves)
     assert (mode, tile) == (1, 256)
+
+
+@pytest.mark.parametrize("rec,kind,groups", [("listing1", "aos_aligned", 8), ("mixed", "aos_aligned", 8), ("lbm", "aos_aligned", 4)])
+def test_direct_stores_of_narrow_leaves_keep_workgroups(planner, rec, kind, groups):
+    """Large direct stores of leaves under 4 bytes leave 8 workgroups a compute
+    unit, others 64 KiB of tiles, at least 4."""
+    n = (5 << 28) // L.Record(RECORDS[rec]).info()[1] // 64 * 64
+    a, b = (L.Mapping(L.Record(RECORDS[rec]), k, [n]) for k in (kind, "soa_multi"))
+    out = (ctypes.c_uint32 * 3)()
+    assert planner.aside(ctypes.byref(a.desc), ctypes.byref(b.desc), out) == 0
+    assert out[0] and out[1] <= 160 * 1024 // groups and out[2] == 160 * 1024 // groups // 512 * 512
