@@ -1127,7 +1127,8 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
                  (aligned || (split_ok && sz >= 2 && sz <= 8));
         split_src = split_src || !aligned;
     }
-    bool off_grid = false; // a direct store whose spans begin off the 16-byte grid
+    // a direct store with spans off the 16-byte grid, or off the 64-byte one
+    bool off_grid = false, off_line = false;
     if (!direct && (p.flags_in & kPlanDirectStoreOnly))
         return false;
     if (!rq.dst_stride.empty() && (!direct || a.dst.mode != kRecordMajor))
@@ -1143,6 +1144,7 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
             TileEntry& e = ta.e[f];
             const uint32_t phase = a.dst.mode == kFieldMajor ? uint32_t((e.dst_addr & 15) / e.size) : 0u;
             off_grid = off_grid || phase != 0;
+            off_line = off_line || ((a.dst.mode == kFieldMajor || !rq.dst_stride.empty()) && e.dst_addr % 64 != 0);
             // the source alignment (kTileSplitSrc)
             const uint32_t rd = log2_move(uint64_t(e.src_pos) | e.size | src_rm_bits);
             e.move = (e.move & ~(7u | kMoveSplit | (0xFFu << 20))) | log2_exact(e.size) | (phase << 20) |
@@ -1411,14 +1413,16 @@ bool fill_tile(const Request& rq, uint32_t T, uint32_t lds_limit, Plan& p)
         if (granules)
             a.flags |= kTileReadsGranules;
     }
-    // Direct stores off the 16-byte grid stay plain: each reaches into two lines
-    // of which its neighbours write the rest, and the L2 merges them unless
-    // the lines leave it at once (AoS into single-blob SoA of an odd number of
-    // records, 1.3 GB: particles 519 us with streaming stores, 461 with plain
-    // ones; 48-byte records 588 and 529; lattice-Boltzmann cells 566 and 501).
-    // Two leaves do not fill the L2 with open lines (two floats, 1.7 GB: 557
-    // and 568).
-    if (total_bytes(rq.dst.blob_size) >= kStreamStoreBytes && !(off_grid && F > 2))
+    // Direct stores off the grid stay plain: a tile's neighbours write the rest
+    // of the lines that its spans begin and end in, and (off the 16-byte grid)
+    // each store reaches into two; the L2 merges them unless the lines leave it
+    // at once (AoS into single-blob SoA, 1.3 GB, odd records: particles 519 us
+    // with streaming stores, 461 with plain ones; 48-byte records 588 and 529;
+    // lattice-Boltzmann cells 566 and 501.  1.5 GB, spans 16 bytes off: six
+    // floats 557 and 521, particles 580 and 525, but on 64 bytes 515 and 526).
+    // Few leaves do not fill the L2 with open lines (two floats, odd, 557 and
+    // 568; four, 16 bytes off, 514 and 524).
+    if (total_bytes(rq.dst.blob_size) >= kStreamStoreBytes && !(off_grid && F > 2) && !(off_line && F > 4))
         a.flags |= kTileStreamStores;
     if (total_bytes(rq.src.blob_size) >= kStreamLoadBytes)
         a.flags |= kTileStreamLoads;
@@ -1448,7 +1452,7 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
     // pieces needs every wave (the 49-byte mixed record from SoA into aligned
     // AoS, 1.3 GB: 428 us with 10 groups, 529 with 5).
     const uint32_t f = p.tile.h.flags;
-    // Plain stores off the 16-byte grid (fill_tile) need them too where a tile
+    // Plain stores off the grid (fill_tile) need them too where a tile
     // of up to 16 KiB has 256 threads (mixed records from aligned AoS into
     // single-blob SoA, 1.9 GB: 677 us with 4 groups, 650 with 8 and more; 128
     // particles per tile and wave: 461 with 18, 493 with 32; lattice-Boltzmann
@@ -1850,7 +1854,7 @@ Plan make_plan_raw(const Request& rq, const llama_copy_options* opt)
         }
         if (ok && !T && !threads && p.write_bytes >= kStreamStoreBytes && (p.tile.h.flags & kTileDirectStore) &&
             !(p.tile.h.flags & kTileStreamStores)) {
-            // plain stores off the 16-byte grid: 256 threads for tiles of 8 KiB
+            // plain stores off the grid: 256 threads for tiles of 8 KiB
             // and more (AoS into single-blob SoA, 1.3 GB: mixed records 518 us
             // with 128 threads, 472 with 256, 48-byte records 529 and 482;
             // 16-byte records, tiles of 4 KiB, 592 and 597 with 64 and 128)

@@ -950,8 +950,9 @@ def test_plan_reports_the_tiles_own_lds(src, dst):
     (["f32"] * 4, (False, 64), 64), (["f32"] * 2, (True, 64), 64)])
 def test_large_direct_stores_off_the_grid(rec, off_grid, threads):
     """Direct stores of 1 GiB and more stream only where every leaf's span
-    starts on the 16-byte grid (or two leaves are open at most); plain ones run
-    256 threads for tiles of 8 KiB and more."""
+    starts on the 16-byte grid (or two leaves are open at most), and with five
+    leaves and more on the 64-byte one; plain ones run 256 threads for tiles of
+    8 KiB and more."""
     r = L.Record(rec)
     n = (5 << 28) // r.info()[1] // 64 * 64
 
@@ -961,6 +962,9 @@ def test_large_direct_stores_off_the_grid(rec, off_grid, threads):
     assert p["tile_mode"] == q["tile_mode"] == "direct_store" and p["tile_records"] == q["tile_records"]
     assert (p["stream_stores"], p["threads"]) == (True, threads)
     assert (q["stream_stores"], q["threads"]) == off_grid
+    for k in (4, 8, 12):
+        assert plan(n + k)["stream_stores"] == (r.info()[0] <= 4)
+    assert plan(n + 16 * 4)["stream_stores"]
     assert plan(n + 1, threads=128)["threads"] == 128  # a count that is given stands
     assert not plan(n // 8)["stream_stores"] and not plan(n // 8 + 1)["stream_stores"]
 
