@@ -1479,9 +1479,14 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
         bool narrow = false;
         for (uint32_t k = 0; k < p.tile.h.num_leaves && (f & kTileDirectStore); k++)
             narrow = narrow || p.tile.e[k].size < 4;
+        // From records at least 14 waves store (1.5 GB from AoS into SoA, 128
+        // threads: 48-byte records 624 us with 5 groups, 533 with 7, 545 with
+        // 12; 80-byte records 575, 551, 550; with 192 threads, lattice-
+        // Boltzmann cells, 543 with 4 and 5, 556 with 6).
+        const uint64_t waves = (f & kTileDirectStore) && p.tile.h.src.mode == kRecordMajor ? 14 : 0;
         const uint64_t least = (f & kTileVirtualSrc) ? ((f & kTileDirectStore) ? 12 : p.tile.h.slots <= 3 ? 6 : 8)
                                : narrow              ? 8
-                                                     : 4;
+                                                     : std::max<uint64_t>((waves * 64 + p.threads - 1) / p.threads, 4);
         const uint32_t groups = uint32_t(std::max((64 * 1024 + tile / 2) / std::max<uint64_t>(tile, 1), least));
         p.lds_launch = kHardLdsBytes / groups / 512 * 512;
     }

@@ -91,7 +91,7 @@ extern "C" int aside(const llama_mapping_desc* src, const llama_mapping_desc* ds
 }
 """
 
-RECORDS = dict(W.RECORDS, small=["u8", "u16"], pair=["f32", "f32"], vec3=[("f32", 3)], vec4=[("f32", 4)])
+RECORDS = dict(W.RECORDS, small=["u8", "u16"], pair=["f32", "f32"], vec3=[("f32", 3)], twelve=[("f32", 12)], vec4=[("f32", 4)])
 
 
 @pytest.fixture(scope="module")
@@ -281,10 +281,11 @@ def test_parts_of_aligned_records_keep_256(planner, rec, leaves):
     assert (mode, tile) == (1, 256)
 
 
-@pytest.mark.parametrize("rec,kind,groups", [("listing1", "aos_aligned", 8), ("mixed", "aos_aligned", 8), ("lbm", "aos_aligned", 4)])
+@pytest.mark.parametrize("rec,kind,groups", [
+    ("listing1", "aos_aligned", 8), ("mixed", "aos_aligned", 8), ("lbm", "aos_aligned", 5), ("twelve", "aos_packed", 7)])
 def test_direct_stores_of_narrow_leaves_keep_workgroups(planner, rec, kind, groups):
     """Large direct stores of leaves under 4 bytes leave 8 workgroups a compute
-    unit, others 64 KiB of tiles, at least 4."""
+    unit, others 64 KiB of tiles and 14 waves from records, at least 4."""
     n = (5 << 28) // L.Record(RECORDS[rec]).info()[1] // 64 * 64
     a, b = (L.Mapping(L.Record(RECORDS[rec]), k, [n]) for k in (kind, "soa_multi"))
     out = (ctypes.c_uint32 * 3)()
