@@ -480,7 +480,8 @@ typedef struct {
                                loads carry the nontemporal hint (sources of 256 MiB or more, the
                                size of the Infinity Cache); bit 1 (LLAMA_HINT_STREAM_STORES) when
                                the destination's 16-byte stores do (TILE, destinations of 1 GiB or
-                               more) */
+                               more, except direct stores of 3 and more leaves off the 16-byte grid,
+                               or 5 and more off the 64-byte one) */
     uint32_t plan_flags;    /* TILE: LLAMA_PLAN_* bits */
     uint32_t source_chunks; /* TILE with LLAMA_PLAN_GATHERED_SOURCE: chunks of one virtual source block */
 } llama_plan_info;

@@ -1454,7 +1454,7 @@ void tile_grid(Plan& p, uint32_t wg_per_cu)
     const uint32_t f = p.tile.h.flags;
     // Plain stores off the grid (fill_tile) need them too where a tile
     // of up to 16 KiB has 256 threads (mixed records from aligned AoS into
-    // single-blob SoA, 1.9 GB: 677 us with 4 groups, 650 with 8 and more; 128
+    // single-blob SoA, 1.7 GB: 677 us with 4 groups, 650 with 8 and more; 128
     // particles per tile and wave: 461 with 18, 493 with 32; lattice-Boltzmann
     // cells, 20 KiB: 501 with 4, 546 with 8).
     const uint64_t tile = p.read_bytes * (uint64_t(1) << p.tile.h.log2_tile) / std::max<uint64_t>(p.tile.h.n, 1);
