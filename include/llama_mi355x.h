@@ -594,10 +594,10 @@ typedef struct {
  *    LLAMA_COPY_* bits.  Every workgroup reserves
  *    the largest item's LDS, so without a fixed tile size each tiled item
  *    takes the largest tile whose plan fits 32 KB of LDS, of at most 12.5 KB
- *    of source (a tile loaded into registers: 100 bytes per thread) and 16
- *    records per thread, with which the batch's copies of these leaves between
- *    these layouts still are 1,024 work units (512
- *    where a tile is stored from registers without an LDS region); but
+ *    of source (a tile loaded into registers: 100 bytes per thread, where that
+ *    leaves 6,144 work units) and 16 records per thread, with which the batch's
+ *    copies of these leaves between these layouts still are 1,024 work units
+ *    (512 where a tile is stored from registers without an LDS region); but
  *    256 records in any case, and no larger than the item (the tuning cache,
  *    which is measured on standalone launches, is not used).  Without a thread
  *    count, a batch whose items all hold at most 128 KB (their destination's

@@ -107,9 +107,10 @@ constexpr uint32_t kBatchTileBytes = 12800;
 // packed) runs 128 threads per workgroup unless the caller gives a count
 constexpr uint64_t kBatchSmallItemBytes = 128 * 1024;
 // work units that a class of a batch's copies must have left for tiles of more
-// than 256 records (direct stores: fewer), and that a batch must have for half
-// the threads to pay for small items (see batch_plan, BatchUnits::threads)
-constexpr uint64_t kBatchTileUnits = 1024, kBatchStoreUnits = 512, kBatchThreadUnits = 1536;
+// than 256 records (direct stores: fewer; tiles of more than kBatchTileBytes:
+// more), and that a batch must have for half the threads to pay for small items
+// (see batch_plan, BatchUnits::threads)
+constexpr uint64_t kBatchTileUnits = 1024, kBatchStoreUnits = 512, kBatchWideUnits = 6144, kBatchThreadUnits = 1536;
 
 // How a table runs: one workgroup per work unit when its items share one LDS
 // class, else a persistent grid (see create_batch).

@@ -201,6 +201,10 @@ def test_small_batches_keep_small_tiles(planner):
         assert table("listing1", [10 ** 4] * 60) == ({512}, 256)
         assert table("listing1", [10 ** 4] * 25, A, S) == ({256}, 256)
         assert table("listing1", [10 ** 4] * 26, A, S) == ({512}, 256)
+        assert table("mixed", [10 ** 6] * 3) == ({256}, 256)       # tiles of 25 KB: 5,860 units of 512
+        assert table("mixed", [10 ** 6] * 4) == ({512}, 256)       # 7,816
+        assert table("listing1", [10 ** 6] * 6) == ({512}, 256)    # tiles of 21.5 KB: 5,862 units of 1,024; 10.7 KB fit
+        assert table("listing1", [10 ** 6] * 7) == ({1024}, 256)
         assert table("particle", [1000] * 150) == ({256}, 256)     # 600 units, 28,000 bytes each
         assert table("particle", [256] * 150) == ({256}, 128)      # 7,168 bytes each
 
