@@ -595,7 +595,8 @@ typedef struct {
  *    the largest item's LDS, so without a fixed tile size each tiled item
  *    takes the largest tile whose plan fits 32 KB of LDS, of at most 12.5 KB
  *    of source (a tile loaded into registers: 100 bytes per thread, where that
- *    leaves 6,144 work units) and 16 records per thread, with which the batch's
+ *    leaves 6,144 work units, three of four in the batch) and 16 records per
+ *    thread, with which the batch's
  *    copies of these leaves between these layouts still are 1,024 work units
  *    (512 where a tile is stored from registers without an LDS region); but
  *    256 records in any case, and no larger than the item (the tuning cache,

@@ -147,10 +147,14 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // that the units of the batch's copies of the class allow are part of it
         const BatchUnits::Units* units = sizes ? &sizes->of(rq) : nullptr;
         auto units_fit = [&](uint32_t T, uint64_t least) { return !units || (*units)[__builtin_ctz(T)] >= least; };
+        auto wide_fit = [&](uint32_t T) {
+            const uint32_t b = __builtin_ctz(T);
+            return !units || ((*units)[b] >= kBatchWideUnits && 4 * (*units)[b] >= 3 * sizes->all[b]);
+        };
         TuneKey k = class_key(rq);
         for (uint32_t T = 512; T <= 4096 && !lds_budget; T *= 2)
             k.bucket += uint32_t(units_fit(T, kBatchStoreUnits)) + 5 * uint32_t(units_fit(T, kBatchTileUnits)) +
-                        25 * uint32_t(units_fit(T, kBatchWideUnits));
+                        25 * uint32_t(wide_fit(T));
         const auto key = std::make_tuple(k, threads, flags | (lds_budget << 8));
         uint32_t start = 4096;
         {
@@ -170,11 +174,13 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
         // threads hold the tile in registers, takes up to 100 bytes per thread
         // (20 arrays of 10^6, SoA into AoS, 256 threads: listing 1's record
         // 276 us with 256 records, 183 with 512, 160 with 1,024; the mixed
-        // record 397 with 256, 370 with 512), where it leaves four rounds of
-        // workgroups: 6 of its 25 KB fit a compute unit, and a last round of
-        // few costs more (mixed records from single-blob SoA into AoS, 1.6 10^6:
-        // 47.6 us in 6,300 units of 256, 51.8 in 3,150 of 512; 6 10^6: 130.2 in
-        // 23,400, 124.7 in 11,700).  A class of copies that would
+        // record 397 with 256, 370 with 512), where its class is most of the
+        // batch and is left four rounds of workgroups: 6 of its 25 KB fit a
+        // compute unit, a last round of few costs more (mixed records from
+        // single-blob SoA into AoS, 1.6 10^6: 47.6 us in 6,300 units of 256,
+        // 51.8 in 3,150 of 512; 6 10^6: 130.2 in 23,400, 124.7 in 11,700), and
+        // so does that LDS for smaller tiles of the same mode (the 250 arrays:
+        // 1,585 us with both sizes, 1,531 with 256).  A class of copies that would
         // have too few units keeps smaller tiles: they run side by side, and the
         // longest decides (SoA into AoS, arrays of 10^4: 60 of {f32 x 3} 5.7 us in
         // 2,400 units, 6.2 in 600, 100 of them 8.0 in 4,000, 7.6 in 1,000; 30
@@ -191,7 +197,7 @@ Plan batch_plan(const Request& rq, uint32_t threads, uint32_t tile_records, uint
             return lds_budget || T <= 256 ||
                    (T <= 16 * threads && units_fit(T, least) &&
                     (bytes <= kBatchTileBytes ||
-                     ((mode & kTileDirectLoad) && bytes <= 100 * threads && units_fit(T, kBatchWideUnits))));
+                     ((mode & kTileDirectLoad) && bytes <= 100 * threads && wide_fit(T))));
         };
         while (!bytes_fit(start, kTileDirectStore | kTileDirectLoad))
             start /= 2;

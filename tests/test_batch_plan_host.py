@@ -105,8 +105,8 @@ def planner(tmp_path_factory):
     return ctypes.CDLL(str(so))
 
 
-def _items(rec, src, dst, counts):
-    r, at, out = L.Record(RECORDS[rec]), 1 << 40, []
+def _items(rec, src, dst, counts, at=1 << 40):
+    r, out = L.Record(RECORDS[rec]), []
     for n in counts:
         sides = []
         for kind, lanes in (src, dst):
@@ -295,3 +295,18 @@ def test_direct_stores_of_narrow_leaves_keep_workgroups(planner, rec, kind, grou
     out = (ctypes.c_uint32 * 3)()
     assert planner.aside(ctypes.byref(a.desc), ctypes.byref(b.desc), out) == 0
     assert out[0] and out[1] <= 160 * 1024 // groups and out[2] == 160 * 1024 // groups // 512 * 512
+
+
+def test_wide_tiles_where_they_are_most_of_the_batch(planner):
+    """Tiles of more than 12.5 KB raise the LDS of their mode's whole launch:
+    they are taken only where their class is three of four units."""
+    def tile(rec, src, big, others):
+        one, two = _items(rec, src, A, [10 ** 6] * big), _items("particle", A, S, [10 ** 6] * others, 1 << 44)
+        n = big + others
+        arr = (type(one.arr[0]) * n)(*([one.arr[k] for k in range(big)] + [two.arr[k] for k in range(others)]))
+        th, tiles = ctypes.c_uint32(), (ctypes.c_uint32 * n)()
+        assert planner.batch_table(ctypes.c_size_t(n), arr, None, ctypes.byref(th), tiles) == 0
+        return set(tiles)
+    for _ in range(2):
+        assert tile("mixed", S, 9, 3) == {256, 512}  # the particles keep 256
+        assert tile("mixed", S, 9, 4) == {256}
